@@ -118,10 +118,12 @@ __device__ inline void static_for(F&& f) {
 
 // MODE 0: any filter size; 1: 1x1 unpadded (no tap bookkeeping); 2: 1x1 with a second source tensor;
 // 4: any filter size, followed by the expansion tail (ConvArgs::tail_*) on the block's output tile.
-template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_kernel(const ConvArgs a) {
+// STAGES 2: double-buffered operand tiles; more: a ring of that many (see RING below).
+template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0>
+__global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_kernel(const ConvArgs a) {
     constexpr bool ONE = MODE == 1 || MODE == 2, DUAL = MODE == 2;
-    constexpr int NT = 64 * WAVES_M * WAVES_N;  // threads per block
+    constexpr int NW = WAVES_M * WAVES_N;       // wavefronts that multiply
+    constexpr int NT = PROD ? 64 * PROD : 64 * NW;  // threads that load: all, or PROD wavefronts that do nothing else (ring)
     constexpr int BK = BKB / (int)sizeof(T);   // K elements per tile row
     constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
     constexpr int CPR = BKB / 16;              // 16-byte chunks per tile row
@@ -134,23 +136,33 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_kernel(cons
     // rows at one logical chunk fall on 16 different 16-byte slots modulo 256 bytes (and any 8 aligned rows on 8 modulo 128).
     constexpr bool DIRECT = BKB == 128;
     constexpr int LDS_ROW = DIRECT ? BKB : BKB + 16;   // staged path: padded row pitch (an odd multiple of 16 bytes)
+    constexpr bool RING = STAGES > 2;
+    static_assert(RING || PROD == 0, "loading wavefronts exist with the ring only");
+    static_assert(!RING || DIRECT, "the ring holds direct-to-LDS tiles");
     constexpr int KK = BKB / 32;               // MFMA k-steps per tile row (32 bytes = 2 lane halves x 16 bytes)
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wavefront tile (pixels x channels)
-    constexpr int TM = WM / 32, TN = WN / 32;  // 32x32 MFMA tiles per wavefront
+    // F16 (fp32 ring): a wavefront owns one 16x16 tile instead, so that four times as many wavefronts share the work of a
+    // short call; the contraction takes its k in the order of the 32x32 tiles.
+    constexpr bool F16 = WM == 16 && WN == 16;
+    static_assert(!F16 || (std::is_same<T, float>::value && std::is_same<OutT, float>::value && STAGES > 2), "16x16 tiles: fp32 ring only");
+    constexpr int TM = F16 ? 1 : WM / 32, TN = F16 ? 1 : WN / 32;  // 32x32 MFMA tiles per wavefront
     constexpr int LPP = WN / 8;                // epilogue: lanes per pixel (8 channels each)
     constexpr int PPI = 64 / LPP;              // epilogue: pixels per wavefront instruction
     constexpr int NIT = 32 / PPI;              // epilogue: instructions per 32-pixel sub-tile
     constexpr int EPITCH = WN * 4 + 16;        // epilogue: padded fp32 row pitch in LDS (bytes)
     constexpr bool PREFETCH_RES = TM * NIT <= 8;  // residual tile small enough to hold across the K loop
-    static_assert(WAVES_M * WAVES_N * 32 * EPITCH <= 2 * (BN + BM) * LDS_ROW, "epilogue tile must fit in the pipeline buffers");
+    static_assert(WAVES_M * WAVES_N * 32 * EPITCH <= STAGES * (BN + BM) * LDS_ROW, "epilogue tile must fit in the pipeline buffers");
     static_assert(!DIRECT || (CPR == 8 && (NT / 64) % 2 == 0), "direct loads: 8 chunks per row, an even number of wavefronts");
     static_assert(BM % RPP == 0 && BN % RPP == 0, "tile rows must be a multiple of the rows staged per pass");
 
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* sA = smem;                     // [2][BN][LDS_ROW]
-    unsigned char* sB = smem + 2 * BN * LDS_ROW;  // [2][BM][LDS_ROW]
+    unsigned char* sA = smem;                          // [STAGES][BN][LDS_ROW]
+    unsigned char* sB = smem + STAGES * BN * LDS_ROW;  // [STAGES][BM][LDS_ROW]
 
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int lane = threadIdx.x & 63, wave = RING ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    const bool loads = PROD == 0 || wave >= NW;      // this wavefront requests operand tiles
+    const bool multiplies = PROD == 0 || !loads;
+    const int wv = PROD && loads ? wave - NW : wave, t = wv * 64 + lane;             // position among the wavefronts of its kind
     const int wm = wv % WAVES_M, wn = wv / WAVES_M;
     const int HoWo = a.Ho * a.Wo;
     const int M = a.N * HoWo;
@@ -162,7 +174,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_kernel(cons
     const int per_xcd = (total_tiles + 7) >> 3;
     const int tile = (int)(blockIdx.x & 7u) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= total_tiles) return;
-    const int tile_n = tile % tiles_n, tile_m = tile / tiles_n;
+    // (ring: with fewer pixels than output channels an XCD's range walks the pixel tiles of one channel tile first, so
+    // that the larger operand, the weights, is read by one XCD only instead of by all eight)
+    const int tiles_m = (M + BM - 1) / BM;
+    const bool pixels_first = RING && M < a.Cout;
+    const int tile_n = pixels_first ? tile / tiles_m : tile % tiles_n, tile_m = pixels_first ? tile % tiles_m : tile / tiles_n;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
     const T* __restrict__ in = static_cast<const T*>(a.in);
@@ -183,7 +199,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_kernel(cons
         a_ok[p] = n < a.Cout;
         a_base[p] = (size_t)(a_ok[p] ? n : 0) * K + (size_t)lchunk * EPC;
     }
-    if constexpr (DIRECT) {
+    if (DIRECT && loads) {
         unsigned char* dA0 = sA + (size_t)((wv * 64) / CPR) * LDS_ROW;
 #pragma unroll
         for (int p = 0; p < PA; ++p) load_to_lds16(wgt + a_base[p], dA0 + (size_t)(RPP * p) * LDS_ROW);
@@ -343,7 +359,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_kernel(cons
     const bool vec = (a.out1 == nullptr) && ((a.Cout & 7) == 0) && ((a.ld0 & 7) == 0);
     const T* __restrict__ res = static_cast<const T*>(a.res);
     Vec8<T> rres[PREFETCH_RES ? TM * NIT : 1];
-    if (PREFETCH_RES && vec && res != nullptr) {  // residual tile: issued now, consumed after the K loop
+    if (PREFETCH_RES && multiplies && vec && res != nullptr) {  // residual tile: issued now, consumed after the K loop
 #pragma unroll
         for (int j = 0; j < TM; ++j)
 #pragma unroll
@@ -388,7 +404,168 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_kernel(cons
     // address unit takes ~20 cycles per 1 KiB instruction and a wavefront issues in order - but spreading the
     // loads between the MFMAs of the step, pinned with scheduling barriers, was measured 3-8 % slower, also
     // with the two wavefronts of a SIMD taking turns.)
-    if constexpr (DIRECT) {
+    if constexpr (RING) {
+        // Ring of STAGES operand tiles, STAGES - 1 of them requested ahead: a call with few pixels has no more than one or
+        // two blocks per CU, so the time of a K step is the latency of its operands (0.65 us from L2 with one tile in
+        // flight) unless several tiles are in flight.  The order of the sums is the two-buffer loop's: same values bit for bit.
+        // PROD wavefronts do nothing but request tiles: issued by the multiplying wavefronts the requests stand in line with
+        // their fragment reads and products (300 x 1024, K 12544: 128 us with two buffers, 60 with the ring, 39 / 32 with two /
+        // four loading wavefronts; the ring's depth beyond 4 changes nothing).
+        // Step kt: the fragments of tile kt are in registers; tile kt + 1 is waited for (the newest STAGES - 2 tiles may
+        // still be on their way; loads complete in order), and past the barrier every wavefront has tile kt in registers,
+        // so its buffer takes tile kt + STAGES while the fragments of kt + 1 are read under the products of kt.
+        constexpr int PER_TILE = PA + PB;                       // requests of one thread per tile
+        constexpr int LEFT = (STAGES - 2) * PER_TILE;           // requests that may be outstanding when the next tile is needed
+        static_assert(LEFT < 64, "vmcnt counts to 63");
+        constexpr int WAIT_LEFT = 0x0070 | (LEFT & 15) | ((LEFT >> 4) << 14);   // vmcnt(LEFT) lgkmcnt(0)
+        int q_kt = 0, q_c = 0, q_kx = 0, q_tap = 0;
+        long long q_off = 0;                                    // element offset of (tap, first channel) from the pixel's tap 0
+        const int kt1 = DUAL ? a.Cin / BK : 0;
+        auto request = [&](int buf) {                           // next tile in K order into buffer buf
+            unsigned char* dA = sA + (size_t)(buf * BN + (wv * 64) / CPR) * LDS_ROW;
+            unsigned char* dB = sB + (size_t)(buf * BM + (wv * 64) / CPR) * LDS_ROW;
+#pragma unroll
+            for (int p = 0; p < PB; ++p) {
+                const T* src;
+                if constexpr (ONE) {
+                    src = (!DUAL || q_kt < kt1) ? in + b_base[p] + (size_t)q_kt * BK : in2 + b_base2[DUAL ? p : 0] + (size_t)(q_kt - kt1) * BK;
+                } else {
+                    const bool ok = (b_taps[ONE ? 0 : p] >> q_tap) & 1u;
+                    src = ok ? in + (b_off0[ONE ? 0 : p] + q_off) : reinterpret_cast<const T*>(g_zero_page);
+                }
+                load_to_lds16(src, dB + (size_t)(RPP * p) * LDS_ROW);
+            }
+            if (q_kt > 0) {
+#pragma unroll
+                for (int p = 0; p < PA; ++p) load_to_lds16(wgt + a_base[p] + (size_t)q_kt * BK, dA + (size_t)(RPP * p) * LDS_ROW);
+            }
+            ++q_kt;
+            if constexpr (!ONE) {
+                q_off += BK;
+                if (++q_c == cin_tiles) {                       // next tap: along the filter row, then to the next input row
+                    q_c = 0;
+                    ++q_tap;
+                    if (++q_kx == a.kw) { q_kx = 0; q_off += (long long)(a.W - a.kw) * a.Cin; }
+                }
+            }
+        };
+        auto barrier = [&]() {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+        auto landed = [&](bool steady) {                        // what this thread requested of the next tile has arrived
+            asm volatile("" ::: "memory");
+            if (steady) __builtin_amdgcn_s_waitcnt(WAIT_LEFT);
+            else __builtin_amdgcn_s_waitcnt(0x0070);            // the last tiles: vmcnt(0) lgkmcnt(0)
+        };
+        if (loads) {
+#pragma unroll
+            for (int s = 0; s < STAGES - 1; ++s)
+                if (s < KT) request(s);
+        }
+        if (PROD && loads) {
+            landed(KT >= STAGES - 1);
+            barrier();
+            if (STAGES - 1 < KT) request(STAGES - 1);
+            int buf = 0;
+            for (int kt = 0; kt + 1 < KT; ++kt) {
+                landed(kt + STAGES - 1 < KT);
+                barrier();
+                if (kt + STAGES < KT) request(buf);
+                buf = buf + 1 == STAGES ? 0 : buf + 1;
+            }
+            barrier();                                          // the one in front of the epilogue
+            return;
+        }
+        struct TileFrags { Frags k[KK]; };
+        TileFrags g0, g1;
+        f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};
+        auto read_tile = [&](int buf, TileFrags& g) {
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                if constexpr (F16) {
+                    // lane group g = lane / 16 supplies k slot g: k = 0, 4, 1, 5 of the 8-wide group, then 2, 6, 3, 7
+                    const int row = lane & 15, koff = ((2 * kk + ((lane >> 4) & 1)) ^ (row & 7) ^ (row >> 3)) * 16;
+                    g.k[kk].a[0] = *reinterpret_cast<const u32x4_t*>(sA + (size_t)(buf * BN + wn * WN + row) * LDS_ROW + koff);
+                    g.k[kk].b[0] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + row) * LDS_ROW + koff);
+                } else {
+                    read_frags(buf, kk, g.k[kk]);
+                }
+            }
+        };
+        auto mma_tile = [&](const TileFrags& g) {
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                if constexpr (F16) {
+                    // (16-byte reads, half of each used: two 4-byte reads per lane conflict in the banks, 360 against 292 us)
+                    const f32x4_t fa = __builtin_bit_cast(f32x4_t, g.k[kk].a[0]), fb = __builtin_bit_cast(f32x4_t, g.k[kk].b[0]);
+                    const bool odd = lane >= 32;
+                    acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? fa.y : fa.x, odd ? fb.y : fb.x, acc4, 0, 0, 0);
+                    acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? fa.w : fa.z, odd ? fb.w : fb.z, acc4, 0, 0, 0);
+                } else {
+                    mma_frags(g.k[kk]);
+                }
+            }
+        };
+        auto in_registers = [&](bool steady) {                  // the fragments read last are in registers
+            if constexpr (PROD == 0) {
+                landed(steady);
+            } else {
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_waitcnt(0xc07f);             // lgkmcnt(0)
+            }
+        };
+        in_registers(KT >= STAGES - 1);
+        barrier();                                              // tile 0 has landed
+        if (PROD == 0 && STAGES - 1 < KT) request(STAGES - 1);
+        read_tile(0, g0);
+        int buf = 0;                                            // buffer of tile kt
+        auto step = [&](int kt, const TileFrags& now, TileFrags& next) {
+            if (kt + 1 < KT) {
+                in_registers(kt + STAGES - 1 < KT);
+                barrier();
+                if (PROD == 0 && kt + STAGES < KT) request(buf);
+                buf = buf + 1 == STAGES ? 0 : buf + 1;
+                read_tile(buf, next);
+            }
+            mma_tile(now);
+        };
+        for (int kt = 0; kt < KT; kt += 2) {
+            step(kt, g0, g1);
+            if (kt + 1 < KT) step(kt + 1, g1, g0);
+        }
+        // (a wavefront's epilogue region lies in other wavefronts' operand tiles)
+        in_registers(false);
+        barrier();
+        if constexpr (F16) {
+            // accumulator element e of lane l: channel 4 (l / 16) + e, pixel l % 16
+            const int pix = m0 + wm * WM + (lane & 15), ch = n0 + wn * WN + 4 * (lane >> 4);
+            if (pix >= M) return;
+            float* o0 = static_cast<float*>(a.out0);
+            float* o1 = static_cast<float*>(a.out1);
+            const float* r0 = static_cast<const float*>(a.res);
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool in_range = ch + e < a.Cout;
+                v[e] = acc4[e] + (in_range ? a.bias[ch + e] : 0.f);
+                if (r0 && in_range) v[e] += r0[(size_t)pix * a.Cout + ch + e];
+                if (a.relu) v[e] = fmaxf(v[e], 0.f);
+            }
+            if (o1 == nullptr && (a.Cout & 3) == 0 && (a.ld0 & 3) == 0) {
+                if (ch < a.Cout) store4(o0 + (size_t)pix * a.ld0 + ch, v);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int c = ch + e;
+                    if (c < a.n_split) { if (c < a.Cout) o0[(size_t)pix * a.ld0 + c] = v[e]; }
+                    else if (c < a.Cout) o1[(size_t)pix * a.ld1 + (c - a.n_split)] = v[e];
+                }
+            }
+            return;
+        }
+    } else if constexpr (DIRECT) {
         // Two LDS buffers: tile kt + 1 is requested as soon as every wavefront has finished reading its buffer (the
         // barrier that ends step kt - 1) and has the whole of step kt to arrive.
         // The fragments of k-step kk + 1 are read while k-step kk is multiplied, and the barrier sits in front of a
@@ -806,14 +983,14 @@ bool conv_supported(const ConvArgs& a, int precision) {
     return true;
 }
 
-template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT>
+template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0>
 static hipError_t launch_cfg(const ConvArgs& a, hipStream_t s) {
     // (the expansion tail parks an unpadded 256 x 512-byte tile and gives each of the 8 wavefronts 4 KB beside it: the CU's whole LDS)
-    const size_t pipe = (size_t)2 * (BN + BM) * (BKB == 128 ? BKB : BKB + 16);
+    const size_t pipe = (size_t)STAGES * (BN + BM) * (BKB == 128 ? BKB : BKB + 16);
     // (the fused-predictor path of the large bf16 tile parks a padded 256 x 528-byte tile, more than the two pipeline buffers)
     const size_t heads = (std::is_same<T, bf16_t>::value && BM == 256 && BN == 256 && MODE == 0) ? (size_t)BM * (BN * 2 + 16) : 0;
     const size_t lds = MODE == 4 ? (size_t)160 * 1024 : (pipe > heads ? pipe : heads);
-    auto kern = conv_igemm_kernel<T, BM, BN, BKB, WAVES_M, WAVES_N, MODE, OutT>;
+    auto kern = conv_igemm_kernel<T, BM, BN, BKB, WAVES_M, WAVES_N, MODE, OutT, STAGES, PROD>;
     {
         hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
         if (e != hipSuccess) return e;
@@ -822,19 +999,19 @@ static hipError_t launch_cfg(const ConvArgs& a, hipStream_t s) {
     const long long tiles = ((M + BM - 1) / BM) * ((a.Cout + BN - 1) / BN);
     if (tiles <= 0 || tiles >= (1ll << 30)) return hipErrorInvalidValue;
     const long long grid = ((tiles + 7) / 8) * 8;  // 8 XCDs x equal ranges; surplus workgroups exit at once
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WAVES_M * WAVES_N), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * (WAVES_M * WAVES_N + PROD)), lds, s, a);
     return hipGetLastError();
 }
 
 // 1x1 unpadded convolutions (and the FC layers) get the variant without filter-tap bookkeeping.
-template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, typename OutT, bool ALLOW_DUAL = false>
+template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, typename OutT, bool ALLOW_DUAL = false, int STAGES = 2, int PROD = 0>
 static hipError_t launch_one(const ConvArgs& a, hipStream_t s) {
     if (a.in2 != nullptr) {
-        if constexpr (ALLOW_DUAL) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 2, OutT>(a, s);
+        if constexpr (ALLOW_DUAL) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 2, OutT, STAGES, PROD>(a, s);
         else return hipErrorInvalidValue;
     }
-    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 1, OutT>(a, s);
-    return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 0, OutT>(a, s);
+    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 1, OutT, STAGES, PROD>(a, s);
+    return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 0, OutT, STAGES, PROD>(a, s);
 }
 
 bool conv_tail_supported(const ConvArgs& a, int precision) {
@@ -844,6 +1021,64 @@ bool conv_tail_supported(const ConvArgs& a, int precision) {
     if (a.Cout != 256 || !a.relu || a.res != nullptr || a.out1 != nullptr || a.in2 != nullptr || a.head_w != nullptr) return false;
     const long long M = (long long)a.N * a.Ho * a.Wo;
     return M * a.tail_n < (1ll << 31);
+}
+
+// Tiles of bm x bn, in rounds of one block per CU.
+static long long tile_rounds(const ConvArgs& a, int bm, int bn) {
+    const long long M = (long long)a.N * a.Ho * a.Wo;
+    return (((M + bm - 1) / bm) * ((a.Cout + bn - 1) / bn) + 255) / 256;
+}
+
+// Smallest tile, with four loading wavefronts for 1x1 layers (32.3 us against 38.7 with two at 300 x 1024, K 12544) and two
+// for the others (17.4 against 19.1 at 510 x 512, K 4608).
+static hipError_t launch_ring_32x64(const ConvArgs& a, hipStream_t s) {
+    if (a.in2 != nullptr) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 2, bf16_t, 6, 4>(a, s);
+    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 1, bf16_t, 6, 4>(a, s);
+    return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 0, bf16_t, 6, 2>(a, s);
+}
+
+// Calls with few pixels.  A 128 x 128 tile takes 0.64 us per K step (64 bf16 / 32 fp32 of every row) however few blocks
+// there are, because a block waits for the one tile it has in flight; the ring tiles take, per K step and round of 256
+// blocks: 32 x 64 0.16 us, 64 x 64 0.24, 64 x 128 0.31, 128 x 128 0.49 (measured at K 12544).  The rule takes the
+// cheapest by that count.  Measured in us, two-buffer tile / ring tile: 300 x 1024, K 12544: 128 / 32 (32 x 64);
+// 900: 212 / 47 (64 x 64); 1500: 212 / 67 (64 x 128); 2400: 212 / 98 (128 x 128); 3x3 256 -> 256: 2 040 pixels
+// 24.6 / 10.8, 8 160 26 / 17.5; 3x3 512 -> 512: 510 pixels 45 / 17.4, 4 080 55 / 30, 8 160 60 / 47.  More than 256 tiles
+// of 128 x 128 run two blocks per CU and overlap each other: no ring tile is faster there.  Below K 512 (768 for the
+// 128 x 128 ring) the time is set-up and epilogue and one block per CU hides neither.  Returns false if no ring tile pays.
+static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipError_t* e) {
+    if (K < 256 || a.out1 != nullptr) return false;
+    const bool narrow = a.Cout <= 64;
+    if (narrow ? tile_rounds(a, 64, 64) > 1 : tile_rounds(a, 128, 128) > 1) return false;
+    const long long c32 = 16 * tile_rounds(a, 32, 64), c64 = 24 * tile_rounds(a, 64, 64);
+    const long long c64w = K >= 512 && !narrow ? 31 * tile_rounds(a, 64, 128) : 1000, c128 = K >= 768 && !narrow ? 49 : 1000;
+    const long long best = c32 < c64 ? c32 : c64, wide = c64w < c128 ? c64w : c128;
+    if ((best < wide ? best : wide) >= 64) return false;
+    if (best <= wide) *e = c32 < c64 ? launch_ring_32x64(a, s) : launch_one<bf16_t, 64, 64, 128, 2, 2, bf16_t, true, 5, 4>(a, s);
+    else *e = c64w <= c128 ? launch_one<bf16_t, 64, 128, 128, 2, 2, bf16_t, true, 3, 4>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, bf16_t, true, 4, 4>(a, s);
+    return true;
+}
+
+// fp32: the fp32 matrix instructions bound every tile (1024 cycles per K step of a 64 x 64 tile), so what counts is how many
+// SIMDs share the work.  Per K step and round of 256 blocks: 128 x 128 2.07 us, 128 x 64 1.5, 64 x 64 ring 0.57, 32 x 32
+// ring (16x16 matrix tiles, four wavefronts) 0.33.  Measured in us, 128 x 128 / 64 x 64 / 32 x 32: 200 x 1024, K 12544:
+// 815 / 223 / 130; 600 x 1024: 819 / 226 / 292; 3x3 256 -> 256, 1 024 pixels 162 / 49 / 29, 4 096 163 / 53 / 74,
+// 16 320 168 / 161 / 280.
+static hipError_t launch_fp32(const ConvArgs& a, hipStream_t s) {
+    const bool narrow = a.Cout <= 64;
+    const long long c32 = 33 * tile_rounds(a, 32, 32), c64 = 57 * tile_rounds(a, 64, 64);
+    const long long base = narrow ? 150 * tile_rounds(a, 128, 64) : 207 * tile_rounds(a, 128, 128);
+    if (c32 < c64 && c32 < base) return launch_one<float, 32, 32, 128, 2, 2, float, true, 8, 4>(a, s);
+    if (c64 < base) return launch_one<float, 64, 64, 128, 2, 2, float, true, 5, 4>(a, s);
+    return narrow ? launch_one<float, 128, 64, 128, 2, 2, float>(a, s) : launch_one<float, 128, 128, 128, 2, 2, float, true>(a, s);
+}
+
+// fp32 outputs of bf16 tensors (the predictors, at most a few channel tiles wide): the general epilogue's time goes with the
+// tile.  Measured, 128-pixel tile / ring: 75 channels, K 256: 300 pixels 17.3 / 5.7 us (32 x 64), 16 320 17.5 / 8.2 and
+// 32 640 18.3 / 14.2 (64 x 64); 55 channels, K 1024, 4 800 rows: 15.5 / 7.5.
+static hipError_t launch_out_f32(const ConvArgs& a, hipStream_t s) {
+    if (tile_rounds(a, 32, 64) <= 1) return launch_one<bf16_t, 32, 64, 128, 1, 2, float, false, 6, 4>(a, s);
+    if (tile_rounds(a, 64, 64) <= 4) return launch_one<bf16_t, 64, 64, 128, 2, 2, float, false, 5, 4>(a, s);
+    return a.Cout <= 64 ? launch_one<bf16_t, 128, 64, 128, 2, 2, float>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, float>(a, s);
 }
 
 hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream_t s) {
@@ -857,10 +1092,8 @@ hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream
         return launch_one<bf16_t, 256, 256, 128, 2, 4, bf16_t, true>(a, s);
     }
     const bool narrow = a.Cout <= 64;
-    if (precision == 0) {
-        return narrow ? launch_one<float, 128, 64, 128, 2, 2, float>(a, s) : launch_one<float, 128, 128, 128, 2, 2, float, true>(a, s);
-    }
-    if (out_f32) return narrow ? launch_one<bf16_t, 128, 64, 128, 2, 2, float>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, float>(a, s);
+    if (precision == 0) return launch_fp32(a, s);
+    if (out_f32) return launch_out_f32(a, s);
     // Long-K layers are bound by L2 -> CU bandwidth with a 128 x 128 tile (64 flop per byte staged); a
     // 256 x 256 tile halves that traffic.  It runs with 8 wavefronts (128 x 64 each), so that one block per
     // CU still keeps two wavefronts per SIMD, and with 128-byte K rows, which doubles the bytes in flight
@@ -878,10 +1111,15 @@ hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream
         // flight, so they take the small-footprint 128 x 64 tile (4 blocks of 4 wavefronts per CU).
         if (K <= 128 && a.out1 == nullptr && a.in2 == nullptr) return launch_one<bf16_t, 128, 64, 64, 2, 2, bf16_t>(a, s);
         const long long tiles_l = ((M + 255) / 256) * ((a.Cout + 255) / 256);
+        hipError_t e;
+        if (tiles_l < 200 && launch_ring_bf16(a, K, s, &e)) return e;
         // Very long K with a tile count that leaves CUs idle in a single round (the first FC layer: 152 tiles of
-        // 256 x 256 on 256 CUs): 192-pixel tiles give 200 tiles of 3/4 the work each.
+        // 256 x 256 on 256 CUs): 192-pixel tiles give 200 tiles of 3/4 the work each.  Up to two 128 x 128 tiles per CU the
+        // pair is faster than one large tile on part of the CUs (4 800 x 1024, K 12544: 175 against 213 us; 8 000: 209 / 224;
+        // 9 600, 600 tiles: 347 / 278).
         const long long tiles_192 = ((M + 191) / 192) * ((a.Cout + 255) / 256);
-        if (a.Cout % 256 == 0 && K >= 8192 && tiles_l < 200 && tiles_192 <= 256 && tiles_192 > tiles_l && a.out1 == nullptr && a.in2 == nullptr)
+        if (a.Cout % 256 == 0 && K >= 8192 && tiles_l < 200 && tiles_192 <= 256 && tiles_192 > tiles_l && tile_rounds(a, 128, 128) > 2 &&
+            a.out1 == nullptr && a.in2 == nullptr)
             return launch_one<bf16_t, 192, 256, 128, 2, 4, bf16_t>(a, s);
         if (a.Cout % 256 == 0 && (K >= 512 || (a.in2 != nullptr && K >= 384)) && (tiles_l >= 200 || (tiles_l >= 150 && K >= 8192)) && a.out1 == nullptr)
             return launch_one<bf16_t, 256, 256, 128, 2, 4, bf16_t, true>(a, s);

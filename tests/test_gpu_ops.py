@@ -71,6 +71,43 @@ def test_conv_op_matches_oracle(precision, case):
         assert relerr(got, ref) <= tol, (case, use_res, relu, out_f32, relerr(got, ref))
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("case", [
+    dict(H=1, W=1, Cin=256, Cout=256, k=1, stride=1, pad=0),       # K tiles: 4 bf16, fewer than the ring holds; 8 fp32
+    dict(H=1, W=1, Cin=320, Cout=200, k=1, stride=1, pad=0),       # odd tile count, ragged channels, fewer pixels than channels
+    dict(H=1, W=1, Cin=1024, Cout=55, k=1, stride=1, pad=0),       # channel count that is not a multiple of 4
+    dict(H=7, W=5, Cin=64, Cout=128, k=3, stride=1, pad=1),        # 3x3 borders, rows shorter than a tile
+    dict(H=9, W=21, Cin=128, Cout=136, k=3, stride=2, pad=1),      # strided 3x3, ragged channels
+])
+def test_conv_result_does_not_depend_on_the_tile(precision, case):
+    """The tile a layer runs on is chosen by its number of pixels (32 x 32 or 32 x 64 up to 256 x 256).  Every tile adds in
+    the same order, so the images of a batch come out bit for bit the same whatever the batch; and the smallest batch agrees
+    with the oracle (tolerances as above)."""
+    m, _ = _model(precision)
+    c = dict(case)
+    Ho, Wo = (c["H"] + 2 * c["pad"] - c["k"]) // c["stride"] + 1, (c["W"] + 2 * c["pad"] - c["k"]) // c["stride"] + 1
+    rs = np.random.RandomState(c["Cin"] + c["Cout"])
+    w = (rs.randn(c["Cout"], c["Cin"], c["k"], c["k"]) * np.sqrt(2.0 / (c["Cin"] * c["k"] ** 2))).astype(np.float32)
+    b = rs.randn(c["Cout"]).astype(np.float32) * 0.1
+    images = [-(-pixels // (Ho * Wo)) for pixels in (1, 33, 1100, 2100, 9000, 40000)]
+    g = torch.Generator(device="cuda").manual_seed(c["Cin"])
+    x = torch.randn(images[-1], c["H"], c["W"], c["Cin"], generator=g, device="cuda").to(m.elem)
+    res = torch.randn(images[-1], Ho, Wo, c["Cout"], generator=g, device="cuda").to(m.elem)
+    for use_res, out_f32 in [(False, False), (True, False), (False, True)]:
+        run = lambda n: m.op_conv(x[:n].contiguous(), w, b, stride=c["stride"], pad=c["pad"],
+                                  residual=res[:n].contiguous() if use_res else None, relu=True, out_f32=out_f32)
+        got = [run(n) for n in images]
+        torch.cuda.synchronize()
+        for n, y in zip(images[:-1], got):
+            assert torch.equal(y, got[-1][:n]), (use_res, out_f32, n, int((y != got[-1][:n]).sum()))
+        n = images[1]
+        ref = oracle.conv2d(nhwc_to_nchw(x[:n].float().cpu().numpy()), w, b, stride=c["stride"], pad=c["pad"], relu=True,
+                            residual=nhwc_to_nchw(res[:n].float().cpu().numpy()) if use_res else None,
+                            bf16_weights=precision, round_out=int(bool(precision) and not out_f32))
+        tol = TOL_BF16_STEP if (precision and not out_f32) else TOL_F32
+        assert relerr(nhwc_to_nchw(got[1].float().cpu().numpy()), ref) <= tol, (use_res, out_f32)
+
+
 def test_bf16_output_rounding_is_nearest_even_bit_exact():
     """The kernels round fp32 results to bf16 with the hardware conversion; the oracle with integer
     arithmetic.  A convolution with zero weights returns round(bias): ties both ways, values next to
