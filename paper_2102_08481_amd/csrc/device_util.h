@@ -16,33 +16,59 @@ __device__ inline float key_score(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// n2 (a power of two) keys in LDS, sorted descending by the whole block (a multiple of 64 threads).  A thread owns
-// compare-exchange pair q of a stage: lower element ((q & ~(j-1)) << 1) | (q & (j-1)), partner = lower | j.  The 64 pairs
-// of one wavefront iteration lie within one aligned block of 128 elements for every distance j <= 64, so between two such
-// stages only the wavefront's own LDS traffic has to be ordered; the block barrier is kept around the stages with j >= 128
-// (10 of the 66 stages at 2048 keys) and after the last one.
-__device__ inline void bitonic_sort_desc_lds(uint64_t* keys, int n2) {
-    const int pairs = n2 >> 1, nt = blockDim.x;
-    for (int k = 2; k <= n2; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int q = threadIdx.x; q < pairs; q += nt) {
-                const int i = ((q & ~(j - 1)) << 1) | (q & (j - 1)), p = i | j;
-                const uint64_t a = keys[i], b = keys[p];
-                const bool desc = (i & k) == 0;
-                if (desc ? (a < b) : (a > b)) { keys[i] = b; keys[p] = a; }
+// n2 keys (a power of two, at least 64) in LDS, sorted descending by the whole block: every wavefront sorts runs of 64 in
+// registers (a bitonic network over the lanes), then pairs of runs are merged, each key finding its place by a binary search
+// in the other run.  Two buffers of n2 keys; returns the one that holds the result.  A merge level is ~10 dependent LDS
+// reads and one barrier; the 66-stage network in LDS it replaces paid a round trip through LDS per stage (the
+// top-k tail on up to 2048 keys: 26.4 -> 22.6 us, now bound by the random LDS reads of the searches).  The caller's writes to `keys` need no barrier of their own.
+__device__ inline uint64_t* block_sort_desc(uint64_t* keys, uint64_t* tmp, int n2) {
+    const int lane = threadIdx.x & 63;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n2; i += blockDim.x) {   // (n2 and the block size are multiples of 64: whole wavefronts)
+        uint64_t v = keys[i];
+        for (int k = 2; k <= 64; k <<= 1)
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                const uint64_t o = __shfl_xor((unsigned long long)v, j);
+                const bool larger = ((lane & k) == 0) == ((lane & j) == 0);   // this lane keeps the larger of the two
+                v = (o > v) == larger ? o : v;
             }
-            const int jn = j > 1 ? (j >> 1) : k;   // distance of the stage that follows (k: first stage of the next merge)
-            if (j >= 128 || jn >= 128 || (j == 1 && k == n2)) {
-                __syncthreads();
-            } else {
-                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-                __builtin_amdgcn_wave_barrier();
-                asm volatile("" ::: "memory");
-            }
+        keys[i] = v;
+    }
+    __syncthreads();
+    for (int len = 64; len < n2; len <<= 1) {
+        for (int i = threadIdx.x; i < n2; i += blockDim.x) {
+            const uint64_t v = keys[i];
+            const int run = i & ~(len - 1);
+            const bool second = (run & len) != 0;
+            const uint64_t* other = keys + (run ^ len);
+            // keys of the other run that come first (equal keys, i.e. padding: the first run's)
+            int lo = 0;
+            for (int step = len; step > 0; step >>= 1)
+                if (lo + step <= len && (second ? other[lo + step - 1] >= v : other[lo + step - 1] > v)) lo += step;
+            tmp[(run & ~len) + (i - run) + lo] = v;
         }
+        __syncthreads();
+        uint64_t* t = keys; keys = tmp; tmp = t;
+    }
+    return keys;
 }
 
-// The same network with a block barrier after every stage: keys may live in LDS or in global memory.
+// Greedy suppression among up to 64 rows, one per lane, decided by a whole wavefront: `open` = rows not suppressed from
+// outside, `earlier` = this lane's earlier rows that overlap it.  A row is kept once all of its overlapping earlier rows
+// are suppressed, and suppressed once one of them is kept; the lowest open row is decided in every round, and usually all
+// rows are after a few, where stepping from one kept row to the next costs ~120 cycles for each of them.
+__device__ inline uint64_t greedy_keep(uint64_t open, uint64_t earlier) {
+    const uint64_t me = 1ull << (threadIdx.x & 63);
+    uint64_t kept = 0ull;
+    while (open != 0ull) {
+        kept |= __ballot((open & me) != 0ull && (earlier & (open | kept)) == 0ull);
+        open &= ~kept;
+        open &= ~__ballot((open & me) != 0ull && (earlier & kept) != 0ull);
+    }
+    return kept;
+}
+
+// Bitonic network with a block barrier after every stage: keys may live in LDS or in global memory.
 __device__ inline void bitonic_sort_desc(uint64_t* keys, int n2) {
     for (int k = 2; k <= n2; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {

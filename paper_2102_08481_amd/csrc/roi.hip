@@ -279,177 +279,122 @@ __global__ __launch_bounds__(1024) void select_kernel(const float* __restrict__ 
     if (t == 0 && out_n) out_n[f] = nk;
 }
 
-// Same selection with one wavefront per foreground class (post <= 512, Kc - 1 <= 16, D <= 128).  Same-class NMS
-// never looks across classes and the global walk stops after D kept boxes, so the result equals: per class, greedy
-// NMS over that class's candidates in key order, cut after its first D kept; then the D largest keys among all
-// kept.  Every wavefront gathers and sorts its class's candidates in LDS (wave-level barriers only), resolves 64
-// candidates at a time (overlap bits against the earlier candidates of the group, then a register-only greedy
-// chain), and the block finally ranks the <= (Kc - 1) * D kept keys by counting.
-constexpr int SELC_MAX_POST = 512, SELC_MAX_CLASSES = 16, SELC_MAX_D = 128;
+// Same selection with one block per frame and foreground class, then one block per frame that merges (post <= 1024,
+// (Kc - 1) * min(D, post) <= 8192).  Same-class NMS never looks across classes and the global walk stops after D kept boxes,
+// so the result equals: per class, greedy NMS over that class's candidates in key order, cut after its first D kept; then
+// the D largest keys among all kept.  The class block sorts its candidates in LDS and resolves them 64 at a time: its
+// wavefronts share the tests against the kept boxes and the group's overlap words, one wavefront decides.  What bounds it is
+// the chain of groups (one block for all classes of a frame: 72 us for 32 frames of 300 ROIs x 7 classes, 15 + 7 now; the
+// single chain over all classes in select_kernel: 346 us for 8 frames of 1000 ROIs x 19 classes, 21 + 17 now).
+constexpr int SELC_MAX_POST = 1024, SELC_MAX_KEPT = 8192, SELC_THREADS = 512;
 
-__global__ __launch_bounds__(1024) void select_classes_kernel(const float* __restrict__ scores, const float* __restrict__ boxes,
-                                                              const int32_t* __restrict__ roi_n, int post, int Kc,
-                                                              float score_thr, float nms_thr, int D,
-                                                              float* __restrict__ out_boxes, float* __restrict__ out_scores,
-                                                              int32_t* __restrict__ out_labels, int32_t* __restrict__ out_n) {
-    extern __shared__ __align__(16) unsigned char sel_smem[];
-    const int NC = Kc - 1;
-    Box* gbox = reinterpret_cast<Box*>(sel_smem);                        // [NC][64] boxes of the group being resolved
-    Box* kbox = gbox + (size_t)NC * 64;                                  // [NC][D] kept boxes (16-byte aligned: read as float4)
-    uint64_t* keys = reinterpret_cast<uint64_t*>(kbox + (size_t)NC * D); // [NC][SELC_MAX_POST]
-    uint64_t* kkey = keys + (size_t)NC * SELC_MAX_POST;                  // [NC][D]
-    int* kcount = reinterpret_cast<int*>(kkey + (size_t)NC * D);         // [NC]
-    const int f = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+// gkeys [n][key_cap]: class c's kept keys at c * Dc (sorted descending), the classes' counts behind all of them.
+__global__ __launch_bounds__(SELC_THREADS) void select_class_kernel(const float* __restrict__ scores, const float* __restrict__ boxes,
+                                                                    const int32_t* __restrict__ roi_n, int post, int Kc, float score_thr,
+                                                                    float nms_thr, int Dc, uint64_t* __restrict__ gkeys, int key_cap) {
+    __shared__ uint64_t lkeys[2 * SELC_MAX_POST];
+    __shared__ float4 sbox[SELC_MAX_POST];                               // boxes in key order
+    __shared__ float4 kbox[SELC_MAX_POST];                               // kept boxes
+    __shared__ uint64_t early[64];                                       // group: earlier candidates that overlap
+    __shared__ unsigned long long s_dead;                                // group: suppressed by kept boxes
+    __shared__ int s_count, s_nk;
+    constexpr int NWV = SELC_THREADS / 64, JW = 64 / NWV;                // a wavefront's share of a group's overlap words
+    const int c = blockIdx.x, f = blockIdx.y, t = threadIdx.x, lane = t & 63, wv = t >> 6;
     int nr = roi_n[f];
     nr = nr < post ? nr : post;
     const float* sc = scores + (size_t)f * post * Kc;
     const float* bx = boxes + (size_t)f * post * Kc * 4;
-
-    if (wv < NC) {
-        const int c = wv;                       // label c + 1
-        uint64_t* ck = keys + (size_t)c * SELC_MAX_POST;
-        // candidates of the class, packed to the front of the list in ROI order
-        int nc = 0;
-        for (int r0 = 0; r0 < nr; r0 += 64) {
-            const int roi = r0 + lane;
-            uint64_t key = 0ull;
-            if (roi < nr) {
-                const int j = roi * Kc + c + 1;
-                const float s = sc[j];
-                if (s > score_thr) {
-                    const float4 b = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
-                    if ((b.z - b.x >= 1e-3f) && (b.w - b.y >= 1e-3f)) key = ((uint64_t)score_key(s) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
-                }
-            }
-            const uint64_t has = __ballot(key != 0ull);
-            if (key != 0ull) ck[nc + __popcll(has & ((1ull << lane) - 1ull))] = key;
-            nc += __popcll(has);
+    uint64_t* out = gkeys + (size_t)f * key_cap + (size_t)c * Dc;
+    if (t == 0) { s_count = 0; s_nk = 0; s_dead = 0ull; }
+    __syncthreads();
+    for (int r0 = 0; r0 < nr; r0 += SELC_THREADS) {
+        const int roi = r0 + t;
+        uint64_t key = 0ull;
+        if (roi < nr) {
+            const int j = roi * Kc + c + 1;
+            const float s = sc[j];
+            const float4 b = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
+            if (s > score_thr && (b.z - b.x >= 1e-3f) && (b.w - b.y >= 1e-3f)) key = ((uint64_t)score_key(s) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
         }
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        __builtin_amdgcn_wave_barrier();
-        // Sorted descending by counting: keys are unique, so a key's place is the number of larger keys.  Every lane holds up
-        // to SELC_MAX_POST / 64 keys in registers and walks the list once (all lanes read the same entry: a broadcast);
-        // ~15 000 cycles for 300 candidates against ~57 000 for a 512-key bitonic network run by one wavefront.
-        {
-            constexpr int QMAX = SELC_MAX_POST / 64;
-            uint64_t mine[QMAX];
-            int rank[QMAX];
-#pragma unroll
-            for (int q = 0; q < QMAX; ++q) {
-                mine[q] = (lane + 64 * q < nc) ? ck[lane + 64 * q] : ~0ull;   // (absent slots compare as "nothing is larger")
-                rank[q] = 0;
-            }
-            auto count = [&](auto qc) {
-                constexpr int QN = decltype(qc)::value;
-#pragma unroll 4
-                for (int k = 0; k < nc; ++k) {
-                    const uint64_t o = ck[k];
-#pragma unroll
-                    for (int q = 0; q < QN; ++q) rank[q] += (o > mine[q]) ? 1 : 0;
-                }
-            };
-            if (nc <= 128) count(std::integral_constant<int, 2>{});
-            else if (nc <= 256) count(std::integral_constant<int, 4>{});
-            else count(std::integral_constant<int, QMAX>{});
-            __builtin_amdgcn_s_waitcnt(0xc07f);   // every lane has read the whole list
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int q = 0; q < QMAX; ++q)
-                if (lane + 64 * q < nc) ck[rank[q]] = mine[q];
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-        }
-        int nk = 0;
-        for (int s0 = 0; s0 < nc && nk < D; s0 += 64) {
-            const int i = s0 + lane;
-            bool alive = i < nc;
-            Box me = {0.f, 0.f, 0.f, 0.f};
-            uint64_t key = 0ull;
-            if (alive) {
-                key = ck[i];
-                const uint32_t j = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
-                const float4 b = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
-                me = {b.x, b.y, b.z, b.w};
-            }
-            {   // against the boxes this class has kept so far: four at a time, no early exit (the loads pipeline)
-                bool hit = false;
-                const Box* kb = kbox + (size_t)c * D;
-                int q = 0;
-                auto ld = [&](int k) { const float4 v = *reinterpret_cast<const float4*>(kb + k); return Box{v.x, v.y, v.z, v.w}; };
-                for (; q + 4 <= nk; q += 4) {
-                    const Box b0 = ld(q), b1 = ld(q + 1), b2 = ld(q + 2), b3 = ld(q + 3);
-                    const int h = (int)iou_over(b0, me, nms_thr) | (int)iou_over(b1, me, nms_thr) | (int)iou_over(b2, me, nms_thr) | (int)iou_over(b3, me, nms_thr);
-                    hit = hit || h != 0;
-                }
-                for (; q < nk; ++q) hit = hit || iou_over(ld(q), me, nms_thr);
-                alive = alive && !hit;
-            }
-            // column b of the group's overlap matrix (which later candidates candidate b suppresses), held by lane b.
-            // Every lane walks the group's boxes in LDS (all lanes read the same address: a broadcast) and tests its own
-            // box against them; broadcasting box b through scalar registers and collecting a ballot per b instead made
-            // each of the 64 steps a chain of dependent scalar and vector instructions.
-            uint64_t col = 0ull;
-            const int live = (nc - s0) < 64 ? (nc - s0) : 64;   // candidates in this group
-            Box* gb = gbox + (size_t)c * 64;
-            gb[lane] = me;
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-            if (i < nc) {
-                // four boxes per step, loaded together and tested independently (slots past `live` hold zero boxes: no overlap)
-                uint32_t word[2] = {0u, 0u};
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (32 * h >= live) break;   // uniform
-                    uint32_t w = 0u;
-#pragma unroll 2
-                    for (int j0 = 0; j0 < 32; j0 += 4) {
-                        float4 q[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const float4*>(gb + 32 * h + j0 + u);
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int j = 32 * h + j0 + u;
-                            const Box o = {q[u].x, q[u].y, q[u].z, q[u].w};
-                            w |= (j > lane && iou_over(me, o, nms_thr)) ? (1u << (j0 + u)) : 0u;
-                        }
-                    }
-                    word[h] = w;
-                }
-                col = (uint64_t)word[0] | ((uint64_t)word[1] << 32);
-            }
-            uint64_t dead = ~__ballot(alive);
-            uint64_t kept = 0ull;
-            const uint32_t clo = (uint32_t)col, chi = (uint32_t)(col >> 32);
-            for (uint64_t avail = ~dead; avail != 0ull;) {   // from one kept candidate to the next: suppressed ones are not visited
-                const int b = __builtin_ctzll(avail);
-                kept |= 1ull << b;
-                const uint64_t d = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(clo, b) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(chi, b) << 32);
-                avail &= ~d & ~((2ull << b) - 1ull);
-            }
-            if ((kept >> lane) & 1ull) {
-                const int pos = nk + __popcll(kept & ((1ull << lane) - 1ull));
-                if (pos < D) { kbox[(size_t)c * D + pos] = me; kkey[(size_t)c * D + pos] = key; }
-            }
-            nk += __popcll(kept);
-            nk = nk < D ? nk : D;
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-        }
-        if (lane == 0) kcount[c] = nk;
+        const uint64_t has = __ballot(key != 0ull);
+        int base = 0;
+        if (lane == 0 && has != 0ull) base = atomicAdd(&s_count, (int)__popcll(has));
+        base = __shfl(base, 0);
+        if (key != 0ull) lkeys[base + __popcll(has & ((1ull << lane) - 1ull))] = key;
     }
     __syncthreads();
-    // rank of every kept key among all kept keys (each class list is sorted descending: binary search per class)
+    const int nc = s_count;
+    int n2 = 64;
+    while (n2 < nc) n2 <<= 1;
+    for (int i = nc + t; i < n2; i += SELC_THREADS) lkeys[i] = 0ull;
+    const uint64_t* keys = block_sort_desc(lkeys, lkeys + SELC_MAX_POST, n2);
+    for (int i = t; i < nc; i += SELC_THREADS) {
+        const uint32_t j = 0xFFFFFFFFu - (uint32_t)(keys[i] & 0xFFFFFFFFull);
+        sbox[i] = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
+    }
+    __syncthreads();
+    auto as_box = [](const float4& v) { return Box{v.x, v.y, v.z, v.w}; };
+    int nk = 0;
+    for (int s0 = 0; s0 < nc && nk < Dc; s0 += 64) {
+        const int i = s0 + lane;
+        const bool valid = i < nc;
+        const Box me = valid ? as_box(sbox[i]) : Box{0.f, 0.f, 0.f, 0.f};
+        // every wavefront: its share of the kept boxes against the group's 64, one candidate per lane
+        bool hit = false;
+        for (int q = wv; q < nk; q += NWV) hit = iou_over(as_box(kbox[q]), me, nms_thr) || hit;
+        const uint64_t dead = __ballot(hit);
+        if (lane == 0 && dead != 0ull) atomicOr(&s_dead, (unsigned long long)dead);
+        // and JW earlier candidates of the group against every later one
+        uint32_t bits = 0u;
+#pragma unroll
+        for (int u = 0; u < JW; ++u) {
+            const int j = wv * JW + u;
+            if (j < lane && valid && iou_over(as_box(sbox[s0 + j]), me, nms_thr)) bits |= 1u << u;
+        }
+        static_assert(JW == 8, "one byte of a row's word per wavefront");
+        reinterpret_cast<unsigned char*>(early)[lane * 8 + wv] = (unsigned char)bits;
+        __syncthreads();
+        if (wv == 0) {
+            const uint64_t in_group = nc - s0 < 64 ? (1ull << (nc - s0)) - 1ull : ~0ull;
+            const uint64_t kept = greedy_keep(in_group & ~s_dead, early[lane]);
+            const int pos = nk + __popcll(kept & ((1ull << lane) - 1ull));
+            const bool mine = ((kept >> lane) & 1ull) != 0ull && pos < Dc;
+            if (mine) { kbox[pos] = sbox[i]; out[pos] = keys[i]; }
+            if (lane == 0) { s_nk = nk + __popcll(kept) < Dc ? nk + __popcll(kept) : Dc; s_dead = 0ull; }
+        }
+        __syncthreads();
+        nk = s_nk;
+    }
+    if (t == 0) reinterpret_cast<int32_t*>(gkeys + (size_t)f * key_cap + (size_t)gridDim.x * Dc)[c] = nk;
+}
+
+// The D largest of a frame's kept keys: a key's rank is its place in its own class list plus, found by binary search, the
+// number of larger keys in every other list.
+__global__ __launch_bounds__(1024) void select_merge_kernel(const uint64_t* __restrict__ gkeys, int key_cap, const float* __restrict__ boxes,
+                                                            int post, int Kc, int Dc, int D, float* __restrict__ out_boxes,
+                                                            float* __restrict__ out_scores, int32_t* __restrict__ out_labels,
+                                                            int32_t* __restrict__ out_n) {
+    extern __shared__ __align__(16) unsigned char sel_smem[];
+    const int NC = Kc - 1, f = blockIdx.x, t = threadIdx.x;
+    uint64_t* kkey = reinterpret_cast<uint64_t*>(sel_smem);              // [NC][Dc]
+    int* kcount = reinterpret_cast<int*>(kkey + (size_t)NC * Dc);        // [NC]
+    const uint64_t* gk = gkeys + (size_t)f * key_cap;
+    const int32_t* gn = reinterpret_cast<const int32_t*>(gk + (size_t)NC * Dc);
+    for (int c = t; c < NC; c += 1024) kcount[c] = gn[c];
+    for (int e = t; e < NC * Dc; e += 1024) kkey[e] = gk[e];             // (entries behind a class's count are never used)
+    __syncthreads();
     int total = 0;
     for (int c = 0; c < NC; ++c) total += kcount[c];
     const int nk_out = total < D ? total : D;
-    for (int e = t; e < NC * D; e += 1024) {
-        const int c = e / D, q = e - c * D;
+    for (int e = t; e < NC * Dc; e += 1024) {
+        const int c = e / Dc, q = e - c * Dc;
         if (q >= kcount[c]) continue;
-        const uint64_t key = kkey[(size_t)c * D + q];
-        int rank = 0;
-        for (int c2 = 0; c2 < NC; ++c2) {
-            const uint64_t* l = kkey + (size_t)c2 * D;
-            int lo = 0, hi = kcount[c2];          // first position whose key is <= key
+        const uint64_t key = kkey[e];
+        int rank = q;
+        for (int c2 = 0; c2 < NC && rank < D; ++c2) {
+            if (c2 == c) continue;
+            const uint64_t* l = kkey + (size_t)c2 * Dc;
+            int lo = 0, hi = kcount[c2];          // first position whose key is smaller
             while (lo < hi) {
                 const int mid = (lo + hi) >> 1;
                 if (l[mid] > key) lo = mid + 1; else hi = mid;
@@ -457,8 +402,8 @@ __global__ __launch_bounds__(1024) void select_classes_kernel(const float* __res
             rank += lo;
         }
         if (rank < D) {
-            const Box b = kbox[(size_t)c * D + q];
-            *reinterpret_cast<float4*>(out_boxes + ((size_t)f * D + rank) * 4) = make_float4(b.x1, b.y1, b.x2, b.y2);
+            const uint32_t j = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
+            *reinterpret_cast<float4*>(out_boxes + ((size_t)f * D + rank) * 4) = *reinterpret_cast<const float4*>(boxes + ((size_t)f * post * Kc + j) * 4);
             out_scores[(size_t)f * D + rank] = key_score((uint32_t)(key >> 32));
             out_labels[(size_t)f * D + rank] = c + 1;
         }
@@ -475,16 +420,14 @@ hipError_t launch_select(const float* scores, const float* boxes, const int32_t*
                          float score_thr, float nms_thr, int D, uint64_t* keys, int key_cap, float* out_boxes,
                          float* out_scores, int32_t* out_labels, int32_t* out_n, hipStream_t s) {
     if (n <= 0 || D <= 0 || D > SEL_MAX_D || key_cap < post * Kc) return hipErrorInvalidValue;
-    if (post <= SELC_MAX_POST && Kc >= 2 && Kc - 1 <= SELC_MAX_CLASSES && D <= SELC_MAX_D) {
-        const int NC = Kc - 1;
-        const size_t lds = (size_t)NC * 64 * sizeof(Box) + (size_t)NC * SELC_MAX_POST * 8 + (size_t)NC * D * (8 + sizeof(Box)) + (size_t)NC * 4;
-        {
-            const size_t lds_max = (size_t)SELC_MAX_CLASSES * 64 * sizeof(Box) + (size_t)SELC_MAX_CLASSES * SELC_MAX_POST * 8 +
-                                   (size_t)SELC_MAX_CLASSES * SELC_MAX_D * (8 + sizeof(Box)) + (size_t)SELC_MAX_CLASSES * 4;
-            hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(select_classes_kernel), lds_max);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(select_classes_kernel, dim3(n), dim3(1024), lds, s, scores, boxes, roi_n, post, Kc, score_thr, nms_thr, D,
+    const int NC = Kc - 1, Dc = D < post ? D : post;   // a class keeps at most Dc
+    if (post <= SELC_MAX_POST && NC >= 1 && NC <= 2 * post && (long)NC * Dc <= SELC_MAX_KEPT && n <= 65535) {
+        // (key_cap >= post * Kc holds the NC * Dc kept keys and, in the post that are left, the NC counts)
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(select_merge_kernel), (size_t)SELC_MAX_KEPT * 8 + 2 * SELC_MAX_POST * 4);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(select_class_kernel, dim3(NC, n), dim3(SELC_THREADS), 0, s, scores, boxes, roi_n, post, Kc, score_thr, nms_thr, Dc,
+                           keys, key_cap);
+        hipLaunchKernelGGL(select_merge_kernel, dim3(n), dim3(1024), (size_t)NC * Dc * 8 + (size_t)NC * 4, s, keys, key_cap, boxes, post, Kc, Dc, D,
                            out_boxes, out_scores, out_labels, out_n);
         return hipGetLastError();
     }

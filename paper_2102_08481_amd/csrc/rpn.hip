@@ -11,13 +11,12 @@
 // candidate list (twice the next power of two of k, at most 4096): with real-valued logits
 // that is after the second digit, and the last three digits only ever run when logits tie
 // at the cut.  All elements with key >= that bound are then gathered (any order) and
-// sorted by key in LDS with a bitonic network, which makes the output order deterministic;
+// sorted by key in LDS, which makes the output order deterministic;
 // the first k are the result.  The same block decodes the k anchors and compacts the
 // non-empty boxes in order.
 //
 // NMS: a k x k upper-triangular overlap bit matrix (64-bit words) is computed by
-// 64-thread blocks, then one wavefront per frame scans it 64 rows at a time from LDS,
-// holding the "removed" bit vector one word per lane.
+// 64-thread blocks, then one block per frame scans it 64 rows at a time from LDS.
 #include "device_util.h"
 
 namespace thia {
@@ -34,6 +33,8 @@ constexpr int HIST_CHUNK = 8192;  // elements per histogram block
 // block is bound by same-address LDS atomics (neighbouring logits share their leading digit), 161 against 99 us at 122 400
 // anchors and 814 against 137 us at 486 000; counting a wavefront's shared digits once per ballot round was slower still.
 constexpr long FUSED_MAX_ANCHORS = 50000;
+constexpr size_t TOPK_MAX_LDS = (size_t)2 * 4096 * 8;   // two key buffers of the largest candidate list
+__host__ __device__ inline int lds_keys(int cap) { return cap < 64 ? 64 : cap; }   // keys per buffer (whole wavefronts sort them)
 
 __device__ inline uint64_t rank_key(float logit, uint32_t idx) {
     return ((uint64_t)score_key(logit) << IDX_BITS) | (uint64_t)(IDX_MASK - idx);
@@ -161,8 +162,8 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(const float* __restric
         if (base + j < (unsigned long long)cap) cand[(size_t)f * cap + base + j] = s_keys[j];
 }
 
-// Tail shared by the two top-k paths, run by a 1024-thread block for frame f: `keys` (LDS, cap entries, the gathered
-// candidates first, the rest zero) is sorted, the first k emitted as indices, their anchors decoded and clipped, non-empty
+// Tail shared by the two top-k paths, run by a 1024-thread block for frame f: `keys` (LDS, 2 x lds_keys(cap), the gathered
+// candidates first, the rest of the first buffer zero) is sorted, the first k emitted as indices, their anchors decoded and clipped, non-empty
 // boxes compacted in order.
 __device__ inline void sort_decode_emit(uint64_t* keys, int got, int k_want, int cap, int pre, long nA, const float* __restrict__ deltas,
                                         int Wk, int stride, float imgW, float imgH, const AnchorSpec& anc, int f,
@@ -173,8 +174,9 @@ __device__ inline void sort_decode_emit(uint64_t* keys, int got, int k_want, int
     if (t == 0) base_sh = 0;
     __syncthreads();
     const int k = got < k_want ? got : k_want;
-    // the usual case gathers k or a few more keys: half the list then holds them all, and the network is a stage shorter
-    bitonic_sort_desc_lds(keys, 2 * got <= cap ? cap / 2 : cap);
+    int n2 = 64;   // (the usual case gathers k or a few more keys of the cap)
+    while (n2 < got) n2 <<= 1;
+    keys = block_sort_desc(keys, keys + lds_keys(cap), n2);
 
     const int A = anc.n_sizes * anc.n_ratios;
     const float* dl = deltas + (size_t)f * nA * 4;
@@ -225,11 +227,11 @@ __global__ __launch_bounds__(1024) void topk_sort_decode_kernel(const uint64_t* 
                                                                 int32_t* __restrict__ out_idx, float* __restrict__ out_boxes,
                                                                 int32_t* __restrict__ out_n) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint64_t* keys = reinterpret_cast<uint64_t*>(smem_raw);  // [cap]
+    uint64_t* keys = reinterpret_cast<uint64_t*>(smem_raw);  // [2][lds_keys(cap)]
     const int f = blockIdx.x, t = threadIdx.x;
     int got = (int)state[4 * f + 3];
     if (got > cap) got = cap;
-    for (int i = t; i < cap; i += 1024) keys[i] = i < got ? cand[(size_t)f * cap + i] : 0ull;
+    for (int i = t; i < lds_keys(cap); i += 1024) keys[i] = i < got ? cand[(size_t)f * cap + i] : 0ull;
     sort_decode_emit(keys, got, k_want, cap, pre, nA, deltas, Wk, stride, imgW, imgH, anc, f, out_idx, out_boxes, out_n);
 }
 
@@ -314,8 +316,8 @@ __global__ __launch_bounds__(1024) void topk_fused_kernel(const float* __restric
                                                           AnchorSpec anc, int32_t* __restrict__ out_idx, float* __restrict__ out_boxes,
                                                           int32_t* __restrict__ out_n) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint64_t* keys = reinterpret_cast<uint64_t*>(smem_raw);                  // [cap]
-    uint32_t* hist = reinterpret_cast<uint32_t*>(keys + cap);                // [HIST_BINS]
+    uint64_t* keys = reinterpret_cast<uint64_t*>(smem_raw);                  // [2][lds_keys(cap)]
+    uint32_t* hist = reinterpret_cast<uint32_t*>(keys + 2 * (size_t)lds_keys(cap));   // [HIST_BINS]
     __shared__ uint32_t part[256];
     __shared__ uint32_t above[256];
     __shared__ uint64_t s_prefix;
@@ -326,7 +328,7 @@ __global__ __launch_bounds__(1024) void topk_fused_kernel(const float* __restric
     __syncthreads();
     block_select_passes(lg, nA, 0, k_want, cap, hist, part, above, &s_prefix, &s_krem, &s_done);
     const uint64_t thr = s_prefix;
-    for (int i = t; i < cap; i += 1024) keys[i] = 0ull;
+    for (int i = t; i < lds_keys(cap); i += 1024) keys[i] = 0ull;
     __syncthreads();
     for (long b = 0; b < nA; b += 8 * 1024) {
         float v[8];
@@ -356,8 +358,13 @@ hipError_t launch_rpn_proposals(const float* logits, const float* deltas, int n,
     const int cap = topk_cand_cap(pre);
     const unsigned bpf = (unsigned)((nA + HIST_CHUNK - 1) / HIST_CHUNK);
     if (n > 65535) return hipErrorInvalidValue;
+    {
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(topk_fused_kernel), TOPK_MAX_LDS + HIST_BINS * 4);
+        if (e == hipSuccess) e = ensure_dynamic_lds(reinterpret_cast<const void*>(topk_sort_decode_kernel), TOPK_MAX_LDS);
+        if (e != hipSuccess) return e;
+    }
     if (nA <= FUSED_MAX_ANCHORS) {
-        hipLaunchKernelGGL(topk_fused_kernel, dim3(n), dim3(1024), (size_t)cap * 8 + HIST_BINS * 4, s, logits, nA, k, cap, pre, deltas, Wk,
+        hipLaunchKernelGGL(topk_fused_kernel, dim3(n), dim3(1024), (size_t)lds_keys(cap) * 16 + HIST_BINS * 4, s, logits, nA, k, cap, pre, deltas, Wk,
                            stride, imgW, imgH, anc, out_idx, out_boxes, out_n);
         return hipGetLastError();
     }
@@ -368,12 +375,14 @@ hipError_t launch_rpn_proposals(const float* logits, const float* deltas, int n,
     }
     hipLaunchKernelGGL(topk_finish_kernel, dim3(n), dim3(1024), 0, s, logits, nA, work.state, k, cap);
     hipLaunchKernelGGL(topk_gather_kernel, dim3(bpf, n), dim3(256), 0, s, logits, nA, work.state, work.cand, cap);
-    hipLaunchKernelGGL(topk_sort_decode_kernel, dim3(n), dim3(1024), (size_t)cap * 8, s, work.cand, work.state, cap, k, pre, nA,
+    hipLaunchKernelGGL(topk_sort_decode_kernel, dim3(n), dim3(1024), (size_t)lds_keys(cap) * 16, s, work.cand, work.state, cap, k, pre, nA,
                        deltas, Wk, stride, imgW, imgH, anc, out_idx, out_boxes, out_n);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------- NMS
+// Word (row i, tile bx): which boxes of tile bx box i overlaps, for the tiles behind its own.  In its own tile the EARLIER
+// boxes instead (the overlap test is symmetric): what the greedy decision of row i depends on.
 __global__ __launch_bounds__(64) void nms_mask_kernel(const float* __restrict__ boxes, const int32_t* __restrict__ counts,
                                                       int cap, int words, float thr, uint64_t* __restrict__ mask) {
     const int bx = blockIdx.x, by = blockIdx.y, f = blockIdx.z;
@@ -397,101 +406,102 @@ __global__ __launch_bounds__(64) void nms_mask_kernel(const float* __restrict__ 
     const int jn = (cnt - 64 * bx) < 64 ? (cnt - 64 * bx) : 64;
     for (int b = 0; b < jn; ++b) {
         const int j = 64 * bx + b;
-        if (j > i && iou_over(me, cb[b], thr)) bits |= 1ull << b;
+        if ((bx == by ? j < i : j > i) && iou_over(me, cb[b], thr)) bits |= 1ull << b;
     }
     mask[((size_t)f * cap + i) * words + bx] = bits;
 }
 
-// One 256-thread block per frame.  The bit matrix is consumed 64 rows at a time: all threads
-// fetch the next 64 x words tile into registers while wavefront 0 resolves the current one from
-// LDS.  Within a tile the greedy decisions only need the diagonal word of each row, which is
-// held one row per lane and broadcast with readlane, so the serial chain is register-only; the
-// rows that were kept are then OR-ed into the "removed" vector (one 64-bit word per lane).
-__global__ __launch_bounds__(256) void nms_reduce_kernel(const uint64_t* __restrict__ mask, const float* __restrict__ boxes,
-                                                         const int32_t* __restrict__ counts, int cap, int words, int max_keep,
-                                                         int32_t* __restrict__ out_keep, int32_t* __restrict__ out_n,
-                                                         float* __restrict__ rois_out) {
+// One 512-thread block per frame.  The bit matrix is consumed 64 rows at a time: wavefront 0 decides the rows of a tile from
+// the tile's own words (one row per lane, greedy_keep), then all threads OR the kept rows' words into the frame's "removed"
+// set.  Four tiles are in flight: a tile takes ~0.5 us, less than a load from another XCD's results.  What bounds the kernel
+// is this chain of tiles.  (Rows decided one by one and OR-ed by one wavefront: 143 us at 2000 boxes of 8 frames, now 27; 42 -> 10 at 1000 of one.)
+constexpr int NMS_THREADS = 512, NMS_AHEAD = 4;
+__global__ __launch_bounds__(NMS_THREADS) void nms_reduce_kernel(const uint64_t* __restrict__ mask, const float* __restrict__ boxes,
+                                                                 const int32_t* __restrict__ counts, int cap, int words, int max_keep,
+                                                                 int32_t* __restrict__ out_keep, int32_t* __restrict__ out_n,
+                                                                 float* __restrict__ rois_out) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     uint64_t* tile = reinterpret_cast<uint64_t*>(smem_raw);                 // [64][words]
     int32_t* keep = reinterpret_cast<int32_t*>(tile + (size_t)64 * words);  // [max_keep]
+    __shared__ unsigned long long removed[64];
+    __shared__ unsigned long long s_kept;
     __shared__ int s_nk;
     const int f = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int cnt = counts[f] < cap ? counts[f] : cap;
     const int wc = (cnt + 63) / 64;
     const uint64_t* mf = mask + (size_t)f * cap * words;
-    const int per_thread = (64 * words + 255) / 256;   // <= 16 for words <= 64
-    // two tiles ahead: a tile's words are requested while the tile before the previous one is resolved
-    uint64_t stage_a[16], stage_b[16];
-    auto fetch = [&](int c, uint64_t (&stage)[16]) {
+    constexpr int PER = 64 * 64 / NMS_THREADS;                              // staged words per thread and tile, words <= 64
+    const int per_thread = (64 * words + NMS_THREADS - 1) / NMS_THREADS;
+    uint64_t stage[NMS_AHEAD][PER];
+    auto fetch = [&](int c, uint64_t (&st)[PER]) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < PER; ++q) {
             if (q >= per_thread) break;
-            const int e = q * 256 + t, r = e / words, w = e - r * words;
+            const int e = q * NMS_THREADS + t, r = e / words, w = e - r * words;
             uint64_t v = 0ull;
             if (e < 64 * words && 64 * c + r < cnt && w >= c && w < wc) v = mf[(size_t)(64 * c + r) * words + w];
-            stage[q] = v;
+            st[q] = v;
         }
     };
-    auto stash = [&](const uint64_t (&stage)[16]) {
+    auto stash = [&](const uint64_t (&st)[PER]) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < PER; ++q) {
             if (q >= per_thread) break;
-            const int e = q * 256 + t;
-            if (e < 64 * words) tile[e] = stage[q];
+            const int e = q * NMS_THREADS + t;
+            if (e < 64 * words) tile[e] = st[q];
         }
     };
-    if (t == 0) s_nk = -1;    // becomes the final count as soon as max_keep boxes are kept (early exit for all wavefronts)
-    uint64_t removed = 0ull;  // wavefront 0: lane w holds word w
-    int nk = 0;
-    if (wc > 0) fetch(0, stage_a);
-    if (wc > 1) fetch(1, stage_b);
-    __syncthreads();
+    if (t < 64) removed[t] = 0ull;
+    if (t == 0) s_nk = -1;    // becomes the final count as soon as max_keep boxes are kept
+    int wpow = 1;             // lanes per row in the OR step
+    while (wpow < words) wpow <<= 1;
+    int nk = 0;               // (wavefront 0's)
+#pragma unroll
+    for (int c = 0; c < NMS_AHEAD; ++c)
+        if (c < wc) fetch(c, stage[c]);
     // one tile: returns true once max_keep boxes are kept
-    auto step = [&](int c, uint64_t (&stage)[16]) {
-        stash(stage);
+    auto step = [&](int c, uint64_t (&st)[PER]) {
+        stash(st);
         __syncthreads();
-        if (c + 2 < wc) fetch(c + 2, stage);
+        if (c + NMS_AHEAD < wc) fetch(c + NMS_AHEAD, st);
         if (wv == 0) {
             const int rows = (cnt - 64 * c) < 64 ? (cnt - 64 * c) : 64;
-            const uint64_t diag = lane < rows ? tile[(size_t)lane * words + c] : 0ull;
-            const uint32_t dlo = (uint32_t)diag, dhi = (uint32_t)(diag >> 32);
-            const uint32_t rlo = (uint32_t)removed, rhi = (uint32_t)(removed >> 32);
-            uint64_t cur = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(rlo, c) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(rhi, c) << 32);
-            // serial greedy chain over the tile's rows, registers and scalars only.  It steps from one kept row to the next
-            // (lowest row not yet suppressed): with one wavefront on the SIMD every dependent instruction pays its full
-            // latency, ~120 cycles per step, so stepping over suppressed rows one by one was most of the kernel.
-            uint64_t kept = 0ull;
-            int room = max_keep - nk;
-            uint64_t avail = ~cur & (rows < 64 ? (1ull << rows) - 1ull : ~0ull);
-            while (avail != 0ull && room > 0) {
-                const int b = __builtin_ctzll(avail);
-                kept |= 1ull << b;
-                --room;
-                const uint64_t d = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(dlo, b) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(dhi, b) << 32);
-                avail &= ~d & ~((2ull << b) - 1ull);   // rows b suppresses, and rows up to b, are decided
-            }
-            // kept rows -> keep list (lane b writes its own slot) and OR of their mask rows into the removed set
-            if ((kept >> lane) & 1ull) keep[nk + __popcll(kept & ((1ull << lane) - 1ull))] = 64 * c + lane;
+            const uint64_t earlier = lane < rows ? tile[(size_t)lane * words + c] : 0ull;
+            const uint64_t in_tile = rows < 64 ? (1ull << rows) - 1ull : ~0ull;
+            uint64_t kept = greedy_keep(in_tile & ~removed[c], earlier);
+            const int pos = nk + __popcll(kept & ((1ull << lane) - 1ull));
+            kept = __ballot(((kept >> lane) & 1ull) != 0ull && pos < max_keep);   // later rows do not change earlier decisions
+            if ((kept >> lane) & 1ull) keep[pos] = 64 * c + lane;
             nk += __popcll(kept);
-            if (nk < max_keep && lane < words) {
-                uint64_t acc = 0ull;
-                for (uint64_t k = kept; k != 0ull; k &= k - 1ull) acc |= tile[(size_t)__builtin_ctzll(k) * words + lane];   // kept rows only
-                removed |= acc;
+            if (lane == 0) {
+                s_kept = kept;
+                if (nk == max_keep) s_nk = nk;
             }
-            if (nk == max_keep && lane == 0) s_nk = nk;
         }
         __syncthreads();
-        return s_nk >= 0;   // uniform: written before the barrier
+        if (s_nk >= 0) return true;   // uniform: written before the barrier
+        const uint64_t kept = s_kept;
+        const int w = t & (wpow - 1);
+        if (w > c && w < words) {
+            uint64_t acc = 0ull;
+            for (int r = t / wpow; r < 64; r += NMS_THREADS / wpow)
+                if ((kept >> r) & 1ull) acc |= tile[(size_t)r * words + w];
+            if (acc) atomicOr(&removed[w], (unsigned long long)acc);
+        }
+        __syncthreads();
+        return false;
     };
-    for (int c = 0; c < wc; c += 2) {
-        if (step(c, stage_a)) break;
-        if (c + 1 < wc && step(c + 1, stage_b)) break;
+    bool full = false;
+    for (int c = 0; c < wc && !full; c += NMS_AHEAD) {
+#pragma unroll
+        for (int q = 0; q < NMS_AHEAD; ++q)
+            if (c + q < wc && !full) full = step(c + q, stage[q]);
     }
     if (t == 0 && s_nk < 0) s_nk = nk;
     __syncthreads();
     nk = s_nk;
     const float* bf = boxes + (size_t)f * cap * 4;
-    for (int j = t; j < max_keep; j += 256) {
+    for (int j = t; j < max_keep; j += NMS_THREADS) {
         const int src = j < nk ? keep[j] : -1;
         out_keep[(size_t)f * max_keep + j] = src;
         if (rois_out) {
@@ -509,7 +519,7 @@ hipError_t launch_nms(const float* boxes, const int32_t* counts, int n, int cap,
     const int words = (cap + 63) / 64;
     hipLaunchKernelGGL(nms_mask_kernel, dim3(words, words, n), dim3(64), 0, s, boxes, counts, cap, words, thr, mask);
     const size_t lds = (size_t)64 * words * 8 + (size_t)max_keep * 4;
-    hipLaunchKernelGGL(nms_reduce_kernel, dim3(n), dim3(256), lds, s, mask, boxes, counts, cap, words, max_keep, out_keep, out_n,
+    hipLaunchKernelGGL(nms_reduce_kernel, dim3(n), dim3(NMS_THREADS), lds, s, mask, boxes, counts, cap, words, max_keep, out_keep, out_n,
                        rois_out);
     return hipGetLastError();
 }

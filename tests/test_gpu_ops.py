@@ -2,6 +2,8 @@
 tensor through the C ABI (thia_op_*) and compared with the oracle's downstream tensor.
 Orderings, indices and NMS keeps must be bit-exact; floating-point tensors within the
 tolerance written next to each check."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 import torch
@@ -394,3 +396,24 @@ def test_select_detections_op_is_bit_exact():
         assert cnt[f] == rn, f
         assert np.array_equal(ol[f], rl) and np.array_equal(ob[f], rb) and np.array_equal(osc[f], rs_), f
     assert cnt[0] == D and cnt[3] == 0
+
+
+@pytest.mark.parametrize("post,Kc,D", [(1, 2, 4), (63, 3, 100), (65, 2, 64), (520, 5, 200), (1024, 9, 130), (1025, 3, 100)])
+def test_select_detections_op_edges_of_the_class_lists(post, Kc, D):
+    """Fewer ROIs than detections, lists around one wavefront and at the largest the per-class kernels take, one beyond it
+    (single-chain kernel); many kept boxes per class, and equal scores within and across classes."""
+    spec = replace(MINI_BF16, pre_nms=max(post, 64), post_nms=post, n_classes=Kc, max_det=D)
+    m, _ = gpu_model(spec, 0xBEEF + 77)
+    rs = np.random.RandomState(post + Kc)
+    n = 3
+    scores = rs.dirichlet(np.ones(Kc) * 0.7, size=(n, post)).astype(np.float32)
+    scores[1] = np.round(scores[1] * 16) / 16
+    boxes = _rand_boxes(rs, n * post * Kc, 500.0).reshape(n, post, Kc, 4)
+    boxes[2] = np.round(boxes[2] / 50) * 50 + np.float32([0, 0, 40, 40])     # identical boxes in most groups
+    roi_n = np.array([post, post, max(post - 1, 0)], np.int32)
+    ob, osc, ol, cnt = m.op_select_detections(to_dev(scores), to_dev(boxes), to_dev(roi_n))
+    torch.cuda.synchronize()
+    for f in range(n):
+        rb, rs_, rl, rn = oracle.select_detections(scores[f, :roi_n[f]], boxes[f, :roi_n[f]], spec.score_thr, spec.det_nms_thr, D)
+        assert cnt[f].item() == rn, f
+        assert np.array_equal(ol[f].cpu().numpy(), rl) and np.array_equal(ob[f].cpu().numpy(), rb) and np.array_equal(osc[f].cpu().numpy(), rs_), f
