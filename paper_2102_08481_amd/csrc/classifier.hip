@@ -3,8 +3,9 @@
 // convolution layer and owns a classifier unit: global average pooling, one fully connected layer, soft-max, arg-max.
 // Inference stops at the chosen exit: layers behind the tapped one are never launched.
 //
-// The convolutions run on the library's implicit-GEMM matrix-core kernel (launch_conv); the first layer's three input
-// channels are zero-padded to one K tile by the kernel that normalises the frames and lays them out as NHWC.  The pooled
+// The convolutions run on the library's implicit-GEMM matrix-core kernel (launch_conv), except for the first one or two of a
+// bf16 model, which read the frames (first_layers.hip); for fp32 models the first layer's three input channels are
+// zero-padded to one K tile by the kernel that normalises the frames and lays them out as NHWC.  The pooled
 // means are formed as per-slab partial sums that the unit's kernel adds in a fixed order (no floating-point atomics: the
 // result does not depend on scheduling).
 #include <algorithm>
@@ -25,12 +26,11 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 constexpr int32_t kClsMagic = 0x43494854;
 constexpr int kMaxLayers = 16, kMaxExits = 8, kSlabs = 64;
 
-// frames u8 [n,3,H,W] -> x [n,H,W,CP] with x[.., c] = (u8 - mean) / std for c < 3 and 0 above; one thread per 16-byte chunk.
-template <bool BF16>
+// fp32 models: frames u8 [n,3,H,W] -> x [n,H,W,CP] with x[.., c] = (u8 - mean) / std for c < 3 and 0 above; one thread per
+// 16-byte chunk.
 __global__ void pack_frames_kernel(const uint8_t* __restrict__ frames, size_t pixels, int HW, int CP, float mean, float stdv,
-                                   void* __restrict__ out_) {
-    constexpr int EPC = BF16 ? 8 : 4;
-    const int chunks = CP / EPC;
+                                   float* __restrict__ out) {
+    const int chunks = CP / 4;
     const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= pixels * chunks) return;
     const int ck = (int)(gid % chunks);
@@ -40,13 +40,8 @@ __global__ void pack_frames_kernel(const uint8_t* __restrict__ frames, size_t pi
         const size_t img = px / HW, p = px - img * HW;
         for (int c = 0; c < 3; ++c) v[c] = ((float)frames[(img * 3 + c) * HW + p] - mean) / stdv;
     }
-    if (BF16) {
-        const u32x4_t o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], 0.f), 0u, 0u};
-        *reinterpret_cast<u32x4_t*>(static_cast<bf16_t*>(out_) + px * CP + (size_t)ck * EPC) = o;
-    } else {
-        const f32x4_t o = {v[0], v[1], v[2], 0.f};
-        *reinterpret_cast<f32x4_t*>(static_cast<float*>(out_) + px * CP + (size_t)ck * EPC) = o;
-    }
+    const f32x4_t o = {v[0], v[1], v[2], 0.f};
+    *reinterpret_cast<f32x4_t*>(out + px * CP + (size_t)ck * 4) = o;
 }
 
 // 2x2 / stride 2 max-pool without padding (a trailing odd row / column is dropped), NHWC; one thread per 16-byte chunk.
@@ -238,17 +233,37 @@ hipError_t launch_head(const thia_classifier* c, const void* feat, int n, int HW
 // nb frames up to the layer exit ep taps; *feat points at the tapped tensor [nb,h,w,C] (NHWC), *hw = h * w.
 int run_to_tap(thia_classifier* c, const uint8_t* frames, int nb, int H, int W, int ep, const void** feat, int* hw) {
     const int tap = c->taps[ep - 1];
-    {
-        const int epc = c->precision ? 8 : 4;
-        const size_t total = (size_t)nb * H * W * (c->cin_pad / epc), blocks = (total + 255) / 256;
+    void *x = c->act[1], *y = c->act[0];
+    int h = H, w = W, first = 0;
+    if (c->precision) {
+        // bf16: the first layer reads the frames; with a second one behind it and 64 channels in both, the two layers and the
+        // pool that follows are one launch (64 pictures of 224 x 224: 258 us, 1 232 us as packing, two
+        // layers and pool)
+        const ConvLayer &L1 = c->conv[0], &L2 = c->conv[1];
+        hipError_t e;
+        if (tap >= 2 && L1.co == 64 && L2.co == 64 && !c->pool[0]) {
+            const bool pooled = c->pool[1] && tap > 2;
+            e = launch_first_pair(frames, nb, H, W, static_cast<const bf16_t*>(L1.w), L1.b, static_cast<const bf16_t*>(L2.w), L2.b, pooled, c->mean,
+                                  c->stdv, static_cast<bf16_t*>(x), c->stream);
+            if (pooled) { h /= 2; w /= 2; }
+            first = 2;
+        } else {
+            e = launch_first_layer(frames, nb, H, W, static_cast<const bf16_t*>(L1.w), L1.b, L1.co, c->mean, c->stdv, static_cast<bf16_t*>(x), c->stream);
+            first = 1;
+            if (e == hipSuccess && c->pool[0] && tap > 1) {
+                e = launch_pool2x2(x, nb, h, w, L1.co, c->precision, y, c->stream);
+                std::swap(x, y);
+                h /= 2; w /= 2;
+            }
+        }
+        if (e != hipSuccess) return cfail(c, THIA_E_HIP, "first layers: launch failed");
+    } else {
+        const size_t total = (size_t)nb * H * W * (c->cin_pad / 4), blocks = (total + 255) / 256;
         if (blocks >= (1ull << 31)) return cfail(c, THIA_E_SHAPE, "chunk too large");
-        if (c->precision) hipLaunchKernelGGL(pack_frames_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, c->stream, frames, (size_t)nb * H * W, H * W, c->cin_pad, c->mean, c->stdv, c->act[1]);
-        else hipLaunchKernelGGL(pack_frames_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, c->stream, frames, (size_t)nb * H * W, H * W, c->cin_pad, c->mean, c->stdv, c->act[1]);
+        hipLaunchKernelGGL(pack_frames_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream, frames, (size_t)nb * H * W, H * W, c->cin_pad, c->mean, c->stdv, static_cast<float*>(x));
         if (hipGetLastError() != hipSuccess) return cfail(c, THIA_E_HIP, "frame packing launch failed");
     }
-    void *x = c->act[1], *y = c->act[0];
-    int h = H, w = W;
-    for (int i = 0; i < tap; ++i) {
+    for (int i = first; i < tap; ++i) {
         const ConvLayer& L = c->conv[i];
         ConvArgs a{};
         a.in = x; a.w = L.w; a.bias = L.b; a.res = nullptr; a.out0 = y; a.out1 = nullptr;

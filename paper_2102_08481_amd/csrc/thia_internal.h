@@ -128,6 +128,15 @@ hipError_t launch_fused_block(const FusedBlockArgs& a, int width, hipStream_t s)
 // lane l holds w[32 ct + l % 32][16 ks + 8 (l / 32) .. + 7].
 void pack_mfma_fragments(const bf16_t* w, int Cout, int K, bf16_t* dst);
 
+// ---------------------------------------------------------------- first layers of the bf16 classifier
+// frames u8 [n,3,H,W], x = (u8 - mean) / stdv in bf16, 3x3 layers with padding 1 and ReLU; weights bf16 [Cout][3][3][64], the
+// first layer's input channels 3..63 zeros; out NHWC.  launch_first_layer: Cout a multiple of 32.  launch_first_pair: both
+// layers have 64 channels; with `pool` the 2x2 / stride 2 maximum of the second (a trailing odd row / column is dropped).
+hipError_t launch_first_layer(const uint8_t* frames, int n, int H, int W, const bf16_t* w, const float* bias, int Cout, float mean, float stdv,
+                              bf16_t* out, hipStream_t s);
+hipError_t launch_first_pair(const uint8_t* frames, int n, int H, int W, const bf16_t* w1, const float* b1, const bf16_t* w2, const float* b2,
+                             bool pool, float mean, float stdv, bf16_t* out, hipStream_t s);
+
 // ---------------------------------------------------------------- stem + pool
 // frames u8 [n,3,H,W].  x = (u8 - mean) / stdv, zero padding after normalisation.
 // fp32 models: launch_stem (out float [n,Hs,Ws,64] NHWC with ReLU applied; w: fp32 [(c*7+ky)*7+kx][64]) followed by

@@ -149,3 +149,32 @@ def test_classifier_argument_errors():
     lab, conf = c.classify_chunk(tiny, 1)              # exit 1 has no pool in front of it
     torch.cuda.synchronize()
     assert 0 <= int(lab[0]) < spec.n_classes
+
+
+@pytest.mark.parametrize("channels,pools", [((64, 64, 64), (2,)), ((64, 64, 64), (1, 2)), ((128, 64, 64), (1,)), ((64, 128, 64), ())])
+@pytest.mark.parametrize("n,H,W", [(3, 4, 5), (2, 16, 32), (5, 17, 33), (2, 35, 70), (70, 15, 31)])
+def test_first_layers_at_tile_edges(channels, pools, n, H, W):
+    """The bf16 layers that read the frames (16 x 32 and 8 x 32 tiles; 70 frames: one tile each; (2, 35, 70) and 5 frames of
+    17 x 33: ragged ones), alone, as a pair and with the pool, against the oracle's steps with bf16 storage.  Sums taken in
+    another order turn single roundings of a stored value: at most 2^-8 of it in each of the two layers behind the first."""
+    spec = ClassifierSpec(precision=1, channels=channels, pool_after=pools, taps=(1, 2, 3), n_classes=7)
+    c, blob = _clf(spec, 72)
+    fr = np.random.RandomState(H * W).randint(0, 256, (n, 3, H, W)).astype(np.uint8)
+    for ep in (1, 2, 3):
+        log = c.classify_chunk(to_dev(fr), ep, want_logits=True)[2]
+        torch.cuda.synchronize()
+        some = [0, n - 1]
+        ref = oc.classify(blob, fr[some], ep)["logits"]
+        assert relerr(log.cpu().numpy()[some], ref) <= 2.0 ** -7, (ep, relerr(log.cpu().numpy()[some], ref))
+
+
+def test_first_pair_walks_several_tiles_per_block():
+    """More tiles than blocks (60 frames of 3 x 4 tiles on 256 blocks): every frame's answer is that of the frame alone."""
+    spec = ClassifierSpec(precision=1, channels=(64, 64, 64), pool_after=(2,), taps=(2, 3), n_classes=7)
+    c, _ = _clf(spec, 72)
+    fr = to_dev(np.random.RandomState(3).randint(0, 256, (60, 3, 41, 100)).astype(np.uint8))
+    for ep in (1, 2):
+        log = c.classify_chunk(fr, ep, want_logits=True)[2]
+        one = torch.cat([c.classify_chunk(fr[i:i + 1], ep, want_logits=True)[2] for i in (0, 17, 59)])
+        torch.cuda.synchronize()
+        assert torch.equal(log[[0, 17, 59]], one)
