@@ -3,11 +3,8 @@
 // [n,3,H,W]; outputs are NHWC.
 //
 // bf16 models: one persistent matrix-core kernel does normalisation, stem, ReLU and pool
-// (stem_pool_mfma_kernel).  fp32 models: the stem contracts only K = 3*7*7 = 147 values per
-// output and runs on the vector ALUs (stem_kernel: a 256-thread block owns a 16x16 tile of
-// output pixels, stages the normalised 37x37x3 patch in LDS once, and every thread
-// accumulates all 64 output channels of its pixel; weights are wavefront-uniform), followed
-// by maxpool_kernel.
+// (stem_pool_mfma_kernel).  fp32 models: stem_kernel on the fp32 matrix instructions, followed by
+// maxpool_kernel.
 #include <algorithm>
 #include <type_traits>
 
@@ -18,65 +15,62 @@ namespace thia {
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-constexpr int ST = 16;               // output tile side
-constexpr int SP = 2 * ST + 5;       // input patch side (stride 2, 7 taps)
-constexpr int SC = 64;               // stem output channels
+constexpr int SC = 64;                           // stem output channels
+constexpr int SR = 2, SW = 32;                   // fp32 stem: output tile (rows, columns)
+constexpr int SPR = 2 * SR + 5, SPW = 2 * SW + 6;  // input patch (stride 2, 7 taps; one column of padding)
+constexpr int SK = 147, SKP = 148;               // contraction length, padded to whole matrix steps
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
-template <bool BF16>
-__global__ __launch_bounds__(256) void stem_kernel(const uint8_t* __restrict__ frames, int H, int W, int Hs, int Ws,
-                                                   const float* __restrict__ w, const float* __restrict__ bias,
-                                                   float mean, float stdv, void* __restrict__ out_) {
-    __shared__ float patch[3][SP][SP + 1];
-    const int t = threadIdx.x, tx = t & (ST - 1), ty = t / ST;
-    const int ox0 = blockIdx.x * ST, oy0 = blockIdx.y * ST, img = blockIdx.z;
-    const int ix0 = 2 * ox0 - 3, iy0 = 2 * oy0 - 3;
-    const uint8_t* f = frames + (size_t)img * 3 * H * W;
-    for (int i = t; i < 3 * SP * SP; i += 256) {
-        const int c = i / (SP * SP), r = i - c * SP * SP, py = r / SP, px = r - py * SP;
-        const int iy = iy0 + py, ix = ix0 + px;
-        float v = 0.f;  // zero padding applies to the normalised tensor
-        if ((unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)W) {
-            v = ((float)f[((size_t)c * H + iy) * W + ix] - mean) / stdv;
-            if (BF16) v = bf16_to_f32(f32_to_bf16(v));
-        }
-        patch[c][py][px] = v;
+// fp32 stem on the fp32 matrix instructions: wavefront wv of a block owns one row of 32 pixels and half of the channels, and
+// takes K two at a time in the order (channel, filter row, filter column), each pair in sequence: the sums are those of a
+// chain of fused multiply-adds.  Bound by the matrix pipe (64 cycles per step); small tiles, because a call with few pixels
+// has little else to fill the chip.  One thread per pixel with all 64 channels, its weights through the scalar cache, left
+// three quarters of a small call's SIMDs idle and waited for every tap's weights.  Measured, before / now: four 128 x 128 frames
+// 64 / 12 us, two of 540 x 960 112 / 73.
+__global__ __launch_bounds__(256) void stem_kernel(const uint8_t* __restrict__ frames, int H, int W, int Hs, int Ws, int tiles_x, int tiles_y,
+                                                   int total, const float* __restrict__ w, const float* __restrict__ bias, float mean, float stdv,
+                                                   float* __restrict__ out) {
+    __shared__ float patch[3 * SPR * SPW];
+    __shared__ __align__(16) float wl[SKP * SC];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, g = lane >> 5, col = lane & 31;
+    for (int i = t; i < SKP * SC / 4; i += 256) {
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+        if (i < SK * SC / 4) v = *reinterpret_cast<const f32x4_t*>(w + 4 * i);
+        *reinterpret_cast<f32x4_t*>(wl + 4 * i) = v;
     }
-    __syncthreads();
-
-    float acc[SC];
-#pragma unroll
-    for (int ch = 0; ch < SC; ++ch) acc[ch] = 0.f;
-    for (int c = 0; c < 3; ++c)
-        for (int ky = 0; ky < 7; ++ky)
-#pragma unroll
-            for (int kx = 0; kx < 7; ++kx) {
-                const float x = patch[c][2 * ty + ky][2 * tx + kx];
-                const float* wt = w + ((c * 7 + ky) * 7 + kx) * SC;
-#pragma unroll
-                for (int ch = 0; ch < SC; ++ch) acc[ch] = fmaf(x, wt[ch], acc[ch]);
-            }
-
-    const int oy = oy0 + ty, ox = ox0 + tx;
-    if (oy >= Hs || ox >= Ws) return;
-    const size_t o = (((size_t)img * Hs + oy) * Ws + ox) * SC;
-    if (BF16) {
-        bf16_t* out = static_cast<bf16_t*>(out_) + o;
-#pragma unroll
-        for (int ch = 0; ch < SC; ch += 8) {
-            u32x4_t v;
-            float h[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) h[q] = fmaxf(acc[ch + q] + bias[ch + q], 0.f);
-            v.x = pack_bf16x2(h[0], h[1]); v.y = pack_bf16x2(h[2], h[3]); v.z = pack_bf16x2(h[4], h[5]); v.w = pack_bf16x2(h[6], h[7]);
-            *reinterpret_cast<u32x4_t*>(out + ch) = v;
+    const int row = wv >> 1, ch0 = (wv & 1) * 32;
+    const float* pl = patch + 2 * row * SPW + 2 * col;
+    const float* al = wl + g * SC + ch0 + col;
+    auto tap = [](int k) { return k < SK ? (k / 49) * SPR * SPW + ((k / 7) % 7) * SPW + k % 7 : 0; };   // (the padding's weights are 0)
+    for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+        const int img = tile / (tiles_x * tiles_y), rem = tile - img * tiles_x * tiles_y;
+        const int oy0 = (rem / tiles_x) * SR, ox0 = (rem % tiles_x) * SW, ix0 = 2 * ox0 - 3, iy0 = 2 * oy0 - 3;
+        const uint8_t* f = frames + (size_t)img * 3 * H * W;
+        for (int i = t; i < 3 * SPR * SPW; i += 256) {
+            const int c = i / (SPR * SPW), r = i - c * SPR * SPW, py = r / SPW, px = r - py * SPW;
+            const int iy = iy0 + py, ix = ix0 + px;
+            float v = 0.f;  // zero padding applies to the normalised tensor
+            if ((unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)W) v = ((float)f[((size_t)c * H + iy) * W + ix] - mean) / stdv;
+            patch[i] = v;
         }
-    } else {
-        float* out = static_cast<float*>(out_) + o;
+        __syncthreads();
+        f32x16_t acc;
 #pragma unroll
-        for (int ch = 0; ch < SC; ch += 4) {
-            f32x4_t v = {fmaxf(acc[ch] + bias[ch], 0.f), fmaxf(acc[ch + 1] + bias[ch + 1], 0.f),
-                         fmaxf(acc[ch + 2] + bias[ch + 2], 0.f), fmaxf(acc[ch + 3] + bias[ch + 3], 0.f)};
-            *reinterpret_cast<f32x4_t*>(out + ch) = v;
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+        for (int s = 0; s < SKP / 2; ++s) {
+            const int o0 = tap(2 * s), o1 = tap(2 * s + 1);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(al[2 * s * SC], pl[g ? o1 : o0], acc, 0, 0, 0);
+        }
+        __syncthreads();   // every wavefront has read the patch
+        const int oy = oy0 + row, ox = ox0 + col;
+        if (oy >= Hs || ox >= Ws) continue;
+        float* o = out + (((size_t)img * Hs + oy) * Ws + ox) * SC + ch0 + 4 * g;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {   // accumulator element e: channel 8 (e / 4) + 4 g + e % 4
+            const f32x4_t b = *reinterpret_cast<const f32x4_t*>(bias + ch0 + 8 * v + 4 * g);
+            const f32x4_t r = {fmaxf(acc[4 * v] + b.x, 0.f), fmaxf(acc[4 * v + 1] + b.y, 0.f), fmaxf(acc[4 * v + 2] + b.z, 0.f), fmaxf(acc[4 * v + 3] + b.w, 0.f)};
+            *reinterpret_cast<f32x4_t*>(o + 8 * v) = r;
         }
     }
 }
@@ -314,9 +308,11 @@ hipError_t launch_stem_pool(const uint8_t* frames, int n, int H, int W, const bf
 hipError_t launch_stem(const uint8_t* frames, int n, int H, int W, const float* w, const float* bias, float mean, float stdv, void* out,
                        hipStream_t s) {
     const int Hs = (H + 6 - 7) / 2 + 1, Ws = (W + 6 - 7) / 2 + 1;
-    dim3 grid((Ws + ST - 1) / ST, (Hs + ST - 1) / ST, n);
-    if (grid.y > 65535u || grid.z > 65535u) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(stem_kernel<false>, grid, dim3(256), 0, s, frames, H, W, Hs, Ws, w, bias, mean, stdv, out);
+    const int tx = (Ws + SW - 1) / SW, ty = (Hs + SR - 1) / SR;
+    const long long tiles = (long long)tx * ty * n;
+    if (n <= 0 || n > 65535 || tiles <= 0 || tiles >= (1ll << 30)) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)std::min<long long>(tiles, 768);   // three resident blocks (LDS) on each of the 256 CUs
+    hipLaunchKernelGGL(stem_kernel, dim3(grid), dim3(256), 0, s, frames, H, W, Hs, Ws, tx, ty, (int)tiles, w, bias, mean, stdv, static_cast<float*>(out));
     return hipGetLastError();
 }
 
