@@ -82,27 +82,37 @@ __global__ __launch_bounds__(256) void topk_hist_kernel(const float* __restrict_
         if (lh[i]) atomicAdd(&hist[(size_t)f * HIST_BINS + i], lh[i]);
 }
 
+// Sum of `v` over the threads behind this one among a block's first 256 (whole wavefronts call it; the block's other threads
+// take part in the barrier only).  One thread adding the 256 sums up one by one was 2 to 3 us of every digit.
+__device__ inline uint32_t sum_behind(uint32_t v, uint32_t* wave_sum /* LDS [4] */) {
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint32_t incl = v;
+    if (t < 256) {
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_down((int)incl, d);
+            if (lane + d < 64) incl += o;
+        }
+        if (lane == 0) wave_sum[wv] = incl;
+    }
+    __syncthreads();
+    uint32_t behind = incl - v;
+    for (int q = wv + 1; q < 4; ++q) behind += wave_sum[q];
+    return behind;
+}
+
 // One block per frame: find digit d with  #(digit > d) < k_rem <= #(digit >= d); clears the histogram.
 __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ hist, uint64_t* __restrict__ state, int pass, int k_want,
                                                         int cand_cap) {
     const int f = blockIdx.x;
     if (state[4 * f + 2]) return;  // uniform: written only by this block in earlier launches
-    __shared__ uint32_t part[256];
-    __shared__ uint32_t above[256];
+    __shared__ uint32_t wave_sum[4];
     const int t = threadIdx.x;
     uint32_t h[8], sum = 0;
     uint32_t* hf = hist + (size_t)f * HIST_BINS;
     const uint32_t k_rem = (uint32_t)state[4 * f + 1];  // read before the barriers: written below by one thread
 #pragma unroll
     for (int q = 0; q < 8; ++q) { h[q] = hf[8 * t + q]; sum += h[q]; hf[8 * t + q] = 0u; }
-    part[t] = sum;
-    __syncthreads();
-    if (t == 0) {
-        uint32_t run = 0;
-        for (int i = 255; i >= 0; --i) { above[i] = run; run += part[i]; }
-    }
-    __syncthreads();
-    uint32_t run = above[t];  // elements in bins above this thread's 8 bins
+    uint32_t run = sum_behind(sum, wave_sum);  // elements in bins above this thread's 8 bins
     for (int q = 7; q >= 0; --q) {
         if (run < k_rem && k_rem <= run + h[q]) {
             const uint64_t digit = (uint64_t)(8 * t + q);
@@ -237,9 +247,9 @@ __global__ __launch_bounds__(1024) void topk_sort_decode_kernel(const uint64_t* 
 
 // Radix-select passes first .. N_PASS - 1 of one frame by one 1024-thread block: LDS histogram of the digit of the elements
 // that match the prefix, then the digit holding the k-th element.  prefix / k_rem / done are the block's shared search
-// state (k_rem and prefix as left by the passes before `first`); hist [HIST_BINS], part and above [256] are LDS scratch.
+// state (k_rem and prefix as left by the passes before `first`); hist [HIST_BINS] and wave_sum [4] are LDS scratch.
 __device__ inline void block_select_passes(const float* __restrict__ lg, long nA, int first, int k_want, int cand_cap, uint32_t* hist,
-                                           uint32_t* part, uint32_t* above, uint64_t* s_prefix, uint32_t* s_krem, uint32_t* s_done) {
+                                           uint32_t* wave_sum, uint64_t* s_prefix, uint32_t* s_krem, uint32_t* s_done) {
     const int t = threadIdx.x;
     for (int pass = first; pass < N_PASS; ++pass) {
         if (*s_done) break;                                                  // uniform: written before the last barrier
@@ -266,16 +276,9 @@ __device__ inline void block_select_passes(const float* __restrict__ lg, long nA
         if (t < 256) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) { h[q] = hist[8 * t + q]; sum += h[q]; }
-            part[t] = sum;
         }
-        __syncthreads();
-        if (t == 0) {
-            uint32_t run = 0;
-            for (int i = 255; i >= 0; --i) { above[i] = run; run += part[i]; }
-        }
-        __syncthreads();
+        uint32_t run = sum_behind(sum, wave_sum);
         if (t < 256) {
-            uint32_t run = above[t];
             for (int q = 7; q >= 0; --q) {
                 if (run < k_rem && k_rem <= run + h[q]) {                    // exactly one (thread, q) satisfies this
                     *s_prefix = prefix | ((uint64_t)(8 * t + q) << shift);
@@ -297,13 +300,12 @@ __global__ __launch_bounds__(1024) void topk_finish_kernel(const float* __restri
     const int f = blockIdx.x, t = threadIdx.x;
     if (state[4 * f + 2]) return;   // uniform
     __shared__ uint32_t hist[HIST_BINS];
-    __shared__ uint32_t part[256];
-    __shared__ uint32_t above[256];
+    __shared__ uint32_t wave_sum[4];
     __shared__ uint64_t s_prefix;
     __shared__ uint32_t s_krem, s_done;
     if (t == 0) { s_prefix = state[4 * f + 0]; s_krem = (uint32_t)state[4 * f + 1]; s_done = 0u; }
     __syncthreads();
-    block_select_passes(logits + (size_t)f * nA, nA, 2, k_want, cand_cap, hist, part, above, &s_prefix, &s_krem, &s_done);
+    block_select_passes(logits + (size_t)f * nA, nA, 2, k_want, cand_cap, hist, wave_sum, &s_prefix, &s_krem, &s_done);
     if (t == 0) { state[4 * f + 0] = s_prefix; state[4 * f + 1] = (uint64_t)s_krem; state[4 * f + 2] = 1ull; }
 }
 
@@ -318,15 +320,14 @@ __global__ __launch_bounds__(1024) void topk_fused_kernel(const float* __restric
     extern __shared__ __align__(16) unsigned char smem_raw[];
     uint64_t* keys = reinterpret_cast<uint64_t*>(smem_raw);                  // [2][lds_keys(cap)]
     uint32_t* hist = reinterpret_cast<uint32_t*>(keys + 2 * (size_t)lds_keys(cap));   // [HIST_BINS]
-    __shared__ uint32_t part[256];
-    __shared__ uint32_t above[256];
+    __shared__ uint32_t wave_sum[4];
     __shared__ uint64_t s_prefix;
     __shared__ uint32_t s_krem, s_done, s_count;
     const int f = blockIdx.x, t = threadIdx.x;
     const float* lg = logits + (size_t)f * nA;
     if (t == 0) { s_prefix = 0ull; s_krem = (uint32_t)k_want; s_done = 0u; s_count = 0u; }
     __syncthreads();
-    block_select_passes(lg, nA, 0, k_want, cap, hist, part, above, &s_prefix, &s_krem, &s_done);
+    block_select_passes(lg, nA, 0, k_want, cap, hist, wave_sum, &s_prefix, &s_krem, &s_done);
     const uint64_t thr = s_prefix;
     for (int i = t; i < lds_keys(cap); i += 1024) keys[i] = 0ull;
     __syncthreads();
