@@ -130,6 +130,7 @@ __global__ __launch_bounds__(256) void classifier_head_kernel(const float* __res
     const int f = blockIdx.x, t = threadIdx.x;
     for (int c = t; c < C; c += 256) {
         float sum = 0.f;
+#pragma unroll 16
         for (int s = 0; s < kSlabs; ++s) sum += partial[((size_t)f * kSlabs + s) * C + c];
         sg[c] = sum / (float)HW;
     }
