@@ -485,24 +485,41 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 if constexpr (F16) {
-                    // lane group g = lane / 16 supplies k slot g: k = 0, 4, 1, 5 of the 8-wide group, then 2, 6, 3, 7
-                    const int row = lane & 15, koff = ((2 * kk + ((lane >> 4) & 1)) ^ (row & 7) ^ (row >> 3)) * 16;
-                    g.k[kk].a[0] = *reinterpret_cast<const u32x4_t*>(sA + (size_t)(buf * BN + wn * WN + row) * LDS_ROW + koff);
-                    g.k[kk].b[0] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + row) * LDS_ROW + koff);
+                    // k groups come in pairs: lanes 0..31 read group kk, lanes 32..63 group kk + 1 (16 bytes of row lane % 16,
+                    // half (lane / 16) & 1 of the group); pair_k deals them out
+                    if ((kk & 1) == 0) {
+                        const int row = lane & 15, koff = ((2 * (kk + (lane >> 5)) + ((lane >> 4) & 1)) ^ (row & 7) ^ (row >> 3)) * 16;
+                        g.k[kk].a[0] = *reinterpret_cast<const u32x4_t*>(sA + (size_t)(buf * BN + wn * WN + row) * LDS_ROW + koff);
+                        g.k[kk].b[0] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + row) * LDS_ROW + koff);
+                    }
                 } else {
                     read_frags(buf, kk, g.k[kk]);
                 }
             }
         };
+        // (lanes 0..31 of x, lanes 0..31 of y) and (lanes 32..63 of x, lanes 32..63 of y): lane group g = lane / 16 supplies k
+        // slot g, k = 0, 4, 1, 5 of the group's 8, then 2, 6, 3, 7 - the order of the 32x32 tiles - for group kk and kk + 1.
+        // (Every lane reading 16 bytes and using half of them needs twice the LDS reads: 130 us against 118 at 200 x 1024,
+        // K 12544; two 4-byte reads per lane conflict in the banks.)
+        auto pair_k = [&](uint32_t x, uint32_t y, float& first, float& second) {
+#if defined(__HIP_DEVICE_COMPILE__)
+            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            first = __uint_as_float(r[0]);
+            second = __uint_as_float(r[1]);
+#endif
+        };
         auto mma_tile = [&](const TileFrags& g) {
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 if constexpr (F16) {
-                    // (16-byte reads, half of each used: two 4-byte reads per lane conflict in the banks, 360 against 292 us)
-                    const f32x4_t fa = __builtin_bit_cast(f32x4_t, g.k[kk].a[0]), fb = __builtin_bit_cast(f32x4_t, g.k[kk].b[0]);
-                    const bool odd = lane >= 32;
-                    acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? fa.y : fa.x, odd ? fb.y : fb.x, acc4, 0, 0, 0);
-                    acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? fa.w : fa.z, odd ? fb.w : fb.z, acc4, 0, 0, 0);
+                    if ((kk & 1) == 0) {
+                        const u32x4_t fa = g.k[kk].a[0], fb = g.k[kk].b[0];
+                        float a0[4], b0[4];   // group kk: [0], [1]; group kk + 1: [2], [3]
+                        pair_k(fa.x, fa.y, a0[0], a0[2]); pair_k(fa.z, fa.w, a0[1], a0[3]);
+                        pair_k(fb.x, fb.y, b0[0], b0[2]); pair_k(fb.z, fb.w, b0[1], b0[3]);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[q], b0[q], acc4, 0, 0, 0);
+                    }
                 } else {
                     mma_frags(g.k[kk]);
                 }
@@ -522,8 +539,10 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
         read_tile(0, g0);
         int buf = 0;                                            // buffer of tile kt
         auto step = [&](int kt, const TileFrags& now, TileFrags& next) {
+            // (waited for on both sides of the branch: where only one side does, the compiler puts a wait for everything in
+            // front of the products and the next tile's reads are no longer behind them)
+            in_registers(kt + STAGES - 1 < KT);
             if (kt + 1 < KT) {
-                in_registers(kt + STAGES - 1 < KT);
                 barrier();
                 if (PROD == 0 && kt + STAGES < KT) request(buf);
                 buf = buf + 1 == STAGES ? 0 : buf + 1;
