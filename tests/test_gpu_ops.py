@@ -417,3 +417,20 @@ def test_select_detections_op_edges_of_the_class_lists(post, Kc, D):
         rb, rs_, rl, rn = oracle.select_detections(scores[f, :roi_n[f]], boxes[f, :roi_n[f]], spec.score_thr, spec.det_nms_thr, D)
         assert cnt[f].item() == rn, f
         assert np.array_equal(ol[f].cpu().numpy(), rl) and np.array_equal(ob[f].cpu().numpy(), rb) and np.array_equal(osc[f].cpu().numpy(), rs_), f
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_roialign_split_over_blocks_is_the_same(precision):
+    """Few ROIs are split over several blocks each, many are not: a frame's values do not depend on how many came with it."""
+    m, _ = _model(precision)
+    spec = MINI_BF16 if precision else MINI_FP32
+    rs = np.random.RandomState(10)
+    post, Hk, Wk, stride = spec.post_nms, 19, 27, 8
+    n = 600 // post + 1
+    feat = to_dev(rs.randn(n, Hk, Wk, spec.head_ch).astype(np.float32), m.elem)
+    rois = to_dev(_rand_boxes(rs, n * post, 150.0).reshape(n, post, 4))
+    many = m.op_roialign(feat, rois, stride)
+    for f in (0, n - 1):
+        one = m.op_roialign(feat[f:f + 1].contiguous(), rois[f:f + 1].contiguous(), stride)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], many[f])
