@@ -16,7 +16,7 @@
 // non-empty boxes in order.
 //
 // NMS: a k x k upper-triangular overlap bit matrix (64-bit words) is computed by
-// 64-thread blocks, then one block per frame scans it 64 rows at a time from LDS.
+// one block per 64 x 64 tile, then one block per frame scans it 64 rows at a time from LDS.
 #include "device_util.h"
 
 namespace thia {
@@ -384,32 +384,38 @@ hipError_t launch_rpn_proposals(const float* logits, const float* deltas, int n,
 // ------------------------------------------------------------------------- NMS
 // Word (row i, tile bx): which boxes of tile bx box i overlaps, for the tiles behind its own.  In its own tile the EARLIER
 // boxes instead (the overlap test is symmetric): what the greedy decision of row i depends on.
-__global__ __launch_bounds__(64) void nms_mask_kernel(const float* __restrict__ boxes, const int32_t* __restrict__ counts,
-                                                      int cap, int words, float thr, uint64_t* __restrict__ mask) {
+// A tile's word is a chain of 64 overlap tests: four wavefronts take 16 columns each (one wavefront for all of them left a
+// SIMD with one chain: 12.4 us for 1000 boxes of one frame, now 4.5; 27.9 -> 20.2 of 32 frames).
+__global__ __launch_bounds__(256) void nms_mask_kernel(const float* __restrict__ boxes, const int32_t* __restrict__ counts,
+                                                       int cap, int words, float thr, uint64_t* __restrict__ mask) {
     const int bx = blockIdx.x, by = blockIdx.y, f = blockIdx.z;
     if (bx < by) return;
     const int cnt = counts[f] < cap ? counts[f] : cap;
     if (64 * by >= cnt || 64 * bx >= cnt) return;
     __shared__ Box cb[64];
-    const int t = threadIdx.x;
+    __shared__ uint32_t part[4][64];
+    const int t = threadIdx.x, lane = t & 63, quarter = t >> 6;
     const float* bf = boxes + (size_t)f * cap * 4;
-    const int cj = 64 * bx + t;
-    if (cj < cnt) {
+    if (t < 64) {
+        const int cj = 64 * bx + t < cnt ? 64 * bx + t : cnt - 1;   // (columns past the end are masked out below)
         const float4 v = *reinterpret_cast<const float4*>(bf + 4 * (size_t)cj);
         cb[t] = {v.x, v.y, v.z, v.w};
     }
-    __syncthreads();
-    const int i = 64 * by + t;
-    if (i >= cnt) return;
-    const float4 v = *reinterpret_cast<const float4*>(bf + 4 * (size_t)i);
+    const int i = 64 * by + lane;
+    const float4 v = *reinterpret_cast<const float4*>(bf + 4 * (size_t)(i < cnt ? i : cnt - 1));
     const Box me = {v.x, v.y, v.z, v.w};
-    uint64_t bits = 0ull;
-    const int jn = (cnt - 64 * bx) < 64 ? (cnt - 64 * bx) : 64;
-    for (int b = 0; b < jn; ++b) {
-        const int j = 64 * bx + b;
-        if ((bx == by ? j < i : j > i) && iou_over(me, cb[b], thr)) bits |= 1ull << b;
-    }
-    mask[((size_t)f * cap + i) * words + bx] = bits;
+    __syncthreads();
+    uint32_t bits = 0u;
+#pragma unroll
+    for (int b = 0; b < 16; ++b) bits |= iou_over(me, cb[16 * quarter + b], thr) ? 1u << b : 0u;
+    part[quarter][lane] = bits;
+    __syncthreads();
+    if (t >= 64 || i >= cnt) return;
+    uint64_t word = (uint64_t)(part[0][t] | part[1][t] << 16) | (uint64_t)(part[2][t] | part[3][t] << 16) << 32;
+    const int jn = cnt - 64 * bx;
+    if (jn < 64) word &= (1ull << jn) - 1ull;
+    if (bx == by) word &= (1ull << t) - 1ull;   // its own tile: the earlier boxes
+    mask[((size_t)f * cap + i) * words + bx] = word;
 }
 
 // One 512-thread block per frame.  The bit matrix is consumed 64 rows at a time: wavefront 0 decides the rows of a tile from
@@ -518,7 +524,7 @@ hipError_t launch_nms(const float* boxes, const int32_t* counts, int n, int cap,
                       int32_t* out_keep, int32_t* out_n, float* rois_out, hipStream_t s) {
     if (n <= 0 || cap <= 0 || cap > 4096 || max_keep <= 0 || max_keep > 4096 || n > 65535) return hipErrorInvalidValue;
     const int words = (cap + 63) / 64;
-    hipLaunchKernelGGL(nms_mask_kernel, dim3(words, words, n), dim3(64), 0, s, boxes, counts, cap, words, thr, mask);
+    hipLaunchKernelGGL(nms_mask_kernel, dim3(words, words, n), dim3(256), 0, s, boxes, counts, cap, words, thr, mask);
     const size_t lds = (size_t)64 * words * 8 + (size_t)max_keep * 4;
     hipLaunchKernelGGL(nms_reduce_kernel, dim3(n), dim3(NMS_THREADS), lds, s, mask, boxes, counts, cap, words, max_keep, out_keep, out_n,
                        rois_out);
