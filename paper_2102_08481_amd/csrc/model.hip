@@ -564,6 +564,11 @@ Tail stage_tail(const thia_model* m, int s, int ep_here) {
     return tl;
 }
 
+// Tiles of 8 x 16 pixels up to which a 128-wide block runs layer by layer: the single kernel's chain of three layers takes as
+// long for one tile as for one on every CU, the layers spread few pixels over small tiles.  Measured, single kernel / layers: 72
+// tiles (one 540 x 960 frame) 28.1 / 24.1 us, 144 tiles 30.1 / 32.0.
+constexpr long long kFewTiles128 = 96;
+
 // Bottleneck stage s (0-based) applied to t.x; the stage's output becomes t.x.  `tail` (optional) is handed to the
 // stage's last block if that block runs as a single kernel of the 64-wide variant; *tail_applied tells whether it was.
 int run_stage(thia_model* m, int s, int nb, Trunk& t, const Tail* tail = nullptr, bool* tail_applied = nullptr) {
@@ -582,7 +587,8 @@ int run_stage(thia_model* m, int s, int nb, Trunk& t, const Tail* tail = nullptr
             fa.x = static_cast<const bf16_t*>(x); fa.y = static_cast<bf16_t*>(y);
             fa.w1f = B.f1; fa.w2f = B.f2; fa.w3f = B.f3; fa.b1 = B.c1.b; fa.b2 = B.c2.b; fa.b3 = B.c3.b;
             fa.N = nb; fa.H = h; fa.W = w; fa.first = B.has_sc ? 1 : 0;
-            if (B.stride == 1 && fused_block_supported(fa, B.c1.co)) {
+            const long long tiles = (long long)nb * ((h + 7) / 8) * ((w + 15) / 16);
+            if (B.stride == 1 && (B.c1.co != 128 || tiles > kFewTiles128 || m->fuse_always) && fused_block_supported(fa, B.c1.co)) {
                 bool with_tail = false;
                 if (tail && tail->wtf && bi + 1 == nblocks && !B.has_sc && B.c1.co == 64) {
                     FusedBlockArgs ft = fa;
