@@ -413,3 +413,24 @@ def test_argument_errors_return_codes():
     b, s, l = m.detect_chunk(frames, 0)                    # skip
     torch.cuda.synchronize()
     assert (l == -1).all() and (s == 0).all()
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_128_wide_blocks_on_either_side_of_the_tile_rule(n):
+    """One frame has 64 tiles in the 128-wide stage (layer by layer), two have 128 (single kernel): both as with the single
+    kernel forced on and with every layer on its own, to one bf16 ulp of the exit tensor's max."""
+    spec = ModelSpec(precision=1, blocks=(1, 3, 1, 1), fc_dim=128, pre_nms=300, post_nms=100, n_classes=5)
+    m, _ = gpu_model(spec, 0xBEEF + 57)
+    frames = to_dev(make_frames(SceneSpec(512, 1024, n, 4, 10, 10, 90), 47))
+    feats = []
+    m.set_debug(True)
+    for mode in (1, 2, 0):
+        m.set_fusion(mode)
+        m.detect_chunk(frames, 2)
+        torch.cuda.synchronize()
+        feats.append(m.tap("feat").astype(np.float32))
+    m.set_fusion(1)
+    m.set_debug(False)
+    assert np.isfinite(feats[0]).all()
+    for other in feats[1:]:
+        assert relerr(feats[0], other) <= 2.0 ** -7
