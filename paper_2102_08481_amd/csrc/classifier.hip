@@ -238,8 +238,7 @@ int run_to_tap(thia_classifier* c, const uint8_t* frames, int nb, int H, int W, 
     int h = H, w = W, first = 0;
     if (c->precision) {
         // bf16: the first layer reads the frames; with a second one behind it and 64 channels in both, the two layers and the
-        // pool that follows are one launch (64 pictures of 224 x 224: 258 us, 1 232 us as packing, two
-        // layers and pool)
+        // pool that follows are one launch (64 pictures of 224 x 224: 269 us, 1 232 us as packing, two layers and pool)
         const ConvLayer &L1 = c->conv[0], &L2 = c->conv[1];
         hipError_t e;
         if (tap >= 2 && L1.co == 64 && L2.co == 64 && !c->pool[0]) {

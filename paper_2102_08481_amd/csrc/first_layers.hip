@@ -1,14 +1,20 @@
 // First layers of the bf16 image classifier, straight from the uint8 frames (gfx950 matrix cores).
 //
 // The first 3x3 layer contracts 27 values per output.  Padded to a K tile of 64 channels per tap it cost 576, and its padded
-// input had to be written first; here a normalised pixel is 4 bf16 (the fourth is 0) in LDS and K runs over 12 taps x 4, the
-// last three with zero weights: three 32x32x16 products per tile, whose 8 K values per lane are two 8-byte LDS reads.
+// input had to be written first; here a normalised pixel is 4 bf16 (the fourth is 0) in LDS and K runs over 10 taps x 8 (four
+// zeros behind each pixel, the tenth tap's weights zero): five 32x32x16 products per tile, one 8-byte LDS read per lane each.
+//
+// Both layers give the values of the general kernel bit for bit, so an answer does not depend on which of them ran: taps in
+// filter order, a tap's channels 16 at a time, each sum on its own.  The matrix instruction adds the 8 products of lanes 0..31
+// first and then those of lanes 32..63, each 8 as one sum: two taps in the two halves round like a product per tap, two taps
+// within a half (three products per tile instead of five) do not.
 //
 // first_layer_kernel: that layer alone.  Bound by writing its output.
 // first_pair_kernel: 3 -> 64 -> 64 layers (and the 2x2 max-pool behind them) in one launch.  The 64-channel tensor between
 // them is as large as the network's largest and is never written: a block computes it for its own tile and halo in LDS.
-// Bound by the matrix pipe (237 GFLOP at 0.92 PFLOP/s); 64 pictures of 224 x 224: 258 us, against 1 232 us as packing, two
-// layers on the general kernel and pool.
+// Bound by the matrix pipe (237 GFLOP at 0.88 PFLOP/s); 64 pictures of 224 x 224: 269 us, against 1 232 us as packing, two
+// layers on the general kernel and pool (258 us with sums in another order: four taps per product in the first layer, input
+// rows innermost in the second).
 #include <algorithm>
 #include <type_traits>
 
@@ -38,46 +44,45 @@ __device__ inline void mma(f32x16_t& acc, const u32x4_t& a, const u32x4_t& b) {
 
 constexpr int kTaps = 9, kCin = 64;   // weights of both layers: bf16 [Cout][9][64] (the first layer's channels 3..63 are zeros)
 
-// Weight fragment of K step s (taps 4 s .. 4 s + 3) of the first layer: row = this lane's output channel, taps 4 s + 2 g, + 1.
-__device__ inline u32x4_t first_weights(const bf16_t* __restrict__ w, int ch, int s, int g) {
-    u32x4_t r = {0u, 0u, 0u, 0u};
-    const int tap = 4 * s + 2 * g;
-    if (tap < kTaps) {
-        const u32x2_t v = *reinterpret_cast<const u32x2_t*>(w + ((size_t)ch * kTaps + tap) * kCin);
-        r.x = v.x; r.y = v.y;
+constexpr int kSteps1 = 5;   // products per tile of the first layer: taps 2 s (lanes 0..31) and 2 s + 1 (lanes 32..63)
+
+// First layer's weights of this lane's output channel and its half's tap of step s.
+__device__ inline u32x2_t first_weights(const bf16_t* __restrict__ w, int ch, int s, int g) {
+    const int tap = 2 * s + g;
+    if (tap >= kTaps) return u32x2_t{0u, 0u};
+    return *reinterpret_cast<const u32x2_t*>(w + ((size_t)ch * kTaps + tap) * kCin);
+}
+
+// Byte offsets, from a pixel's (tap 0) position in the raw patch of COLS columns, of the taps that lane half g feeds to the
+// steps.  The tenth tap has zero weights and re-reads the ninth.
+template <int COLS>
+__device__ inline void first_offsets(int g, int off[kSteps1]) {
+#pragma unroll
+    for (int s = 0; s < kSteps1; ++s) {
+        const int a = 2 * s, b = 2 * s + 1 < kTaps ? 2 * s + 1 : kTaps - 1;
+        off[s] = g ? ((b / 3) * COLS + b % 3) * 8 : ((a / 3) * COLS + a % 3) * 8;
     }
-    if (tap + 1 < kTaps) {
-        const u32x2_t v = *reinterpret_cast<const u32x2_t*>(w + ((size_t)ch * kTaps + tap + 1) * kCin);
-        r.z = v.x; r.w = v.y;
-    }
+}
+
+__device__ inline u32x2_t first_pixels(const unsigned char* px, const int off[kSteps1], int s) {
+    return *reinterpret_cast<const u32x2_t*>(px + off[s]);
+}
+
+__device__ inline u32x4_t tap_operand(const u32x2_t& v) { return u32x4_t{v.x, v.y, 0u, 0u}; }
+
+__device__ inline f32x16_t zero_tile() {
+    f32x16_t r;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) r[e] = 0.f;
     return r;
 }
 
-// Byte offsets, from a pixel's (tap 0) position in the raw patch of `cols` columns, of the two taps that lane half g feeds to
-// K step s.  Taps 9..11 have zero weights and re-read tap 8.
-template <int COLS>
-__device__ inline void first_offsets(int g, int off[6]) {
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        const int t0 = 4 * (q >> 1) + (q & 1), t1 = t0 + 2;
-        const int a = t0 < kTaps ? t0 : kTaps - 1, b = t1 < kTaps ? t1 : kTaps - 1;
-        off[q] = g ? ((b / 3) * COLS + b % 3) * 8 : ((a / 3) * COLS + a % 3) * 8;
-    }
-}
-
-__device__ inline u32x4_t first_pixels(const unsigned char* px, const int off[6], int s) {
-    const u32x2_t lo = *reinterpret_cast<const u32x2_t*>(px + off[2 * s]), hi = *reinterpret_cast<const u32x2_t*>(px + off[2 * s + 1]);
-    return u32x4_t{lo.x, lo.y, hi.x, hi.y};
-}
-
-__device__ inline f32x16_t bias_tile(const float* bias, int g) {   // accumulator element e: channel 8 (e / 4) + 4 g + e % 4
-    f32x16_t r;
+__device__ inline void add_bias(f32x16_t& a, const float* bias, int g) {   // accumulator element e: channel 8 (e / 4) + 4 g + e % 4
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const f32x4_t q = *reinterpret_cast<const f32x4_t*>(bias + 8 * v + 4 * g);
-        r[4 * v] = q.x; r[4 * v + 1] = q.y; r[4 * v + 2] = q.z; r[4 * v + 3] = q.w;
+        a[4 * v] += q.x; a[4 * v + 1] += q.y; a[4 * v + 2] += q.z; a[4 * v + 3] += q.w;
     }
-    return r;
 }
 
 // ReLU'd channels 8 v + 4 g .. + 3 of this lane's pixel, rounded.
@@ -128,24 +133,25 @@ __global__ __launch_bounds__(256) void first_layer_kernel(const uint8_t* __restr
         *reinterpret_cast<u32x2_t*>(raw + i * 8) = raw_pixel(frames + (size_t)img * 3 * HW, HW, oy0 - 1 + py, ox0 - 1 + px, H, W, lut);
     }
     __syncthreads();
-    int off[6];
+    int off[kSteps1];
     first_offsets<F1C + 2>(g, off);
-    u32x4_t px[2][3];
+    u32x2_t px[2][kSteps1];
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int s = 0; s < 3; ++s) px[r][s] = first_pixels(raw + ((2 * wv + r) * (F1C + 2) + col) * 8, off, s);
+        for (int s = 0; s < kSteps1; ++s) px[r][s] = first_pixels(raw + ((2 * wv + r) * (F1C + 2) + col) * 8, off, s);
     for (int c0 = 0; c0 < Cout; c0 += 32) {
         f32x16_t acc[2];
-        acc[0] = acc[1] = bias_tile(bias + c0, g);
+        acc[0] = acc[1] = zero_tile();
 #pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const u32x4_t a = first_weights(w, c0 + col, s, g);
+        for (int s = 0; s < kSteps1; ++s) {
+            const u32x4_t a = tap_operand(first_weights(w, c0 + col, s, g));
 #pragma unroll
-            for (int r = 0; r < 2; ++r) mma(acc[r], a, px[r][s]);
+            for (int r = 0; r < 2; ++r) mma(acc[r], a, tap_operand(px[r][s]));
         }
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
+            add_bias(acc[r], bias + c0, g);
             const int oy = oy0 + 2 * wv + r, ox = ox0 + col;
             store_tile(acc[r], out + (((size_t)img * H + oy) * W + ox) * Cout + c0, g, oy < H && ox < W);
         }
@@ -157,6 +163,7 @@ __global__ __launch_bounds__(256) void first_layer_kernel(const uint8_t* __restr
 // Its 36 weight fragments (144 registers) stay in registers over all tiles of the persistent block.  A fragment of one input
 // row at one column shift serves the output rows above, at and below it, so the contraction reads 6 fragments per 12 products:
 // half of the 128 bytes/cycle of LDS at the full matrix rate, where reading a fragment per product would need all of it.
+// Input rows are walked outermost: an output row then meets its taps in filter order (the order of the general kernel).
 constexpr int PR = 16, PC = 32;                       // output tile
 constexpr int MR = PR + 2, MC = PC + 2;               // first layer's tile with the second's halo
 constexpr int RR = MR + 2, RC = MC + 2;               // raw patch
@@ -172,8 +179,8 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* mid = smem;                                   // [MR * MC][MPITCH]
     unsigned char* raw = mid + MR * MC * MPITCH;                 // [RR * RC][8]
-    unsigned char* wf1 = raw + RR * RC * 8;                      // [2][3][64 lanes][16]
-    float* sb = reinterpret_cast<float*>(wf1 + 2 * 3 * 1024);    // both layers' biases
+    unsigned char* wf1 = raw + RR * RC * 8;                      // [2][kSteps1][64 lanes][8]
+    float* sb = reinterpret_cast<float*>(wf1 + 2 * kSteps1 * 512);   // both layers' biases
     bf16_t* lut = reinterpret_cast<bf16_t*>(sb + 128);
     const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 5, col = lane & 31;
     const int cn = wv & 1, rg = wv >> 1;
@@ -182,11 +189,12 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
     if (t < 256) lut[t] = f32_to_bf16(((float)t - mean) / stdv);
     if (t < 64) sb[t] = b1[t];
     else if (t < 128) sb[t] = b2[t - 64];
-    for (int q = wv; q < 6; q += 8) *reinterpret_cast<u32x4_t*>(wf1 + (q * 64 + lane) * 16) = first_weights(w1, (q / 3) * 32 + col, q % 3, g);
+    for (int q = wv; q < 2 * kSteps1; q += 8)
+        *reinterpret_cast<u32x2_t*>(wf1 + (q * 64 + lane) * 8) = first_weights(w1, (q / kSteps1) * 32 + col, q % kSteps1, g);
     u32x4_t w[36];
 #pragma unroll
     for (int k = 0; k < 36; ++k) w[k] = *reinterpret_cast<const u32x4_t*>(w2 + (size_t)(cn * 32 + col) * (kTaps * kCin) + k * 16 + g * 8);
-    int off[6];
+    int off[kSteps1];
     first_offsets<RC>(g, off);
 
     struct Org { int img, y, x; };
@@ -233,15 +241,15 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
         load_raw(nxt);
         // ---- first layer on the tile and its halo; pixels outside the frame are the second layer's zero padding
         {
-            u32x4_t a[3];
+            u32x4_t a[kSteps1];
 #pragma unroll
-            for (int s = 0; s < 3; ++s) a[s] = *reinterpret_cast<const u32x4_t*>(wf1 + ((cn * 3 + s) * 64 + lane) * 16);
-            const f32x16_t bt = bias_tile(sb + cn * 32, g);
+            for (int s = 0; s < kSteps1; ++s) a[s] = tap_operand(*reinterpret_cast<const u32x2_t*>(wf1 + ((cn * kSteps1 + s) * 64 + lane) * 8));
             for (int mt = rg; mt < MTILES; mt += 4) {
                 const int p = mt * 32 + col, pc = min(p, MR * MC - 1), py = pc / MC, px = pc - py * MC;
-                f32x16_t acc = bt;
+                f32x16_t acc = zero_tile();
 #pragma unroll
-                for (int s = 0; s < 3; ++s) mma(acc, a[s], first_pixels(raw + (py * RC + px) * 8, off, s));
+                for (int s = 0; s < kSteps1; ++s) mma(acc, a[s], tap_operand(first_pixels(raw + (py * RC + px) * 8, off, s)));
+                add_bias(acc, sb + cn * 32, g);
                 const bool in = (unsigned)(cur.y - 1 + py) < (unsigned)H && (unsigned)(cur.x - 1 + px) < (unsigned)W;
                 if (p < MR * MC) {
 #pragma unroll
@@ -253,20 +261,20 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
             }
         }
         __syncthreads();     // `mid` complete
-        // ---- second layer: K in the order (column shift, 16 channels, input row); a ring of four fragments runs three ahead
+        // ---- second layer: steps in the order (input row, column shift, 16 channels); a ring of four fragments runs three ahead
         f32x16_t acc[4];
-        acc[0] = acc[1] = acc[2] = acc[3] = bias_tile(sb + 64 + cn * 32, g);
+        acc[0] = acc[1] = acc[2] = acc[3] = zero_tile();
         const unsigned char* base = mid + (rg * 4 * MC + col) * MPITCH + g * 16;
-        constexpr int STEPS = 3 * 4 * 6, AHEAD = 3;
+        constexpr int STEPS = 6 * 3 * 4, AHEAD = 3;
         u32x4_t f[AHEAD + 1];
         auto fragment = [&](int i) {
-            const int kx = i / 24, ks = (i / 6) % 4, row = i % 6;
+            const int row = i / 12, kx = (i / 4) % 3, ks = i % 4;
             return *reinterpret_cast<const u32x4_t*>(base + (row * MC + kx) * MPITCH + ks * 32);
         };
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) f[i] = fragment(i);
         static_for<0, STEPS>([&](auto ic) {
-            constexpr int i = decltype(ic)::value, kx = i / 24, ks = (i / 6) % 4, row = i % 6;
+            constexpr int i = decltype(ic)::value, row = i / 12, kx = (i / 4) % 3, ks = i % 4;
             if constexpr (i + AHEAD < STEPS) f[(i + AHEAD) % (AHEAD + 1)] = fragment(i + AHEAD);
             static_for<0, 3>([&](auto kc) {
                 constexpr int ky = decltype(kc)::value, r = row - ky;
@@ -275,7 +283,7 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
             __builtin_amdgcn_sched_barrier(0);
         });
         if constexpr (POOL) {
-            // ReLU and rounding are monotonic: the maximum is taken on the sums.  Neighbouring columns are neighbouring lanes;
+            // Adding the bias, ReLU and rounding are monotonic: the maximum is taken on the sums.  Neighbouring columns are neighbouring lanes;
             // the even one of a pair keeps the tile's first 16 channels, the odd one the others.
             const int Ho = H / 2, Wo = W / 2, ox = (cur.x + col) >> 1;
 #pragma unroll
@@ -286,6 +294,7 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
                     const float v = fmaxf(acc[2 * pr][e], acc[2 * pr + 1][e]);
                     m[e] = fmaxf(v, __shfl_xor(v, 1));
                 }
+                add_bias(m, sb + 64 + cn * 32, g);
                 const int oy = (cur.y >> 1) + 2 * rg + pr;
                 const bool ok = oy < Ho && ox < Wo;
                 bf16_t* dst = out + (((size_t)cur.img * Ho + oy) * Wo + ox) * 64 + cn * 32;
@@ -300,6 +309,7 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+                add_bias(acc[r], sb + 64 + cn * 32, g);
                 const int oy = cur.y + rg * 4 + r, ox = cur.x + col;
                 store_tile(acc[r], out + (((size_t)cur.img * H + oy) * W + ox) * 64 + cn * 32, g, oy < H && ox < W);
             }
@@ -308,7 +318,7 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
     }
 }
 
-constexpr size_t kPairLds = (size_t)MR * MC * MPITCH + RR * RC * 8 + 2 * 3 * 1024 + 128 * 4 + 256 * 2;
+constexpr size_t kPairLds = (size_t)MR * MC * MPITCH + RR * RC * 8 + 2 * kSteps1 * 512 + 128 * 4 + 256 * 2;
 
 }  // namespace
 

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import nchw_to_nhwc, relerr, to_dev
+from gpu_common import MINI_BF16, gpu_model, nchw_to_nhwc, relerr, to_dev
 from oracle import classifier as oc
 from thia_synth import ClassifierSpec, VGG16_EXITS, SceneSpec, make_classifier_blob, make_frames, split_classifier_blob
 
@@ -166,6 +166,42 @@ def test_first_layers_at_tile_edges(channels, pools, n, H, W):
         some = [0, n - 1]
         ref = oc.classify(blob, fr[some], ep)["logits"]
         assert relerr(log.cpu().numpy()[some], ref) <= 2.0 ** -7, (ep, relerr(log.cpu().numpy()[some], ref))
+
+
+@pytest.mark.parametrize("channels,pools", [((64, 64, 64), (2,)), ((64, 64, 64), ()), ((64, 64, 64), (1, 2)), ((128, 64, 64), (1,))])
+@pytest.mark.parametrize("n,H,W", [(1, 1, 1), (3, 4, 5), (5, 17, 33), (2, 35, 70)])
+def test_first_layers_are_the_general_layers_bit_for_bit(channels, pools, n, H, W):
+    """Which kernel runs the first layers is not seen in an answer: logits of every exit are those of the convolution kernel
+    on the normalised frames (zero channels up to 64), layer by layer, with biases that are not zero."""
+    spec = ClassifierSpec(precision=1, channels=channels, pool_after=pools, taps=(1, 2, 3), n_classes=7)
+    blob = make_classifier_blob(spec, 73)
+    t = split_classifier_blob(spec, blob)
+    rs = np.random.RandomState(H * W + len(pools))
+    for k in t:
+        if k.endswith(".b"):
+            t[k][...] = 0.3 * rs.randn(*t[k].shape)
+    from paper_2102_08481_amd import thia_classifier_load
+    c = thia_classifier_load(blob, spec.n_exits)
+    m, _ = gpu_model(MINI_BF16, 0xBEEF + 51)
+    fr = rs.randint(0, 256, (n, 3, H, W)).astype(np.uint8)
+    x = np.zeros((n, H, W, 64), np.float32)
+    x[..., :3] = (nchw_to_nhwc(fr).astype(np.float32) - np.float32(spec.mean)) / np.float32(spec.std)
+    x = to_dev(x, torch.bfloat16)
+    for i in (1, 2, 3):
+        if i > 1 and i - 1 in pools:
+            if min(x.shape[1:3]) < 2:
+                break                                   # nothing left behind this pool
+            x = c.op_pool(x)
+        w = t[f"conv{i}.w"]
+        if i == 1:
+            w = np.concatenate([w, np.zeros((w.shape[0], 61, 3, 3), np.float32)], 1)
+        x = m.op_conv(x, w, t[f"conv{i}.b"], pad=1, relu=True)
+        ref = c.op_unit(x.reshape(n, -1, x.shape[-1]), i)
+        got = c.classify_chunk(to_dev(fr), i, want_logits=True)
+        torch.cuda.synchronize()
+        assert torch.equal(got[2], ref[2]), (i, float((got[2] - ref[2]).abs().max()))
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    c.close()
 
 
 def test_first_pair_walks_several_tiles_per_block():
