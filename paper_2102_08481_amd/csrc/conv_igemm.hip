@@ -1062,14 +1062,17 @@ static hipError_t launch_ring_32x64(const ConvArgs& a, hipStream_t s) {
 // cheapest by that count.  Measured in us, two-buffer tile / ring tile: 300 x 1024, K 12544: 128 / 32 (32 x 64);
 // 900: 212 / 47 (64 x 64); 1500: 212 / 67 (64 x 128); 2400: 212 / 98 (128 x 128); 3x3 256 -> 256: 2 040 pixels
 // 24.6 / 10.8, 8 160 26 / 17.5; 3x3 512 -> 512: 510 pixels 45 / 17.4, 4 080 55 / 30, 8 160 60 / 47.  More than 256 tiles
-// of 128 x 128 run two blocks per CU and overlap each other: no ring tile is faster there.  Below K 512 (768 for the
-// 128 x 128 ring) the time is set-up and epilogue and one block per CU hides neither.  Returns false if no ring tile pays.
+// of 128 x 128 run two blocks per CU and overlap each other: no ring tile is faster there.  The count holds for long K; for
+// short K a launch is set-up and epilogue, of which one large block per CU hides nothing.  So 64 x 128 runs from K 512 and in
+// one round only (256 channels: 8 160 pixels K 512 10.2 / 7.9, K 704 12.5 / 9.1; in two rounds, 8 500 pixels, K 512 10.2 / 11.6,
+// K 704 12.7 / 13.6), and 128 x 128 from K 768 (K 768 13.5 / 12.1, K 1024 16.8 / 13.9).  64 x 64 pays from K 256 in up to two rounds
+// (8 160 pixels, 256 channels, K 256 7.0 / 6.4, K 448 9.3 / 7.7).  Returns false if no ring tile pays.
 static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipError_t* e) {
     if (K < 256 || a.out1 != nullptr) return false;
     const bool narrow = a.Cout <= 64;
     if (narrow ? tile_rounds(a, 64, 64) > 1 : tile_rounds(a, 128, 128) > 1) return false;
     const long long c32 = 16 * tile_rounds(a, 32, 64), c64 = 24 * tile_rounds(a, 64, 64);
-    const long long c64w = K >= 512 && !narrow ? 31 * tile_rounds(a, 64, 128) : 1000, c128 = K >= 768 && !narrow ? 49 : 1000;
+    const long long c64w = K >= 512 && !narrow && tile_rounds(a, 64, 128) == 1 ? 31 : 1000, c128 = K >= 768 && !narrow ? 49 : 1000;
     const long long best = c32 < c64 ? c32 : c64, wide = c64w < c128 ? c64w : c128;
     if ((best < wide ? best : wide) >= 64) return false;
     if (best <= wide) *e = c32 < c64 ? launch_ring_32x64(a, s) : launch_one<bf16_t, 64, 64, 128, 2, 2, bf16_t, true, 5, 4>(a, s);
