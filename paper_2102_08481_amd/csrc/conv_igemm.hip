@@ -1080,26 +1080,34 @@ static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipE
     return true;
 }
 
-// fp32: the fp32 matrix instructions bound every tile (1024 cycles per K step of a 64 x 64 tile), so what counts is how many
-// SIMDs share the work.  Per K step and round of 256 blocks: 128 x 128 2.07 us, 128 x 64 1.5, 64 x 64 ring 0.57, 32 x 32
-// ring (16x16 matrix tiles, four wavefronts) 0.33.  Measured in us, 128 x 128 / 64 x 64 / 32 x 32: 200 x 1024, K 12544:
-// 815 / 223 / 130; 600 x 1024: 819 / 226 / 292; 3x3 256 -> 256, 1 024 pixels 162 / 49 / 29, 4 096 163 / 53 / 74,
-// 16 320 168 / 161 / 280.
-static hipError_t launch_fp32(const ConvArgs& a, hipStream_t s) {
+// fp32.  Per K step and round of 256 blocks: 128 x 128 2.1 us and 64 x 64 ring 0.6, both bound by the fp32 matrix instructions
+// (1024 cycles per K step of a 64 x 64 tile), so that what counts is how many SIMDs share the work; 32 x 32 ring (16x16 matrix
+// tiles, four wavefronts) 0.33 in one round and 0.23 to 0.28 in several, about a third of it matrix instructions: the rest is
+// one barrier, the fragment reads and the exchange of lane halves per 32 values of K.  The rule counts 0.28 for it.  Measured
+// in us, 128 x 128 / 64 x 64 / 32 x 32: 200 x 1024, K 12544: 820 / 234 / 130; 600 x 1024: 833 / 250 / 304; 3x3 256 -> 256,
+// 1 020 pixels 164 / 50 / 28, 2 040 165 / 52 / 41, 4 080 168 / 56 / 77, 16 320 186 / 180 / 266; 1x1 64 -> 64, 8 160 pixels 64 x 64
+// 5.9, 32 x 32 5.1, 9 000 pixels 5.9 / 6.8.
+// Up to 64 channels the two-buffer tile is 128 x 64: 1.5 us with one block per CU, 1.06 a round where two share it, so that
+// the ring pays while its last round is not full (64 x 64 ring / 128 x 64: 3x3 64 -> 64, 32 400 pixels 31.2 / 33.8, 66 000 64.6 / 69.9,
+// 64 800 54.8 / 52.6, 259 200 188 / 176), with few K steps in up to two rounds (1x1 64 -> 64: 32 400 pixels 8.7 / 9.4, 33 000
+// 11.3 / 10.8, 259 200 43.0 / 36.2).
+static hipError_t launch_fp32(const ConvArgs& a, long long K, hipStream_t s) {
     const bool narrow = a.Cout <= 64;
-    const long long c32 = 33 * tile_rounds(a, 32, 32), c64 = 57 * tile_rounds(a, 64, 64);
-    const long long base = narrow ? 150 * tile_rounds(a, 128, 64) : 207 * tile_rounds(a, 128, 128);
+    const long long r64 = tile_rounds(a, 64, 64), rw = tile_rounds(a, 128, 64);
+    const long long c32 = 28 * tile_rounds(a, 32, 32), c64 = 57 * r64;
+    const long long base = narrow ? (rw == 1 ? 150 : 106 * rw) : 207 * tile_rounds(a, 128, 128);
     if (c32 < c64 && c32 < base) return launch_one<float, 32, 32, 128, 2, 2, float, true, 8, 4>(a, s);
-    if (c64 < base) return launch_one<float, 64, 64, 128, 2, 2, float, true, 5, 4>(a, s);
+    if (c64 < base && !(narrow && K < 256 && r64 > 2)) return launch_one<float, 64, 64, 128, 2, 2, float, true, 5, 4>(a, s);
     return narrow ? launch_one<float, 128, 64, 128, 2, 2, float>(a, s) : launch_one<float, 128, 128, 128, 2, 2, float, true>(a, s);
 }
 
 // fp32 outputs of bf16 tensors (the predictors, at most a few channel tiles wide): the general epilogue's time goes with the
 // tile.  Measured, 128-pixel tile / ring: 75 channels, K 256: 300 pixels 17.3 / 5.7 us (32 x 64), 16 320 17.5 / 8.2 and
-// 32 640 18.3 / 14.2 (64 x 64); 55 channels, K 1024, 4 800 rows: 15.5 / 7.5.
+// 32 640 18.3 / 14.2 (64 x 64); 55 channels, K 1024, 4 800 rows: 15.5 / 7.5.  Up to 64 channels the 128-pixel tile is no wider
+// than the ring's: 60 channels, K 256, 48 000 pixels 14.5 / 14.2, 64 800 15.7 / 17.5.
 static hipError_t launch_out_f32(const ConvArgs& a, hipStream_t s) {
     if (tile_rounds(a, 32, 64) <= 1) return launch_one<bf16_t, 32, 64, 128, 1, 2, float, false, 6, 4>(a, s);
-    if (tile_rounds(a, 64, 64) <= 4) return launch_one<bf16_t, 64, 64, 128, 2, 2, float, false, 5, 4>(a, s);
+    if (tile_rounds(a, 64, 64) <= (a.Cout <= 64 ? 3 : 4)) return launch_one<bf16_t, 64, 64, 128, 2, 2, float, false, 5, 4>(a, s);
     return a.Cout <= 64 ? launch_one<bf16_t, 128, 64, 128, 2, 2, float>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, float>(a, s);
 }
 
@@ -1114,7 +1122,7 @@ hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream
         return launch_one<bf16_t, 256, 256, 128, 2, 4, bf16_t, true>(a, s);
     }
     const bool narrow = a.Cout <= 64;
-    if (precision == 0) return launch_fp32(a, s);
+    if (precision == 0) return launch_fp32(a, (long long)a.kh * a.kw * a.Cin + (a.in2 ? a.Cin2 : 0), s);
     if (out_f32) return launch_out_f32(a, s);
     // Long-K layers are bound by L2 -> CU bandwidth with a 128 x 128 tile (64 flop per byte staged); a
     // 256 x 256 tile halves that traffic.  It runs with 8 wavefronts (128 x 64 each), so that one block per

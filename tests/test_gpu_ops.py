@@ -110,6 +110,31 @@ def test_conv_result_does_not_depend_on_the_tile(precision, case):
         assert relerr(nhwc_to_nchw(got[1].float().cpu().numpy()), ref) <= tol, (use_res, out_f32)
 
 
+@pytest.mark.parametrize("precision,Cin,Cout,k,out_f32,few,many", [
+    (0, 64, 64, 1, False, 32400, 33000),       # 64 x 64 ring up to two rounds | 128 x 64 with two operand tiles
+    (0, 64, 64, 3, False, 33000, 64800),       # the same with nine taps
+    (0, 128, 75, 1, False, 8160, 9000),        # 64 x 64 ring | 32 x 32 ring (last round of the former nearly empty)
+    (0, 128, 256, 1, False, 2040, 4080),       # 32 x 32 ring | 64 x 64 ring
+    (1, 256, 55, 1, True, 48000, 52000),       # predictors: 64 x 64 ring | 128 x 64
+    (1, 512, 256, 1, False, 8160, 8500),       # 64 x 128 ring in one round | 128 x 128
+    (1, 8192, 1024, 1, False, 300, 8200),      # 32 x 64 ring | 192 x 256
+])
+def test_layers_on_either_side_of_the_tile_rules(precision, Cin, Cout, k, out_f32, few, many):
+    """Pixel counts around the lines between two tiles: the same values bit for bit on both."""
+    m, _ = _model(precision)
+    rs = np.random.RandomState(Cin + Cout)
+    w = (rs.randn(Cout, Cin, k, k) * np.sqrt(2.0 / (Cin * k * k))).astype(np.float32)
+    b = rs.randn(Cout).astype(np.float32) * 0.1
+    W = 1 if k == 1 else 120                   # (3x3: rows of 120 pixels; a band's last row lacks the row below it)
+    g = torch.Generator(device="cuda").manual_seed(Cin)
+    x = torch.randn(1, many // W, W, Cin, generator=g, device="cuda").to(m.elem)
+    a = m.op_conv(x[:, :few // W].contiguous(), w, b, pad=k // 2, out_f32=out_f32)
+    c = m.op_conv(x, w, b, pad=k // 2, out_f32=out_f32)
+    torch.cuda.synchronize()
+    rows = few // W - k // 2
+    assert torch.isfinite(c.float()).all() and torch.equal(a[:, :rows], c[:, :rows])
+
+
 def test_bf16_output_rounding_is_nearest_even_bit_exact():
     """The kernels round fp32 results to bf16 with the hardware conversion; the oracle with integer
     arithmetic.  A convolution with zero weights returns round(bias): ties both ways, values next to
