@@ -8,8 +8,8 @@
 namespace thia {
 
 // ------------------------------------------------------------------ ROIAlign
-// One block per ROI; threads run over channels, so every tap is one contiguous run of Ch
-// elements of the NHWC map.  Convention: texel j has centre j + 0.5; a sample more than one
+// One block per ROI, in calls with few ROIs two or four that share its bins and channels; threads run over channels, so
+// every tap is one contiguous run of Ch elements of the NHWC map.  Convention: texel j has centre j + 0.5; a sample more than one
 // texel outside the map contributes zero; otherwise its coordinates are clamped to the
 // texel-centre range.  Output layout [(ph*P + pw)][c].
 //
@@ -20,7 +20,6 @@ namespace thia {
 // lists are built once per ROI (2 P threads), expanded to one tap table per bin in LDS (texel offset and
 // weight, the 1/4 of the average folded in, entries past the bin's count zero), and every work item runs
 // the smallest unrolled gather that covers its bin's count.
-constexpr int ROI_SPLIT_MAX = 600;   // most ROIs of a call that are split over several blocks
 constexpr int ROI_TAPS = 16;   // most taps per bin (4 rows x 4 columns)
 
 __host__ __device__ inline size_t roialign_lds_bytes(int P) {
@@ -134,10 +133,14 @@ hipError_t launch_roialign(const void* feat, const float* rois, int n, int post,
     if (n <= 0 || post <= 0 || P <= 0 || P > 16 || Ch % 8) return hipErrorInvalidValue;
     const size_t lds = roialign_lds_bytes(P);
     const float scale = 1.0f / (float)stride;
-    // One block per ROI leaves a call with few of them waiting for its ~6 rounds of gathers: up to 600 ROIs are split over
-    // four blocks, which repeat the (short) tap lists (300 ROIs: 15.0 us, 13.0 split; 200 in fp32: 15.7, 9.9; 600 in fp32:
-    // 23.6, 18.9; 1500: 28.3, 39.9).
-    const int parts = (long long)n * post <= ROI_SPLIT_MAX ? 4 : 1;
+    // One block per ROI leaves a call with few of them waiting for its ~6 rounds of gathers (fp32: ~12): few ROIs are split over
+    // two or four blocks, which repeat the (short) tap lists.  Measured in us with 1 / 2 / 4 blocks per ROI, proposals of
+    // 540 x 960 frames at exits 1, 2 and 4: bf16, 300 ROIs 16.0 / 11.9 / 13.4, 15.1 / 11.4 / 11.6 and 12.0 / 10.0 / 12.6; 600
+    // 17.1 / 15.6 / 19.4, 16.3 / 13.6 / 17.0 and 14.2 / 15.3 / 17.9; fp32, 300 ROIs 17.4 / 13.8 / 13.4, 16.7 / 12.4 / 10.6 and
+    // 14.2 / 11.3 / 10.7; 600 26.3 / 22.2 / 25.7, 19.1 / 15.4 / 16.1 and 16.5 / 14.5 / 17.2; four 128 x 128 frames (200, fp32)
+    // 15.7 / 12.0 / 10.4.  Random ROIs, one block / four: 50 bf16 12.3 / 7.7, 200 bf16 14.0 / 10.8; 700 19.3 / 24.9 and fp32 31.4 / 32.9.
+    const long long rois_all = (long long)n * post;
+    const int parts = rois_all <= (precision ? 200 : 300) ? 4 : rois_all <= 600 ? 2 : 1;
     const unsigned blocks = (unsigned)n * (unsigned)post * (unsigned)parts;
     if (precision)
         hipLaunchKernelGGL(roialign_kernel<bf16_t>, dim3(blocks), dim3(256), lds, s, static_cast<const bf16_t*>(feat), rois, post,

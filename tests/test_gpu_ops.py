@@ -459,3 +459,17 @@ def test_roialign_split_over_blocks_is_the_same(precision):
         one = m.op_roialign(feat[f:f + 1].contiguous(), rois[f:f + 1].contiguous(), stride)
         torch.cuda.synchronize()
         assert torch.equal(one[0], many[f])
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_roialign_is_the_same_however_many_blocks_share_a_roi(precision):
+    """100 ROIs per frame: 1 frame (four blocks per ROI), 3 (bf16 two, fp32 four), 6 (two) and 7 (one)."""
+    spec = replace(MINI_BF16 if precision else MINI_FP32, pre_nms=300, post_nms=100)
+    m, _ = gpu_model(spec, 0xBEEF + 78)
+    rs = np.random.RandomState(11)
+    feat = to_dev(rs.randn(7, 19, 27, spec.head_ch).astype(np.float32), m.elem)
+    rois = to_dev(_rand_boxes(rs, 700, 150.0).reshape(7, 100, 4))
+    got = {n: m.op_roialign(feat[:n].contiguous(), rois[:n].contiguous(), 8) for n in (1, 3, 6, 7)}
+    torch.cuda.synchronize()
+    for n in (1, 3, 6):
+        assert torch.equal(got[n], got[7][:n]), n
