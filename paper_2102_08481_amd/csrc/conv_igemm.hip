@@ -14,7 +14,9 @@
 // tiles.  The weights are the MFMA "A" operand (rows = channels) and the activations the
 // "B" operand (columns = pixels): each lane then holds 4 consecutive channels of one
 // pixel per accumulator quad, which is the contiguous direction of the NHWC output.
-// Epilogue: + bias (fp32) [+ residual] [ReLU], then one rounding to the output type.
+// Sums start from the bias (fp32), here as in the single-kernel blocks, the fused predictors and the expansion tail, so a
+// layer's result does not depend on which of them a call's size picks.  Epilogue: [+ residual] [ReLU], then one rounding
+// to the output type.
 #include <type_traits>
 
 #include "thia_internal.h"
@@ -120,7 +122,8 @@ __device__ inline void static_for(F&& f) {
 // 4: any filter size, followed by the expansion tail (ConvArgs::tail_*) on the block's output tile.
 // STAGES 2: double-buffered operand tiles; more: a ring of that many (see RING below).
 template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0>
-__global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_kernel(const ConvArgs a) {
+__global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1) void conv_igemm_kernel(const ConvArgs a) {
+    // (64-byte K rows: streaming layers, which want four blocks per CU, that is 128 registers)
     constexpr bool ONE = MODE == 1 || MODE == 2, DUAL = MODE == 2;
     constexpr int NW = WAVES_M * WAVES_N;       // wavefronts that multiply
     constexpr int NT = PROD ? 64 * PROD : 64 * NW;  // threads that load: all, or PROD wavefronts that do nothing else (ring)
@@ -347,13 +350,42 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
             load_to_lds16(wgt + a_base[p] + (size_t)kt * BK, dA + (size_t)(RPP * p) * LDS_ROW);
     };
 
+    // Sums start from the bias.  Its loads go out behind the first tile's requests and are used behind the wait for that tile.
     f32x16_t acc[TN][TM];
+    f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};                // F16: element e of lane l is channel 4 (l / 16) + e, pixel l % 16
+    f32x4_t bias_q[TN][F16 ? 1 : 4];
+    auto load_bias = [&]() {
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
+        for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
+            for (int v = 0; v < (F16 ? 1 : 4); ++v) {   // element e of lane l: channel 8 (e / 4) + 4 (l / 32) + e % 4
+                const int ch = n0 + wn * WN + (F16 ? 4 * (lane >> 4) : i * 32 + 8 * v + 4 * (lane >> 5));
+                f32x4_t q = {0.f, 0.f, 0.f, 0.f};
+                if (ch + 4 <= a.Cout) {
+                    q = *reinterpret_cast<const f32x4_t*>(a.bias + ch);
+                } else {
+                    if (ch < a.Cout) q.x = a.bias[ch];
+                    if (ch + 1 < a.Cout) q.y = a.bias[ch + 1];
+                    if (ch + 2 < a.Cout) q.z = a.bias[ch + 2];
+                }
+                bias_q[i][v] = q;
+            }
+    };
+    auto start_sums = [&]() {
+        if constexpr (F16) {
+            acc4 = bias_q[0][0];
+        } else {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int j = 0; j < TM; ++j) {
+                        acc[i][j][4 * v] = bias_q[i][v].x; acc[i][j][4 * v + 1] = bias_q[i][v].y;
+                        acc[i][j][4 * v + 2] = bias_q[i][v].z; acc[i][j][4 * v + 3] = bias_q[i][v].w;
+                    }
+        }
+    };
 
     // 8-channel-per-lane epilogue needs Cout, ld0 multiples of 8 and one dense output
     const bool vec = (a.out1 == nullptr) && ((a.Cout & 7) == 0) && ((a.ld0 & 7) == 0);
@@ -480,7 +512,6 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
         }
         struct TileFrags { Frags k[KK]; };
         TileFrags g0, g1;
-        f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};
         auto read_tile = [&](int buf, TileFrags& g) {
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
@@ -533,8 +564,10 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
                 __builtin_amdgcn_s_waitcnt(0xc07f);             // lgkmcnt(0)
             }
         };
+        load_bias();
         in_registers(KT >= STAGES - 1);
         barrier();                                              // tile 0 has landed
+        start_sums();
         if (PROD == 0 && STAGES - 1 < KT) request(STAGES - 1);
         read_tile(0, g0);
         int buf = 0;                                            // buffer of tile kt
@@ -558,7 +591,6 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
         in_registers(false);
         barrier();
         if constexpr (F16) {
-            // accumulator element e of lane l: channel 4 (l / 16) + e, pixel l % 16
             const int pix = m0 + wm * WM + (lane & 15), ch = n0 + wn * WN + 4 * (lane >> 4);
             if (pix >= M) return;
             float* o0 = static_cast<float*>(a.out0);
@@ -568,7 +600,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const bool in_range = ch + e < a.Cout;
-                v[e] = acc4[e] + (in_range ? a.bias[ch + e] : 0.f);
+                v[e] = acc4[e];
                 if (r0 && in_range) v[e] += r0[(size_t)pix * a.Cout + ch + e];
                 if (a.relu) v[e] = fmaxf(v[e], 0.f);
             }
@@ -592,8 +624,10 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
         // has a k-step of matrix work queued, which covers the first fragment reads of the next tile.
         static_assert(KK % 2 == 0, "the fragment double buffer alternates per k-step");
         issue_tiles(0, 0);
+        load_bias();
         __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         __syncthreads();
+        start_sums();
         if (KT > 1) issue_tiles(1, 1);
         Frags f0, f1;
         read_frags(0, 0, f0);
@@ -612,8 +646,10 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
         }
     } else {
     load_tiles(0, st0);
+    load_bias();
     store_tiles(0, st0);
     if (KT > 1) load_tiles(1, st0);
+    start_sums();
     __syncthreads();
     // The requests for tile kt + 2 go out right after the LDS write of tile kt + 1 has freed the staging
     // registers, so the data has a whole step to arrive.  With 8 wavefronts the two that share a SIMD (w and
@@ -657,9 +693,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int ch = wn * WN + i * 32 + 8 * v + 4 * (lane >> 5);
-                        const f32x4_t bv = *reinterpret_cast<const f32x4_t*>(a.bias + n0 + ch);
-                        u32x2_t o = {pack_bf16x2(fmaxf(acc[i][j][4 * v] + bv.x, 0.f), fmaxf(acc[i][j][4 * v + 1] + bv.y, 0.f)),
-                                     pack_bf16x2(fmaxf(acc[i][j][4 * v + 2] + bv.z, 0.f), fmaxf(acc[i][j][4 * v + 3] + bv.w, 0.f))};
+                        u32x2_t o = {pack_bf16x2(fmaxf(acc[i][j][4 * v], 0.f), fmaxf(acc[i][j][4 * v + 1], 0.f)),
+                                     pack_bf16x2(fmaxf(acc[i][j][4 * v + 2], 0.f), fmaxf(acc[i][j][4 * v + 3], 0.f))};
                         *reinterpret_cast<u32x2_t*>(smem + (size_t)(wm * WM + j * 32 + frag_row) * YP + ch * 2) = o;
                     }
             // predictor weight fragments (3 channel tiles per k-step) run HRING k-steps ahead of their use; the first
@@ -738,9 +773,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int ch = wn * WN + i * 32 + 8 * v + 4 * lh;
-                    const f32x4_t bv = *reinterpret_cast<const f32x4_t*>(a.bias + n0 + ch);
-                    u32x2_t o = {pack_bf16x2(fmaxf(acc[i][j][4 * v] + bv.x, 0.f), fmaxf(acc[i][j][4 * v + 1] + bv.y, 0.f)),
-                                 pack_bf16x2(fmaxf(acc[i][j][4 * v + 2] + bv.z, 0.f), fmaxf(acc[i][j][4 * v + 3] + bv.w, 0.f))};
+                    u32x2_t o = {pack_bf16x2(fmaxf(acc[i][j][4 * v], 0.f), fmaxf(acc[i][j][4 * v + 1], 0.f)),
+                                 pack_bf16x2(fmaxf(acc[i][j][4 * v + 2], 0.f), fmaxf(acc[i][j][4 * v + 3], 0.f))};
                     *reinterpret_cast<u32x2_t*>(smem + yoff(wm * WM + j * 32 + frag_row, ch * 2)) = o;
                 }
         __syncthreads();
@@ -840,24 +874,15 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
     OutT* __restrict__ out1 = static_cast<OutT*>(a.out1);
     if (vec) {
         // Coalesced path, one 32-pixel sub-tile at a time: the wavefront parks its 32 pixel x WN channel
-        // fp32 tile (+ bias) in its own LDS region (the pipeline buffers are free now) and re-reads it so
+        // fp32 tile in its own LDS region (the pipeline buffers are free now) and re-reads it so
         // that each lane owns 8 consecutive channels of one pixel: residual loads and output stores are
         // 16-byte and the lanes of one instruction cover whole lines of the NHWC tensors.
         unsigned char* ep = smem + (size_t)wv * (32 * EPITCH);
         if constexpr (std::is_same<OutT, bf16_t>::value && std::is_same<T, bf16_t>::value) {
-            // No residual: bias, ReLU and the rounding to bf16 are applied in accumulator layout, and the tile goes through
+            // No residual: ReLU and the rounding to bf16 are applied in accumulator layout, and the tile goes through
             // LDS already rounded - half the LDS traffic, one 16-byte read per store (same values as the fp32 round trip).
             if (res == nullptr) {
                 constexpr int EPB = WN * 2 + 16;   // bf16 row pitch
-                f32x4_t bv[TN][4];
-#pragma unroll
-                for (int i = 0; i < TN; ++i)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int ch = n0 + wn * WN + i * 32 + 8 * v + 4 * (lane >> 5);
-                        bv[i][v] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                        if (ch < a.Cout) bv[i][v] = *reinterpret_cast<const f32x4_t*>(a.bias + ch);
-                    }
                 const bool relu = a.relu != 0;
                 static_for<0, TM>([&](auto jc) {
                     constexpr int j = decltype(jc)::value;
@@ -865,8 +890,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
                     for (int i = 0; i < TN; ++i)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            float r0 = acc[i][j][4 * v] + bv[i][v].x, r1 = acc[i][j][4 * v + 1] + bv[i][v].y;
-                            float r2 = acc[i][j][4 * v + 2] + bv[i][v].z, r3 = acc[i][j][4 * v + 3] + bv[i][v].w;
+                            float r0 = acc[i][j][4 * v], r1 = acc[i][j][4 * v + 1], r2 = acc[i][j][4 * v + 2], r3 = acc[i][j][4 * v + 3];
                             if (relu) { r0 = fmaxf(r0, 0.f); r1 = fmaxf(r1, 0.f); r2 = fmaxf(r2, 0.f); r3 = fmaxf(r3, 0.f); }
                             const u32x2_t o = {pack_bf16x2(r0, r1), pack_bf16x2(r2, r3)};
                             *reinterpret_cast<u32x2_t*>(ep + (size_t)frag_row * EPB + (i * 32 + 8 * v + 4 * (lane >> 5)) * 2) = o;
@@ -905,11 +929,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int chl = i * 32 + 8 * v + 4 * (lane >> 5);
-                    const int ch = n0 + wn * WN + chl;
-                    f32x4_t bv = {0.f, 0.f, 0.f, 0.f};
-                    if (ch < a.Cout) bv = *reinterpret_cast<const f32x4_t*>(a.bias + ch);
-                    f32x4_t r = {acc[i][j][4 * v] + bv.x, acc[i][j][4 * v + 1] + bv.y, acc[i][j][4 * v + 2] + bv.z,
-                                 acc[i][j][4 * v + 3] + bv.w};
+                    f32x4_t r = {acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]};
                     *reinterpret_cast<f32x4_t*>(ep + (size_t)frag_row * EPITCH + chl * 4) = r;
                 }
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the region is private to this wavefront
@@ -961,7 +981,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD)) void conv_igemm_ke
                 const int pxl = e / WN, cl = e - pxl * WN;
                 const int pix = m0 + wm * WM + j * 32 + pxl, c = n0 + wn * WN + cl;
                 if (pix >= M || c >= a.Cout) continue;
-                float val = *reinterpret_cast<const float*>(ep + (size_t)pxl * EPITCH + cl * 4) + a.bias[c];
+                float val = *reinterpret_cast<const float*>(ep + (size_t)pxl * EPITCH + cl * 4);
                 if (res) val += load_elem(res + (size_t)pix * a.Cout + c);
                 if (a.relu) val = fmaxf(val, 0.f);
                 if (c < a.n_split) store_elem(out0 + (size_t)pix * a.ld0 + c, val);

@@ -5,7 +5,7 @@
 // zeros behind each pixel, the tenth tap's weights zero): five 32x32x16 products per tile, one 8-byte LDS read per lane each.
 //
 // Both layers give the values of the general kernel bit for bit, so an answer does not depend on which of them ran: taps in
-// filter order, a tap's channels 16 at a time, each sum on its own.  The matrix instruction adds the 8 products of lanes 0..31
+// filter order, a tap's channels 16 at a time, each sum on its own, from the bias on.  The matrix instruction adds the 8 products of lanes 0..31
 // first and then those of lanes 32..63, each 8 as one sum: two taps in the two halves round like a product per tap, two taps
 // within a half (three products per tile instead of five) do not.
 //
@@ -70,19 +70,14 @@ __device__ inline u32x2_t first_pixels(const unsigned char* px, const int off[kS
 
 __device__ inline u32x4_t tap_operand(const u32x2_t& v) { return u32x4_t{v.x, v.y, 0u, 0u}; }
 
-__device__ inline f32x16_t zero_tile() {
+__device__ inline f32x16_t bias_tile(const float* bias, int g) {   // accumulator element e: channel 8 (e / 4) + 4 g + e % 4
     f32x16_t r;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) r[e] = 0.f;
-    return r;
-}
-
-__device__ inline void add_bias(f32x16_t& a, const float* bias, int g) {   // accumulator element e: channel 8 (e / 4) + 4 g + e % 4
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const f32x4_t q = *reinterpret_cast<const f32x4_t*>(bias + 8 * v + 4 * g);
-        a[4 * v] += q.x; a[4 * v + 1] += q.y; a[4 * v + 2] += q.z; a[4 * v + 3] += q.w;
+        r[4 * v] = q.x; r[4 * v + 1] = q.y; r[4 * v + 2] = q.z; r[4 * v + 3] = q.w;
     }
+    return r;
 }
 
 // ReLU'd channels 8 v + 4 g .. + 3 of this lane's pixel, rounded.
@@ -142,7 +137,7 @@ __global__ __launch_bounds__(256) void first_layer_kernel(const uint8_t* __restr
         for (int s = 0; s < kSteps1; ++s) px[r][s] = first_pixels(raw + ((2 * wv + r) * (F1C + 2) + col) * 8, off, s);
     for (int c0 = 0; c0 < Cout; c0 += 32) {
         f32x16_t acc[2];
-        acc[0] = acc[1] = zero_tile();
+        acc[0] = acc[1] = bias_tile(bias + c0, g);
 #pragma unroll
         for (int s = 0; s < kSteps1; ++s) {
             const u32x4_t a = tap_operand(first_weights(w, c0 + col, s, g));
@@ -151,7 +146,6 @@ __global__ __launch_bounds__(256) void first_layer_kernel(const uint8_t* __restr
         }
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            add_bias(acc[r], bias + c0, g);
             const int oy = oy0 + 2 * wv + r, ox = ox0 + col;
             store_tile(acc[r], out + (((size_t)img * H + oy) * W + ox) * Cout + c0, g, oy < H && ox < W);
         }
@@ -244,12 +238,12 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
             u32x4_t a[kSteps1];
 #pragma unroll
             for (int s = 0; s < kSteps1; ++s) a[s] = tap_operand(*reinterpret_cast<const u32x2_t*>(wf1 + ((cn * kSteps1 + s) * 64 + lane) * 8));
+            const f32x16_t bt = bias_tile(sb + cn * 32, g);
             for (int mt = rg; mt < MTILES; mt += 4) {
                 const int p = mt * 32 + col, pc = min(p, MR * MC - 1), py = pc / MC, px = pc - py * MC;
-                f32x16_t acc = zero_tile();
+                f32x16_t acc = bt;
 #pragma unroll
                 for (int s = 0; s < kSteps1; ++s) mma(acc, a[s], tap_operand(first_pixels(raw + (py * RC + px) * 8, off, s)));
-                add_bias(acc, sb + cn * 32, g);
                 const bool in = (unsigned)(cur.y - 1 + py) < (unsigned)H && (unsigned)(cur.x - 1 + px) < (unsigned)W;
                 if (p < MR * MC) {
 #pragma unroll
@@ -263,7 +257,7 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
         __syncthreads();     // `mid` complete
         // ---- second layer: steps in the order (input row, column shift, 16 channels); a ring of four fragments runs three ahead
         f32x16_t acc[4];
-        acc[0] = acc[1] = acc[2] = acc[3] = zero_tile();
+        acc[0] = acc[1] = acc[2] = acc[3] = bias_tile(sb + 64 + cn * 32, g);
         const unsigned char* base = mid + (rg * 4 * MC + col) * MPITCH + g * 16;
         constexpr int STEPS = 6 * 3 * 4, AHEAD = 3;
         u32x4_t f[AHEAD + 1];
@@ -283,7 +277,7 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
             __builtin_amdgcn_sched_barrier(0);
         });
         if constexpr (POOL) {
-            // Adding the bias, ReLU and rounding are monotonic: the maximum is taken on the sums.  Neighbouring columns are neighbouring lanes;
+            // ReLU and rounding are monotonic: the maximum is taken on the sums.  Neighbouring columns are neighbouring lanes;
             // the even one of a pair keeps the tile's first 16 channels, the odd one the others.
             const int Ho = H / 2, Wo = W / 2, ox = (cur.x + col) >> 1;
 #pragma unroll
@@ -294,7 +288,6 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
                     const float v = fmaxf(acc[2 * pr][e], acc[2 * pr + 1][e]);
                     m[e] = fmaxf(v, __shfl_xor(v, 1));
                 }
-                add_bias(m, sb + 64 + cn * 32, g);
                 const int oy = (cur.y >> 1) + 2 * rg + pr;
                 const bool ok = oy < Ho && ox < Wo;
                 bf16_t* dst = out + (((size_t)cur.img * Ho + oy) * Wo + ox) * 64 + cn * 32;
@@ -309,7 +302,6 @@ __global__ __launch_bounds__(512, 2) void first_pair_kernel(const uint8_t* __res
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                add_bias(acc[r], sb + 64 + cn * 32, g);
                 const int oy = cur.y + rg * 4 + r, ox = cur.x + col;
                 store_tile(acc[r], out + (((size_t)cur.img * H + oy) * W + ox) * 64 + cn * 32, g, oy < H && ox < W);
             }

@@ -57,7 +57,8 @@ __host__ __device__ inline float bf16_to_f32(bf16_t h) {
 
 // ---------------------------------------------------------------- convolution (implicit GEMM)
 // NHWC activations; weights [Cout][kh][kw][Cin] (K contiguous per output channel).
-// out[m, n] = act(bias[n] + sum_k W[n, k] * im2col(in)[m, k] + res[m, n]),  m = (img, oy, ox).
+// out[m, n] = act(bias[n] + sum_k W[n, k] * im2col(in)[m, k] + res[m, n]),  m = (img, oy, ox); every kernel that runs a layer
+// adds in this order, k ascending.
 // Output columns n < n_split go to out0 (row stride ld0), the others to out1 (row stride ld1).
 struct ConvArgs {
     const void* in;

@@ -23,6 +23,23 @@ def gpu_model(spec, seed):
     return _models[key]
 
 
+def biased_model(spec, seed):
+    """(Model on cuda:0, blob) with biases that are not zero, as folded batch norms and trained heads have them, cached."""
+    from paper_2102_08481_amd import thia_load_model
+    from thia_synth import split_blob
+    from thia_synth.weights import tensor_list
+    key = (spec.header(), seed, "biased")
+    if key not in _models:
+        blob = get_blob(spec, seed).copy()
+        rs = np.random.RandomState(seed & 0xFFFF)
+        tensors, roles = split_blob(spec, blob), {name: role for name, _, role in tensor_list(spec)}
+        for name, t in tensors.items():
+            if name.endswith(".b"):
+                t[...] = {"pred": 0.05, "pred_delta": 0.01}.get(roles[name[:-2] + ".w"], 0.1) * rs.randn(*t.shape)
+        _models[key] = (thia_load_model(blob, spec.n_exits), blob)
+    return _models[key]
+
+
 def relerr(a, b):
     """max |a - b| / max |b| (per tensor, normalised by the reference's max-abs)."""
     a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)

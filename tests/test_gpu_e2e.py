@@ -8,7 +8,7 @@ import torch
 
 import oracle
 from conftest import get_blob
-from gpu_common import MINI_BF16, MINI_FP32, chain_check, gpu_model, match_fraction, nhwc_to_nchw, relerr, to_dev
+from gpu_common import MINI_BF16, MINI_FP32, biased_model, chain_check, gpu_model, match_fraction, nhwc_to_nchw, relerr, to_dev
 from thia_synth import CONFIGS, ModelSpec, SceneSpec, make_frames
 from paper_2102_08481_amd import ThiaError as ThiaErr
 
@@ -415,22 +415,83 @@ def test_argument_errors_return_codes():
     assert (l == -1).all() and (s == 0).all()
 
 
-@pytest.mark.parametrize("n", [1, 2])
-def test_128_wide_blocks_on_either_side_of_the_tile_rule(n):
-    """One frame has 64 tiles in the 128-wide stage (layer by layer), two have 128 (single kernel): both as with the single
-    kernel forced on and with every layer on its own, to one bf16 ulp of the exit tensor's max."""
-    spec = ModelSpec(precision=1, blocks=(1, 3, 1, 1), fc_dim=128, pre_nms=300, post_nms=100, n_classes=5)
-    m, _ = gpu_model(spec, 0xBEEF + 57)
-    frames = to_dev(make_frames(SceneSpec(512, 1024, n, 4, 10, 10, 90), 47))
-    feats = []
+BIASED = ModelSpec(precision=1, blocks=(2, 3, 2, 1), fc_dim=128, pre_nms=300, post_nms=100, n_classes=5)
+
+
+def _same(a, b, what):
+    for x, y, name in zip(a, b, ("boxes", "scores", "labels")):
+        assert torch.equal(x, y), (what, name, float((x.float() - y.float()).abs().max()))
+
+
+@pytest.mark.parametrize("ep", [2, 3])
+def test_128_wide_blocks_on_either_side_of_the_tile_rule(ep):
+    """One frame has 64 tiles in the 128-wide stage (layer by layer), two have 128 (single kernel).  With biases that are not
+    zero, two frames together, each alone, the single kernels forced on and every layer on its own give the same tensors and
+    detections bit for bit."""
+    m, _ = biased_model(BIASED, 0xBEEF + 57)
+    frames = to_dev(make_frames(SceneSpec(512, 1024, 2, 4, 10, 10, 90), 47))
     m.set_debug(True)
-    for mode in (1, 2, 0):
+
+    def run(fr, mode):
         m.set_fusion(mode)
-        m.detect_chunk(frames, 2)
+        out = m.detect_chunk(fr, ep)
         torch.cuda.synchronize()
-        feats.append(m.tap("feat").astype(np.float32))
-    m.set_fusion(1)
-    m.set_debug(False)
-    assert np.isfinite(feats[0]).all()
-    for other in feats[1:]:
-        assert relerr(feats[0], other) <= 2.0 ** -7
+        return m.tap("feat").reshape(len(fr), -1), out
+
+    try:
+        both, dets = run(frames, 1)
+        assert np.isfinite(both).all() and np.abs(both).max() > 0
+        for mode in (2, 0):
+            other, out = run(frames, mode)
+            assert np.array_equal(both, other), (mode, int((both != other).sum()))
+            _same(dets, out, mode)
+        for f in (0, 1):
+            for mode in (1, 2):
+                alone, out = run(frames[f:f + 1], mode)
+                assert np.array_equal(both[f], alone[0]), (f, mode, int((both[f] != alone[0]).sum()))
+                _same([d[f:f + 1] for d in dets], out, (f, mode))
+    finally:
+        m.set_fusion(1)
+        m.set_debug(False)
+
+
+@pytest.mark.parametrize("ep", [1, 2, 3, 4])
+def test_results_do_not_depend_on_the_microbatch(ep):
+    """26 frames of 512 x 1024 in one micro-batch take the kernels of large calls (expansion tail from 25 frames on, predictors
+    in the RPN 3x3's kernel at exit 1 from two on, 128-wide single-kernel blocks from two on); frame by frame they take those
+    of small ones.  Biases are not zero: each of these places adds them in the same order, so all results are the same."""
+    m, _ = biased_model(BIASED, 0xBEEF + 57)
+    frames = to_dev(make_frames(SceneSpec(512, 1024, 26, 4, 10, 10, 90), 48))
+    try:
+        m.set_microbatch(26)
+        whole = m.detect_chunk(frames, ep)
+        torch.cuda.synchronize()
+        assert int((whole[2] >= 0).sum()) > 0
+        for mb in (1, 3):
+            m.set_microbatch(mb)
+            out = m.detect_chunk(frames, ep)
+            torch.cuda.synchronize()
+            _same(whole, out, mb)
+    finally:
+        m.set_microbatch(0)
+
+
+def test_plans_and_all_exits_equal_calls_with_biases():
+    """Chunks of one frame that share a micro-batch in a plan, and every exit of one backbone pass (where exit 1's lateral is a
+    launch of its own and not its stage's last block), against stand-alone calls: same bits, biases not zero."""
+    m, _ = biased_model(BIASED, 0xBEEF + 57)
+    frames = to_dev(make_frames(SceneSpec(512, 1024, 6, 4, 10, 10, 90), 49))
+    plan = [2, 1, 2, 3, 1, 2]
+    got = m.run_plan(frames, 1, plan)
+    torch.cuda.synchronize()
+    for c, ep in enumerate(plan):
+        one = m.detect_chunk(frames[c:c + 1], ep)
+        torch.cuda.synchronize()
+        _same([g[c:c + 1] for g in got], one, (c, ep))
+    for n in (1, 3):
+        every = m.detect_all_exits(frames[:n])
+        torch.cuda.synchronize()
+        for ep in (1, 2, 3, 4):
+            one = m.detect_chunk(frames[:n], ep)
+            torch.cuda.synchronize()
+            _same([e[ep - 1] for e in every], one, (n, ep))
