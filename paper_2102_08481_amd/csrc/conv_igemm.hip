@@ -140,7 +140,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     constexpr bool DIRECT = BKB == 128;
     constexpr int LDS_ROW = DIRECT ? BKB : BKB + 16;   // staged path: padded row pitch (an odd multiple of 16 bytes)
     constexpr bool RING = STAGES > 2;
-    static_assert(RING || PROD == 0, "loading wavefronts exist with the ring only");
+    static_assert(RING == (PROD > 0), "the ring is filled by loading wavefronts, the other paths have none");
     static_assert(!RING || DIRECT, "the ring holds direct-to-LDS tiles");
     constexpr int KK = BKB / 32;               // MFMA k-steps per tile row (32 bytes = 2 lane halves x 16 bytes)
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wavefront tile (pixels x channels)
@@ -495,8 +495,6 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
 #pragma unroll
             for (int s = 0; s < STAGES - 1; ++s)
                 if (s < KT) request(s);
-        }
-        if (PROD && loads) {
             landed(KT >= STAGES - 1);
             barrier();
             if (STAGES - 1 < KT) request(STAGES - 1);
@@ -556,28 +554,22 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
                 }
             }
         };
-        auto in_registers = [&](bool steady) {                  // the fragments read last are in registers
-            if constexpr (PROD == 0) {
-                landed(steady);
-            } else {
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_waitcnt(0xc07f);             // lgkmcnt(0)
-            }
+        auto in_registers = [&]() {                             // the fragments read last are in registers
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xc07f);                 // lgkmcnt(0)
         };
         load_bias();
-        in_registers(KT >= STAGES - 1);
+        in_registers();
         barrier();                                              // tile 0 has landed
         start_sums();
-        if (PROD == 0 && STAGES - 1 < KT) request(STAGES - 1);
         read_tile(0, g0);
         int buf = 0;                                            // buffer of tile kt
         auto step = [&](int kt, const TileFrags& now, TileFrags& next) {
             // (waited for on both sides of the branch: where only one side does, the compiler puts a wait for everything in
             // front of the products and the next tile's reads are no longer behind them)
-            in_registers(kt + STAGES - 1 < KT);
+            in_registers();
             if (kt + 1 < KT) {
                 barrier();
-                if (PROD == 0 && kt + STAGES < KT) request(buf);
                 buf = buf + 1 == STAGES ? 0 : buf + 1;
                 read_tile(buf, next);
             }
@@ -588,7 +580,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             if (kt + 1 < KT) step(kt + 1, g1, g0);
         }
         // (a wavefront's epilogue region lies in other wavefronts' operand tiles)
-        in_registers(false);
+        in_registers();
         barrier();
         if constexpr (F16) {
             const int pix = m0 + wm * WM + (lane & 15), ch = n0 + wn * WN + 4 * (lane >> 4);
