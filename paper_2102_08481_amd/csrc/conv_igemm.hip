@@ -6,12 +6,11 @@
 // n = output channel and k = (ky, kx, ci); activations are NHWC so a K tile of one
 // filter tap is a contiguous run of input channels of one input pixel.
 //
-// Tiling: a 256-thread block (4 wavefronts of 64) owns 128 pixels x BN channels and
-// walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Global loads are 16 bytes
-// per lane, staged in registers and written to a double-buffered LDS tile whose rows
-// are padded to 144 bytes so that the 16-byte fragment reads of 32 consecutive rows
-// fall in distinct banks.  Each wavefront owns 64 pixels x BN/2 channels as 32x32 MFMA
-// tiles.  The weights are the MFMA "A" operand (rows = channels) and the activations the
+// Tiling: a block owns BM pixels x BN channels (32 x 32 to 256 x 256, chosen by the layer's size in launch_conv) and
+// walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Operand tiles go from global memory straight into LDS, two
+// buffers requested by the multiplying wavefronts or, in calls with few pixels, a ring of 3 to 8 filled by wavefronts of
+// its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
+// the tile as 32x32 MFMA tiles.  The weights are the MFMA "A" operand (rows = channels) and the activations the
 // "B" operand (columns = pixels): each lane then holds 4 consecutive channels of one
 // pixel per accumulator quad, which is the contiguous direction of the NHWC output.
 // Sums start from the bias (fp32), here as in the single-kernel blocks, the fused predictors and the expansion tail, so a
@@ -1078,7 +1077,8 @@ static hipError_t launch_ring_32x64(const ConvArgs& a, hipStream_t s) {
 // short K a launch is set-up and epilogue, of which one large block per CU hides nothing.  So 64 x 128 runs from K 512 and in
 // one round only (256 channels: 8 160 pixels K 512 10.2 / 7.9, K 704 12.5 / 9.1; in two rounds, 8 500 pixels, K 512 10.2 / 11.6,
 // K 704 12.7 / 13.6), and 128 x 128 from K 768 (K 768 13.5 / 12.1, K 1024 16.8 / 13.9).  64 x 64 pays from K 256 in up to two rounds
-// (8 160 pixels, 256 channels, K 256 7.0 / 6.4, K 448 9.3 / 7.7).  Returns false if no ring tile pays.
+// (8 160 pixels, 256 channels, K 256 7.0 / 6.4, K 448 9.3 / 7.7).  Below K 256 the detectors have K 64 and 128 only, the streaming
+// tile's; at K 192 the small tiles would pay too (2 040 pixels, 256 channels 5.4 / 4.0).  Returns false if no ring tile pays.
 static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipError_t* e) {
     if (K < 256 || a.out1 != nullptr) return false;
     const bool narrow = a.Cout <= 64;

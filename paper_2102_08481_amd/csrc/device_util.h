@@ -1,5 +1,5 @@
 // Device helpers shared by the proposal and ROI kernels: order-preserving score keys,
-// a block-wide bitonic sort, box decoding and the NMS overlap test.  All geometry is
+// a block-wide sort, greedy suppression among 64 rows, box decoding and the NMS overlap test.  All geometry is
 // plain fp32 with singly rounded operations (the library is built with
 // -ffp-contract=off), so that orderings and keep decisions are reproducible.
 #pragma once

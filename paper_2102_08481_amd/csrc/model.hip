@@ -566,7 +566,8 @@ Tail stage_tail(const thia_model* m, int s, int ep_here) {
 
 // Tiles of 8 x 16 pixels up to which a 128-wide block runs layer by layer: the single kernel's chain of three layers takes as
 // long for one tile as for one on every CU, the layers spread few pixels over small tiles.  Measured, single kernel / layers: 72
-// tiles (one 540 x 960 frame) 28.1 / 24.1 us, 144 tiles 30.1 / 32.0.
+// tiles (one 540 x 960 frame) 28.1 / 24.1 us, 144 tiles 30.1 / 32.0; exit-2 calls with three such blocks: 24 tiles 265 / 238 us, 64
+// 283 / 263, 96 305 / 299, 112 310 / 310, 128 322 / 323, 144 361 / 388.  Both add in the same order: same values bit for bit.
 constexpr long long kFewTiles128 = 96;
 
 // Bottleneck stage s (0-based) applied to t.x; the stage's output becomes t.x.  `tail` (optional) is handed to the
