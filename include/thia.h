@@ -96,8 +96,8 @@ int thia_set_microbatch(thia_model* m, int frames);
 
 /* Bottleneck blocks and layer pairs that have a fused kernel variant run through it (on = 1,
  * the default, where the variant pays; on = 2: wherever it applies, also at sizes too small
- * for it to pay) or layer by layer (on = 0).  All give the same tensors up to the
- * accumulation order; the switch exists for measurements and tests. */
+ * for it to pay) or layer by layer (on = 0).  All add in the same order and give the same
+ * tensors; the switch exists for measurements and tests. */
 int thia_set_fusion(thia_model* m, int on);
 
 /* Micro-batches of one call are independent of each other (Sec. 3: chunks are processed one by one, frames
