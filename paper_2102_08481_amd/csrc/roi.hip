@@ -287,141 +287,235 @@ __global__ __launch_bounds__(1024) void select_kernel(const float* __restrict__ 
     if (t == 0 && out_n) out_n[f] = nk;
 }
 
-// Same selection with one block per frame and foreground class, then one block per frame that merges (post <= 1024,
-// (Kc - 1) * min(D, post) <= 8192).  Same-class NMS never looks across classes and the global walk stops after D kept boxes,
-// so the result equals: per class, greedy NMS over that class's candidates in key order, cut after its first D kept; then
-// the D largest keys among all kept.  The class block sorts its candidates in LDS and resolves them 64 at a time: its
+// Same selection with blocks that take the foreground classes of a frame one by one, then one block per frame that merges
+// (post <= 1024, (Kc - 1) * min(D, post) <= 8192).  Same-class NMS never looks across classes and the global walk stops after
+// D kept boxes, so the result equals: per class, greedy NMS over that class's candidates in key order, cut after its first D
+// kept; then the D largest keys among all kept.  A class's candidates are sorted in LDS and resolved 64 at a time: the
 // wavefronts share the tests against the kept boxes and the group's overlap words, one wavefront decides.  What bounds it is
 // the chain of groups (one block for all classes of a frame: 72 us for 32 frames of 300 ROIs x 7 classes, 15 + 7 now; the
-// single chain over all classes in select_kernel: 346 us for 8 frames of 1000 ROIs x 19 classes, 21 + 17 now).
+// single chain over all classes in select_kernel: 346 us for 8 frames of 1000 ROIs x 19 classes, 10 to 18 + 6 to 8 now).
 constexpr int SELC_MAX_POST = 1024, SELC_MAX_KEPT = 8192, SELC_THREADS = 512;
+constexpr int SELC_FEW = 8;             // most classes merged by binary search
+constexpr int SELC_RESIDENT = 768, SELC_MAX_GROUP = 4;   // blocks the chip holds (LDS: three per CU); most classes per block
 
-// gkeys [n][key_cap]: class c's kept keys at c * Dc (sorted descending), the classes' counts behind all of them.
+// gkeys [n][key_cap]: class c's kept keys at c * Dc (sorted descending), the classes' counts behind all of them.  GROUPED: a
+// block takes up to four classes where a call has more than 32 of them and more than the chip holds blocks; it first looks
+// which of its classes have a score above the threshold (their scores lie side by side).  Of many classes most are usually
+// empty, and a block for each of them costs 2 to 3 us a round: 32 frames, 90 classes without a candidate 12 -> 3 us, with
+// 300 candidates each 23 -> 24.  (With few candidates select_kernel's one block per frame is as fast, 3 to 14 us; with many it
+// takes 25 to 360.)
+template <bool GROUPED>
 __global__ __launch_bounds__(SELC_THREADS) void select_class_kernel(const float* __restrict__ scores, const float* __restrict__ boxes,
-                                                                    const int32_t* __restrict__ roi_n, int post, int Kc, float score_thr,
-                                                                    float nms_thr, int Dc, uint64_t* __restrict__ gkeys, int key_cap) {
+                                                                    const int32_t* __restrict__ roi_n, int post, int Kc, int group,
+                                                                    float score_thr, float nms_thr, int Dc, uint64_t* __restrict__ gkeys,
+                                                                    int key_cap) {
     __shared__ uint64_t lkeys[2 * SELC_MAX_POST];
     __shared__ float4 sbox[SELC_MAX_POST];                               // boxes in key order
     __shared__ float4 kbox[SELC_MAX_POST];                               // kept boxes
-    __shared__ uint64_t early[64];                                       // group: earlier candidates that overlap
-    __shared__ unsigned long long s_dead;                                // group: suppressed by kept boxes
+    __shared__ uint64_t early[64];                                       // group of 64: earlier candidates that overlap
+    __shared__ unsigned long long s_dead;                                // group of 64: suppressed by kept boxes
+    __shared__ uint32_t s_some;                                          // classes with a score above the threshold
     __shared__ int s_count, s_nk;
     constexpr int NWV = SELC_THREADS / 64, JW = 64 / NWV;                // a wavefront's share of a group's overlap words
-    const int c = blockIdx.x, f = blockIdx.y, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int NC = Kc - 1, c0 = blockIdx.x * group, f = blockIdx.y, t = threadIdx.x, lane = t & 63, wv = t >> 6;
     int nr = roi_n[f];
     nr = nr < post ? nr : post;
     const float* sc = scores + (size_t)f * post * Kc;
     const float* bx = boxes + (size_t)f * post * Kc * 4;
-    uint64_t* out = gkeys + (size_t)f * key_cap + (size_t)c * Dc;
-    if (t == 0) { s_count = 0; s_nk = 0; s_dead = 0ull; }
-    __syncthreads();
-    for (int r0 = 0; r0 < nr; r0 += SELC_THREADS) {
-        const int roi = r0 + t;
-        uint64_t key = 0ull;
-        if (roi < nr) {
-            const int j = roi * Kc + c + 1;
-            const float s = sc[j];
-            const float4 b = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
-            if (s > score_thr && (b.z - b.x >= 1e-3f) && (b.w - b.y >= 1e-3f)) key = ((uint64_t)score_key(s) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
-        }
-        const uint64_t has = __ballot(key != 0ull);
-        int base = 0;
-        if (lane == 0 && has != 0ull) base = atomicAdd(&s_count, (int)__popcll(has));
-        base = __shfl(base, 0);
-        if (key != 0ull) lkeys[base + __popcll(has & ((1ull << lane) - 1ull))] = key;
-    }
-    __syncthreads();
-    const int nc = s_count;
-    int n2 = 64;
-    while (n2 < nc) n2 <<= 1;
-    for (int i = nc + t; i < n2; i += SELC_THREADS) lkeys[i] = 0ull;
-    const uint64_t* keys = block_sort_desc(lkeys, lkeys + SELC_MAX_POST, n2);
-    for (int i = t; i < nc; i += SELC_THREADS) {
-        const uint32_t j = 0xFFFFFFFFu - (uint32_t)(keys[i] & 0xFFFFFFFFull);
-        sbox[i] = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
-    }
-    __syncthreads();
+    int32_t* counts = reinterpret_cast<int32_t*>(gkeys + (size_t)f * key_cap + (size_t)NC * Dc);
     auto as_box = [](const float4& v) { return Box{v.x, v.y, v.z, v.w}; };
-    int nk = 0;
-    for (int s0 = 0; s0 < nc && nk < Dc; s0 += 64) {
-        const int i = s0 + lane;
-        const bool valid = i < nc;
-        const Box me = valid ? as_box(sbox[i]) : Box{0.f, 0.f, 0.f, 0.f};
-        // every wavefront: its share of the kept boxes against the group's 64, one candidate per lane
-        bool hit = false;
-        for (int q = wv; q < nk; q += NWV) hit = iou_over(as_box(kbox[q]), me, nms_thr) || hit;
-        const uint64_t dead = __ballot(hit);
-        if (lane == 0 && dead != 0ull) atomicOr(&s_dead, (unsigned long long)dead);
-        // and JW earlier candidates of the group against every later one
-        uint32_t bits = 0u;
-#pragma unroll
-        for (int u = 0; u < JW; ++u) {
-            const int j = wv * JW + u;
-            if (j < lane && valid && iou_over(as_box(sbox[s0 + j]), me, nms_thr)) bits |= 1u << u;
-        }
-        static_assert(JW == 8, "one byte of a row's word per wavefront");
-        reinterpret_cast<unsigned char*>(early)[lane * 8 + wv] = (unsigned char)bits;
+    uint32_t todo = 1u;                                                  // (uniform)
+    if constexpr (GROUPED) {
+        if (t == 0) s_some = 0u;
         __syncthreads();
-        if (wv == 0) {
-            const uint64_t in_group = nc - s0 < 64 ? (1ull << (nc - s0)) - 1ull : ~0ull;
-            const uint64_t kept = greedy_keep(in_group & ~s_dead, early[lane]);
-            const int pos = nk + __popcll(kept & ((1ull << lane) - 1ull));
-            const bool mine = ((kept >> lane) & 1ull) != 0ull && pos < Dc;
-            if (mine) { kbox[pos] = sbox[i]; out[pos] = keys[i]; }
-            if (lane == 0) { s_nk = nk + __popcll(kept) < Dc ? nk + __popcll(kept) : Dc; s_dead = 0ull; }
+        const int gc = NC - c0 < group ? NC - c0 : group;
+        uint32_t some = 0u;
+        for (int i = t; i < nr * gc; i += SELC_THREADS) {
+            const int roi = i / gc, g = i - roi * gc;
+            if (sc[roi * Kc + c0 + g + 1] > score_thr) some |= 1u << g;
         }
+        if (some) atomicOr(&s_some, some);
         __syncthreads();
-        nk = s_nk;
+        todo = s_some;
+        if (t < gc && ((todo >> t) & 1u) == 0u) counts[c0 + t] = 0;
     }
-    if (t == 0) reinterpret_cast<int32_t*>(gkeys + (size_t)f * key_cap + (size_t)gridDim.x * Dc)[c] = nk;
+    for (; todo != 0u; todo &= todo - 1u) {
+        const int c = c0 + (GROUPED ? __builtin_ctz(todo) : 0);
+        uint64_t* out = gkeys + (size_t)f * key_cap + (size_t)c * Dc;
+        if (t == 0) { s_count = 0; s_nk = 0; s_dead = 0ull; }
+        __syncthreads();
+        for (int r0 = 0; r0 < nr; r0 += SELC_THREADS) {
+            const int roi = r0 + t;
+            uint64_t key = 0ull;
+            if (roi < nr) {
+                const int j = roi * Kc + c + 1;
+                const float s = sc[j];
+                const float4 b = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
+                if (s > score_thr && (b.z - b.x >= 1e-3f) && (b.w - b.y >= 1e-3f)) key = ((uint64_t)score_key(s) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
+            }
+            const uint64_t has = __ballot(key != 0ull);
+            int base = 0;
+            if (lane == 0 && has != 0ull) base = atomicAdd(&s_count, (int)__popcll(has));
+            base = __shfl(base, 0);
+            if (key != 0ull) lkeys[base + __popcll(has & ((1ull << lane) - 1ull))] = key;
+        }
+        __syncthreads();
+        const int nc = s_count;
+        int nk = 0;
+        if (nc > 0) {
+            int n2 = 64;
+            while (n2 < nc) n2 <<= 1;
+            for (int i = nc + t; i < n2; i += SELC_THREADS) lkeys[i] = 0ull;
+            const uint64_t* keys = block_sort_desc(lkeys, lkeys + SELC_MAX_POST, n2);
+            for (int i = t; i < nc; i += SELC_THREADS) {
+                const uint32_t j = 0xFFFFFFFFu - (uint32_t)(keys[i] & 0xFFFFFFFFull);
+                sbox[i] = *reinterpret_cast<const float4*>(bx + 4 * (size_t)j);
+            }
+            __syncthreads();
+            for (int s0 = 0; s0 < nc && nk < Dc; s0 += 64) {
+                const int i = s0 + lane;
+                const bool valid = i < nc;
+                const Box me = valid ? as_box(sbox[i]) : Box{0.f, 0.f, 0.f, 0.f};
+                // every wavefront: its share of the kept boxes against the group's 64, one candidate per lane
+                bool hit = false;
+                for (int q = wv; q < nk; q += NWV) hit = iou_over(as_box(kbox[q]), me, nms_thr) || hit;
+                const uint64_t dead = __ballot(hit);
+                if (lane == 0 && dead != 0ull) atomicOr(&s_dead, (unsigned long long)dead);
+                // and JW earlier candidates of the group against every later one
+                uint32_t bits = 0u;
+#pragma unroll
+                for (int u = 0; u < JW; ++u) {
+                    const int j = wv * JW + u;
+                    if (j < lane && valid && iou_over(as_box(sbox[s0 + j]), me, nms_thr)) bits |= 1u << u;
+                }
+                static_assert(JW == 8, "one byte of a row's word per wavefront");
+                reinterpret_cast<unsigned char*>(early)[lane * 8 + wv] = (unsigned char)bits;
+                __syncthreads();
+                if (wv == 0) {
+                    const uint64_t in_group = nc - s0 < 64 ? (1ull << (nc - s0)) - 1ull : ~0ull;
+                    const uint64_t kept = greedy_keep(in_group & ~s_dead, early[lane]);
+                    const int pos = nk + __popcll(kept & ((1ull << lane) - 1ull));
+                    const bool mine = ((kept >> lane) & 1ull) != 0ull && pos < Dc;
+                    if (mine) { kbox[pos] = sbox[i]; out[pos] = keys[i]; }
+                    if (lane == 0) { s_nk = nk + __popcll(kept) < Dc ? nk + __popcll(kept) : Dc; s_dead = 0ull; }
+                }
+                __syncthreads();
+                nk = s_nk;
+            }
+        }
+        if (t == 0) counts[c] = nk;
+        if constexpr (GROUPED) __syncthreads();   // (the next class reuses the lists; s_nk and s_count are read above)
+    }
 }
 
-// The D largest of a frame's kept keys: a key's rank is its place in its own class list plus, found by binary search, the
-// number of larger keys in every other list.
+// The D largest of a frame's kept keys.  A key's place is the number of larger keys.  Up to SELC_FEW classes: its place in its
+// own class's list plus, found by binary search, the number of larger keys in every other list.  That grows with the square
+// of the classes (19 of 50 kept boxes 11 to 18 us, 90 of 50 145 to 295), so with more of them only keys not below a bound are
+// counted: among the first p of every class, p as small as leaves at least D of them, the D-th largest is a lower bound of
+// the D-th largest of all (19 of 50 6 to 7 us, 90 of 50 9 to 11; 4 of 50 4.2 by searching, 5.0 by counting).
 __global__ __launch_bounds__(1024) void select_merge_kernel(const uint64_t* __restrict__ gkeys, int key_cap, const float* __restrict__ boxes,
                                                             int post, int Kc, int Dc, int D, float* __restrict__ out_boxes,
                                                             float* __restrict__ out_scores, int32_t* __restrict__ out_labels,
                                                             int32_t* __restrict__ out_n) {
     extern __shared__ __align__(16) unsigned char sel_smem[];
-    const int NC = Kc - 1, f = blockIdx.x, t = threadIdx.x;
+    __shared__ uint64_t s_bound;
+    __shared__ int s_n[2];
+    const int NC = Kc - 1, f = blockIdx.x, t = threadIdx.x, lane = t & 63;
+    const bool few = NC <= SELC_FEW;
     uint64_t* kkey = reinterpret_cast<uint64_t*>(sel_smem);              // [NC][Dc]
-    int* kcount = reinterpret_cast<int*>(kkey + (size_t)NC * Dc);        // [NC]
+    uint64_t* list = kkey + (size_t)NC * Dc;                             // more classes: [NC * Dc] keys to be counted, in any order
+    int* kcount = reinterpret_cast<int*>(few ? list : list + (size_t)NC * Dc);   // [NC]
     const uint64_t* gk = gkeys + (size_t)f * key_cap;
     const int32_t* gn = reinterpret_cast<const int32_t*>(gk + (size_t)NC * Dc);
+    if (t < 2) s_n[t] = 0;
+    if (t == 0) s_bound = 0ull;
     for (int c = t; c < NC; c += 1024) kcount[c] = gn[c];
     for (int e = t; e < NC * Dc; e += 1024) kkey[e] = gk[e];             // (entries behind a class's count are never used)
     __syncthreads();
-    int total = 0;
-    for (int c = 0; c < NC; ++c) total += kcount[c];
-    const int nk_out = total < D ? total : D;
-    for (int e = t; e < NC * Dc; e += 1024) {
-        const int c = e / Dc, q = e - c * Dc;
-        if (q >= kcount[c]) continue;
-        const uint64_t key = kkey[e];
-        int rank = q;
-        for (int c2 = 0; c2 < NC && rank < D; ++c2) {
-            if (c2 == c) continue;
-            const uint64_t* l = kkey + (size_t)c2 * Dc;
-            int lo = 0, hi = kcount[c2];          // first position whose key is smaller
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (l[mid] > key) lo = mid + 1; else hi = mid;
+    auto put = [&](uint64_t key, int rank) {
+        const uint32_t j = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
+        *reinterpret_cast<float4*>(out_boxes + ((size_t)f * D + rank) * 4) = *reinterpret_cast<const float4*>(boxes + ((size_t)f * post * Kc + j) * 4);
+        out_scores[(size_t)f * D + rank] = key_score((uint32_t)(key >> 32));
+        out_labels[(size_t)f * D + rank] = (int)(j % (uint32_t)Kc);
+    };
+    auto first = [&](int p) {                                            // keys among the first p of every class
+        int sum = 0;
+        for (int c = lane; c < NC; c += 64) sum += kcount[c] < p ? kcount[c] : p;
+        for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+        return sum;
+    };
+    const int total = first(Dc), want = total < D ? total : D;
+    // the first p keys of every class that are not below `bound`, put behind list[0 .. count)
+    auto collect = [&](int p, uint64_t bound, int* count) {
+        for (int e0 = 0; e0 < NC * p; e0 += 1024) {                      // (whole wavefronts)
+            const int e = e0 + t, c = e / p, q = e - c * p;
+            const bool in = e < NC * p && q < kcount[c < NC ? c : 0] && kkey[(size_t)(c < NC ? c : 0) * Dc + q] >= bound;
+            const uint64_t has = __ballot(in);
+            int base = 0;
+            if (lane == 0 && has != 0ull) base = atomicAdd(count, (int)__popcll(has));
+            base = __shfl(base, 0);
+            if (in) list[base + __popcll(has & ((1ull << lane) - 1ull))] = kkey[(size_t)c * Dc + q];
+        }
+        __syncthreads();
+        return *count;
+    };
+    // visit(key, number of larger keys) for list[0 .. m), by one lane per key: 16 lanes count a key together; in the rare longer
+    // list a thread counts alone and stops at `most`
+    auto ranked = [&](int m, int most, auto&& visit) {
+        if (m <= 1024) {
+            const int part = lane & 15;
+            for (int i = t >> 4; i < m; i += 64) {                       // (16 lanes in step: i is theirs)
+                const uint64_t key = list[i];
+                int cnt = 0;
+                for (int j = part; j < m; j += 16) cnt += list[j] > key ? 1 : 0;
+                for (int d = 8; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d);
+                if (part == 0) visit(key, cnt);
             }
-            rank += lo;
+        } else {
+            for (int i = t; i < m; i += 1024) {
+                const uint64_t key = list[i];
+                int cnt = 0;
+                for (int j = 0; j < m && cnt < most; ++j) cnt += list[j] > key ? 1 : 0;
+                visit(key, cnt);
+            }
         }
-        if (rank < D) {
-            const uint32_t j = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
-            *reinterpret_cast<float4*>(out_boxes + ((size_t)f * D + rank) * 4) = *reinterpret_cast<const float4*>(boxes + ((size_t)f * post * Kc + j) * 4);
-            out_scores[(size_t)f * D + rank] = key_score((uint32_t)(key >> 32));
-            out_labels[(size_t)f * D + rank] = c + 1;
+    };
+    if (few) {
+        for (int e = t; e < NC * Dc; e += 1024) {
+            const int c = e / Dc, q = e - c * Dc;
+            if (q >= kcount[c]) continue;
+            const uint64_t key = kkey[e];
+            int rank = q;
+            for (int c2 = 0; c2 < NC && rank < D; ++c2) {
+                if (c2 == c) continue;
+                const uint64_t* l = kkey + (size_t)c2 * Dc;
+                int lo = 0, hi = kcount[c2];                             // first position whose key is smaller
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (l[mid] > key) lo = mid + 1; else hi = mid;
+                }
+                rank += lo;
+            }
+            if (rank < D) put(key, rank);
         }
+    } else {
+        if (total > 2 * D) {
+            int p = (want + NC - 1) / NC;
+            while (first(p) < want) p *= 2;                                  // (first(Dc) = total: ends)
+            p = p < Dc ? p : Dc;
+            const int m = collect(p, 0ull, &s_n[0]);
+            ranked(m, want, [&](uint64_t key, int rank) { if (rank == want - 1) s_bound = key; });   // (keys are unique: one key)
+            __syncthreads();
+        }
+        const int m = collect(Dc, s_bound, &s_n[1]);
+        ranked(m, D, [&](uint64_t key, int rank) { if (rank < D) put(key, rank); });
     }
-    for (int d = nk_out + t; d < D; d += 1024) {
+    for (int d = want + t; d < D; d += 1024) {
         *reinterpret_cast<float4*>(out_boxes + ((size_t)f * D + d) * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
         out_scores[(size_t)f * D + d] = 0.f;
         out_labels[(size_t)f * D + d] = -1;
     }
-    if (t == 0 && out_n) out_n[f] = nk_out;
+    if (t == 0 && out_n) out_n[f] = want;
 }
 
 hipError_t launch_select(const float* scores, const float* boxes, const int32_t* roi_n, int n, int post, int Kc,
@@ -431,11 +525,15 @@ hipError_t launch_select(const float* scores, const float* boxes, const int32_t*
     const int NC = Kc - 1, Dc = D < post ? D : post;   // a class keeps at most Dc
     if (post <= SELC_MAX_POST && NC >= 1 && NC <= 2 * post && (long)NC * Dc <= SELC_MAX_KEPT && n <= 65535) {
         // (key_cap >= post * Kc holds the NC * Dc kept keys and, in the post that are left, the NC counts)
-        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(select_merge_kernel), (size_t)SELC_MAX_KEPT * 8 + 2 * SELC_MAX_POST * 4);
+        hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(select_merge_kernel), (size_t)SELC_MAX_KEPT * 16 + 2 * SELC_MAX_POST * 4);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(select_class_kernel, dim3(NC, n), dim3(SELC_THREADS), 0, s, scores, boxes, roi_n, post, Kc, score_thr, nms_thr, Dc,
-                           keys, key_cap);
-        hipLaunchKernelGGL(select_merge_kernel, dim3(n), dim3(1024), (size_t)NC * Dc * 8 + (size_t)NC * 4, s, keys, key_cap, boxes, post, Kc, Dc, D,
+        const long long blocks = (long long)n * NC;
+        const long long g = (blocks + SELC_RESIDENT - 1) / SELC_RESIDENT;
+        const int group = NC <= 32 ? 1 : g > SELC_MAX_GROUP ? SELC_MAX_GROUP : (int)g;
+        hipLaunchKernelGGL(group > 1 ? select_class_kernel<true> : select_class_kernel<false>, dim3((NC + group - 1) / group, n), dim3(SELC_THREADS),
+                           0, s, scores, boxes, roi_n, post, Kc, group, score_thr, nms_thr, Dc, keys, key_cap);
+        const size_t lds = (size_t)NC * Dc * (NC <= SELC_FEW ? 8 : 16) + (size_t)NC * 4;
+        hipLaunchKernelGGL(select_merge_kernel, dim3(n), dim3(1024), lds, s, keys, key_cap, boxes, post, Kc, Dc, D,
                            out_boxes, out_scores, out_labels, out_n);
         return hipGetLastError();
     }

@@ -444,6 +444,34 @@ def test_select_detections_op_edges_of_the_class_lists(post, Kc, D):
         assert np.array_equal(ol[f].cpu().numpy(), rl) and np.array_equal(ob[f].cpu().numpy(), rb) and np.array_equal(osc[f].cpu().numpy(), rs_), f
 
 
+@pytest.mark.parametrize("post,Kc,D,n,spread", [
+    (50, 91, 50, 3, 0.3),       # many full classes: only keys above a bound are counted
+    (50, 91, 50, 9, 0.3),       # more classes than the chip holds blocks: two per block
+    (60, 91, 50, 30, 1.5),      # four per block, most of them empty; no more kept boxes than twice the detections
+    (300, 34, 100, 40, 0.1),    # two per block, the last block with one class
+    (300, 21, 100, 40, 0.1),    # as many blocks, one class each
+    (64, 20, 1, 3, 0.3),        # one detection
+    (40, 33, 200, 3, 5.0),      # more detections than a class has ROIs
+    (20, 36, 300, 50, 0.2),     # three per block, lists shorter than a wavefront
+])
+def test_select_detections_op_with_many_classes(post, Kc, D, n, spread):
+    spec = replace(MINI_BF16, pre_nms=max(post, 64), post_nms=post, n_classes=Kc, max_det=D)
+    m, _ = gpu_model(spec, 0xBEEF + 77)
+    rs = np.random.RandomState(post + Kc + D)
+    scores = rs.dirichlet(np.ones(Kc) * spread, size=(n, post)).astype(np.float32)
+    scores[0] = np.round(scores[0] * 16) / 16                                # equal scores across classes
+    scores[1, :, 1:] *= 0.01                                                # no candidate
+    boxes = _rand_boxes(rs, n * post * Kc, 500.0).reshape(n, post, Kc, 4)
+    roi_n = np.full(n, post, np.int32)
+    roi_n[-1] = post // 2
+    ob, osc, ol, cnt = m.op_select_detections(to_dev(scores), to_dev(boxes), to_dev(roi_n))
+    torch.cuda.synchronize()
+    for f in range(n):
+        rb, rs_, rl, rn = oracle.select_detections(scores[f, :roi_n[f]], boxes[f, :roi_n[f]], spec.score_thr, spec.det_nms_thr, D)
+        assert cnt[f].item() == rn, f
+        assert np.array_equal(ol[f].cpu().numpy(), rl) and np.array_equal(ob[f].cpu().numpy(), rb) and np.array_equal(osc[f].cpu().numpy(), rs_), f
+
+
 @pytest.mark.parametrize("precision", [0, 1])
 def test_roialign_split_over_blocks_is_the_same(precision):
     """Few ROIs are split over several blocks each, many are not: a frame's values do not depend on how many came with it."""
