@@ -349,7 +349,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             load_to_lds16(wgt + a_base[p] + (size_t)kt * BK, dA + (size_t)(RPP * p) * LDS_ROW);
     };
 
-    // Sums start from the bias.  Its loads go out behind the first tile's requests and are used behind the wait for that tile.
+    // Sums start from the bias.  Its loads go out with the first tile's requests and are used behind the wait for that tile.
     f32x16_t acc[TN][TM];
     f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};                // F16: element e of lane l is channel 4 (l / 16) + e, pixel l % 16
     f32x4_t bias_q[TN][F16 ? 1 : 4];
@@ -390,6 +390,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     const bool vec = (a.out1 == nullptr) && ((a.Cout & 7) == 0) && ((a.ld0 & 7) == 0);
     const T* __restrict__ res = static_cast<const T*>(a.res);
     Vec8<T> rres[PREFETCH_RES ? TM * NIT : 1];
+    if (RING && multiplies) load_bias();   // (in front of the residual: the sums wait for the bias only)
     if (PREFETCH_RES && multiplies && vec && res != nullptr) {  // residual tile: issued now, consumed after the K loop
 #pragma unroll
         for (int j = 0; j < TM; ++j)
@@ -557,10 +558,18 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_waitcnt(0xc07f);                 // lgkmcnt(0)
         };
-        load_bias();
         in_registers();
         barrier();                                              // tile 0 has landed
         start_sums();
+        // (the bias is waited for here: left to the first product, the compiler puts that wait into every step of the loop)
+        if constexpr (F16) {
+            asm volatile("" : "+v"(acc4));
+        } else {
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(acc[i][j]));
+        }
         read_tile(0, g0);
         int buf = 0;                                            // buffer of tile kt
         auto step = [&](int kt, const TileFrags& now, TileFrags& next) {
