@@ -6,96 +6,19 @@
 // n = output channel and k = (ky, kx, ci); activations are NHWC so a K tile of one
 // filter tap is a contiguous run of input channels of one input pixel.
 //
-// Tiling: a block owns BM pixels x BN channels (32 x 32 to 256 x 256, chosen by the layer's size in launch_conv) and
-// walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Operand tiles go from global memory straight into LDS, two
-// buffers requested by the multiplying wavefronts or, in calls with few pixels, a ring of 3 to 8 filled by wavefronts of
-// its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
+// Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.hip, chosen
+// by the layer's size in launch_conv) and walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Operand tiles go from
+// global memory straight into LDS, two buffers requested by the multiplying wavefronts or, in calls with few pixels, a ring
+// of 3 to 8 filled by wavefronts of its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
 // the tile as 32x32 MFMA tiles.  The weights are the MFMA "A" operand (rows = channels) and the activations the
 // "B" operand (columns = pixels): each lane then holds 4 consecutive channels of one
 // pixel per accumulator quad, which is the contiguous direction of the NHWC output.
 // Sums start from the bias (fp32), here as in the single-kernel blocks, the fused predictors and the expansion tail, so a
 // layer's result does not depend on which of them a call's size picks.  Epilogue: [+ residual] [ReLU], then one rounding
 // to the output type.
-#include <type_traits>
-
-#include "thia_internal.h"
+#include "conv_common.h"
 
 namespace thia {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
-
-
-template <typename T>
-__device__ inline void mma_step(f32x16_t& acc, const u32x4_t& a, const u32x4_t& b);
-
-template <>
-__device__ inline void mma_step<bf16_t>(f32x16_t& acc, const u32x4_t& a, const u32x4_t& b) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
-}
-template <>
-__device__ inline void mma_step<float>(f32x16_t& acc, const u32x4_t& a, const u32x4_t& b) {
-    // 16 bytes = 4 consecutive k per lane half; MFMA step j contracts k = {j, 4 + j} of the 8-wide group
-    const f32x4_t fa = __builtin_bit_cast(f32x4_t, a), fb = __builtin_bit_cast(f32x4_t, b);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.x, fb.x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.y, fb.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.z, fb.z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.w, fb.w, acc, 0, 0, 0);
-}
-
-__device__ inline float load_elem(const float* p) { return *p; }
-__device__ inline float load_elem(const bf16_t* p) { return bf16_to_f32(*p); }
-__device__ inline void store_elem(float* p, float v) { *p = v; }
-__device__ inline void store_elem(bf16_t* p, float v) { *p = (bf16_t)pack_bf16x2(v, 0.f); }
-
-__device__ inline void load4(const float* p, float r[4]) {
-    const f32x4_t v = *reinterpret_cast<const f32x4_t*>(p);
-    r[0] = v.x; r[1] = v.y; r[2] = v.z; r[3] = v.w;
-}
-__device__ inline void load4(const bf16_t* p, float r[4]) {
-    const u32x2_t v = *reinterpret_cast<const u32x2_t*>(p);
-    r[0] = __uint_as_float(v.x << 16); r[1] = __uint_as_float(v.x & 0xffff0000u);
-    r[2] = __uint_as_float(v.y << 16); r[3] = __uint_as_float(v.y & 0xffff0000u);
-}
-__device__ inline void store4(float* p, const float r[4]) {
-    f32x4_t v = {r[0], r[1], r[2], r[3]};
-    *reinterpret_cast<f32x4_t*>(p) = v;
-}
-__device__ inline void store4(bf16_t* p, const float r[4]) {
-    u32x2_t v;
-    v.x = pack_bf16x2(r[0], r[1]);
-    v.y = pack_bf16x2(r[2], r[3]);
-    *reinterpret_cast<u32x2_t*>(p) = v;
-}
-
-// 8 consecutive elements of T as one register bundle
-template <typename T> struct Vec8;
-template <> struct __attribute__((aligned(16))) Vec8<bf16_t> { u32x4_t v; };
-template <> struct __attribute__((aligned(16))) Vec8<float> { f32x4_t lo, hi; };
-__device__ inline void unpack8(const Vec8<bf16_t>& x, float r[8]) {
-    const uint32_t w[4] = {x.v.x, x.v.y, x.v.z, x.v.w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) { r[2 * q] = __uint_as_float(w[q] << 16); r[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u); }
-}
-__device__ inline void unpack8(const Vec8<float>& x, float r[8]) {
-    r[0] = x.lo.x; r[1] = x.lo.y; r[2] = x.lo.z; r[3] = x.lo.w; r[4] = x.hi.x; r[5] = x.hi.y; r[6] = x.hi.z; r[7] = x.hi.w;
-}
-__device__ inline void store8(bf16_t* p, const float r[8]) {
-    u32x4_t v;
-    v.x = pack_bf16x2(r[0], r[1]);
-    v.y = pack_bf16x2(r[2], r[3]);
-    v.z = pack_bf16x2(r[4], r[5]);
-    v.w = pack_bf16x2(r[6], r[7]);
-    *reinterpret_cast<u32x4_t*>(p) = v;
-}
-__device__ inline void store8(float* p, const float r[8]) {
-    f32x4_t lo = {r[0], r[1], r[2], r[3]}, hi = {r[4], r[5], r[6], r[7]};
-    *reinterpret_cast<f32x4_t*>(p) = lo;
-    *reinterpret_cast<f32x4_t*>(p + 4) = hi;
-}
 
 // 16 bytes per lane from global memory straight into LDS: lane l's bytes land at lds + 16 l (lds is uniform over the
 // wavefront).  Counted by vmcnt like any vector memory load.  (The builtin exists in the device pass only.)
@@ -108,17 +31,7 @@ __device__ inline void load_to_lds16(const void* g, void* lds) {
 // 16 zero bytes (and some more) in global memory: what a padded filter tap fetches on the direct-to-LDS path
 __device__ __align__(256) unsigned char g_zero_page[256];
 
-// compile-time loop: the body sees the index as a constant (keeps accumulator indices static)
-template <int I, int N, typename F>
-__device__ inline void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
-// MODE 0: any filter size; 1: 1x1 unpadded (no tap bookkeeping); 2: 1x1 with a second source tensor;
-// 4: any filter size, followed by the expansion tail (ConvArgs::tail_*) on the block's output tile.
+// MODE 0: any filter size; 1: 1x1 unpadded (no tap bookkeeping); 2: 1x1 with a second source tensor.
 // STAGES 2: double-buffered operand tiles; more: a ring of that many (see RING below).
 template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0>
 __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1) void conv_igemm_kernel(const ConvArgs a) {
@@ -676,199 +589,6 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     }
     }
 
-    // ---- fused RPN predictors (large bf16 tile only): the block's ReLU'd 256 x 256 tile, rounded to bf16 as the
-    // stored tensor would be, stays in LDS and is contracted with the 1x1 predictor weights right away.
-    if constexpr (std::is_same<T, bf16_t>::value && std::is_same<OutT, bf16_t>::value && BM == 256 && BN == 256 && WAVES_M == 2 &&
-                  WAVES_N == 4 && MODE == 0) {
-        if (a.head_w != nullptr) {
-            constexpr int YP = BN * 2 + 16;            // LDS row pitch of the bf16 tile
-            constexpr int HKS = BN / 16;               // k-steps of the predictor contraction (16)
-            constexpr int HP = 96 * 4 + 16;            // fp32 row pitch of the per-wavefront output tile
-            static_assert(BM * YP <= 160 * 1024 && 32 * HP <= 32 * YP, "tile and output staging fit (launch_cfg requests BM * YP bytes)");
-            const u32x4_t* __restrict__ hwf = reinterpret_cast<const u32x4_t*>(a.head_w) + lane;
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-#pragma unroll
-                for (int i = 0; i < TN; ++i)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int ch = wn * WN + i * 32 + 8 * v + 4 * (lane >> 5);
-                        u32x2_t o = {pack_bf16x2(fmaxf(acc[i][j][4 * v], 0.f), fmaxf(acc[i][j][4 * v + 1], 0.f)),
-                                     pack_bf16x2(fmaxf(acc[i][j][4 * v + 2], 0.f), fmaxf(acc[i][j][4 * v + 3], 0.f))};
-                        *reinterpret_cast<u32x2_t*>(smem + (size_t)(wm * WM + j * 32 + frag_row) * YP + ch * 2) = o;
-                    }
-            // predictor weight fragments (3 channel tiles per k-step) run HRING k-steps ahead of their use; the first
-            // ones and the bias tile are requested once the accumulators are parked, in flight across the barrier
-            constexpr int HRING = 4;   // (8 spills and is slower)
-            __builtin_amdgcn_sched_barrier(0);   // (hoisted above the parking loop they would spill)
-            u32x4_t hw[HRING * 3];
-#pragma unroll
-            for (int ks = 0; ks < HRING; ++ks)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) hw[ks * 3 + i] = hwf[(i * HKS + ks) * 64];
-            f32x16_t hacc[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const f32x4_t q = *reinterpret_cast<const f32x4_t*>(a.head_b + i * 32 + 8 * v + 4 * (lane >> 5));
-                    hacc[i][4 * v] = q.x; hacc[i][4 * v + 1] = q.y; hacc[i][4 * v + 2] = q.z; hacc[i][4 * v + 3] = q.w;
-                }
-            __syncthreads();
-            // wavefront wv: pixels 32 wv .. 32 wv + 31 of the tile against all 96 (padded) predictor rows
-            const unsigned char* yrow = smem + (size_t)(wv * 32 + frag_row) * YP + frag_off;
-            static_for<0, HKS>([&](auto kc) {
-                constexpr int ks = decltype(kc)::value;
-                const u32x4_t b = *reinterpret_cast<const u32x4_t*>(yrow + ks * 32);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    mma_step<T>(hacc[i], hw[(ks % HRING) * 3 + i], b);
-                    if (ks + HRING < HKS) hw[(ks % HRING) * 3 + i] = hwf[(i * HKS + ks + HRING) * 64];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            });
-            // the wavefront's own 32 rows of the tile are dead now: fp32 results go there, then out in dense rows
-            unsigned char* hp = smem + (size_t)(wv * 32) * YP;
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    f32x4_t r = {hacc[i][4 * v], hacc[i][4 * v + 1], hacc[i][4 * v + 2], hacc[i][4 * v + 3]};
-                    *reinterpret_cast<f32x4_t*>(hp + (size_t)frag_row * HP + (i * 32 + 8 * v + 4 * (lane >> 5)) * 4) = r;
-                }
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-            const int A = a.head_a;
-            const int mbase = m0 + wv * 32;
-            for (int e = lane; e < 32 * A; e += 64) {
-                const int px = e / A, q = e - px * A;
-                if (mbase + px >= M) continue;
-                const f32x4_t d = *reinterpret_cast<const f32x4_t*>(hp + (size_t)px * HP + q * 16);
-                *reinterpret_cast<f32x4_t*>(a.head_deltas + ((size_t)(mbase + px) * A + q) * 4) = d;
-                a.head_logits[(size_t)(mbase + px) * A + q] = *reinterpret_cast<const float*>(hp + (size_t)px * HP + (4 * A + q) * 4);
-            }
-            return;
-        }
-    }
-
-    // ---- expansion tail (large bf16 tile only): the block's ReLU'd 256 x 256 tile, rounded to bf16 as the stored tensor
-    // would be, is parked in LDS (unpadded 512-byte rows, 16-byte chunk index XOR-ed with the row) and contracted with the
-    // next 1x1 layer's weights (fragment order, streamed from L2).  Wavefront wv owns output channels tail_n / 8 * wv ..
-    // and walks them 64 at a time over the two 128-pixel halves of the tile.  Residual and result pass through a 4 KB
-    // wavefront-private LDS region as bf16 (32 pixels x 64 channels), so that global loads and stores are 16 bytes per
-    // lane and cover whole 128-byte lines; the sum is formed in accumulator layout in fp32 and rounded once.
-    if constexpr (std::is_same<T, bf16_t>::value && std::is_same<OutT, bf16_t>::value && BM == 256 && BN == 256 && WAVES_M == 2 &&
-                  WAVES_N == 4 && MODE == 4) {
-        constexpr int TKS = BN / 16;               // k-steps of the tail contraction (16)
-        constexpr int TR = 4;                      // k-steps of weight fragments in flight
-        const int lh = lane >> 5;
-        auto yoff = [](int row, int byteoff) { return row * 512 + ((((byteoff >> 4) ^ row) & 31) << 4) + (byteoff & 15); };
-        auto roff = [](int row, int byteoff) { return row * 128 + ((((byteoff >> 4) ^ row) & 7) << 4) + (byteoff & 15); };
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int ch = wn * WN + i * 32 + 8 * v + 4 * lh;
-                    u32x2_t o = {pack_bf16x2(fmaxf(acc[i][j][4 * v], 0.f), fmaxf(acc[i][j][4 * v + 1], 0.f)),
-                                 pack_bf16x2(fmaxf(acc[i][j][4 * v + 2], 0.f), fmaxf(acc[i][j][4 * v + 3], 0.f))};
-                    *reinterpret_cast<u32x2_t*>(smem + yoff(wm * WM + j * 32 + frag_row, ch * 2)) = o;
-                }
-        __syncthreads();
-        const int N3 = a.tail_n, ctw = N3 / 256;   // 32-channel tiles per wavefront
-        const u32x4_t* __restrict__ twf = reinterpret_cast<const u32x4_t*>(a.tail_w) + lane;
-        const T* __restrict__ tres = static_cast<const T*>(a.tail_res);
-        T* __restrict__ tout = static_cast<T*>(a.tail_out);
-        unsigned char* R = smem + 256 * 512 + wv * 4096;
-        // pixel operand of the tail's MFMAs: row q * 128 + j * 32 + frag_row, logical chunk 2 ks + lane / 32; the rows of one
-        // fragment differ in their low five bits only (= frag_row), so the swizzled chunk is (x0 ^ 2 ks) for every j and q
-        const int x0 = ((lane >> 5) ^ frag_row) & 31;
-        const unsigned char* ylane = smem + frag_row * 512;
-        const int pr0 = lane >> 3, chunk = lane & 7;   // this lane's 16-byte pieces: pixels pr0 + 8 it, channels 8 chunk .. + 7
-        for (int cp = 0; cp < ctw; cp += 2) {
-            const int ct0 = wv * ctw + cp;
-            for (int q = 0; q < 2; ++q) {
-                u32x4_t rq[2][4];
-                auto fetch_res = [&](int j, u32x4_t* dst) {
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int pix = m0 + q * 128 + j * 32 + pr0 + 8 * it;
-                        dst[it] = *reinterpret_cast<const u32x4_t*>(tres + (size_t)(pix < M ? pix : 0) * N3 + ct0 * 32 + chunk * 8);
-                    }
-                };
-                fetch_res(0, rq[0]);
-                u32x4_t tw[2][TR];
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int k = 0; k < TR; ++k) tw[i][k] = twf[((size_t)(ct0 + i) * TKS + k) * 64];
-                f32x16_t t4[2][4];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const f32x4_t bq = *reinterpret_cast<const f32x4_t*>(a.tail_b + (ct0 + i) * 32 + 8 * v + 4 * lh);
-                        t4[i][0][4 * v] = bq.x; t4[i][0][4 * v + 1] = bq.y; t4[i][0][4 * v + 2] = bq.z; t4[i][0][4 * v + 3] = bq.w;
-                    }
-#pragma unroll
-                    for (int j = 1; j < 4; ++j) t4[i][j] = t4[i][0];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                static_for<0, TKS>([&](auto kc) {
-                    constexpr int ks = decltype(kc)::value;
-                    u32x4_t wf[2];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        wf[i] = tw[i][ks % TR];
-                        if (ks + TR < TKS) tw[i][ks % TR] = twf[((size_t)(ct0 + i) * TKS + ks + TR) * 64];
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const u32x4_t b = *reinterpret_cast<const u32x4_t*>(ylane + (q * 128 + j * 32) * 512 + ((x0 ^ (2 * ks)) << 4));
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) mma_step<T>(t4[i][j], wf[i], b);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-                static_for<0, 4>([&](auto jc) {
-                    constexpr int j = decltype(jc)::value;
-                    if (j + 1 < 4) fetch_res(j + 1, rq[(j + 1) & 1]);
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) *reinterpret_cast<u32x4_t*>(R + roff(pr0 + 8 * it, chunk * 16)) = rq[j & 1][it];
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            unsigned char* pp = R + roff(frag_row, (i * 32 + 8 * v + 4 * lh) * 2);
-                            const u32x2_t r = *reinterpret_cast<const u32x2_t*>(pp);
-                            const float r0 = fmaxf(t4[i][j][4 * v] + __uint_as_float(r.x << 16), 0.f);
-                            const float r1 = fmaxf(t4[i][j][4 * v + 1] + __uint_as_float(r.x & 0xffff0000u), 0.f);
-                            const float r2 = fmaxf(t4[i][j][4 * v + 2] + __uint_as_float(r.y << 16), 0.f);
-                            const float r3 = fmaxf(t4[i][j][4 * v + 3] + __uint_as_float(r.y & 0xffff0000u), 0.f);
-                            const u32x2_t o = {pack_bf16x2(r0, r1), pack_bf16x2(r2, r3)};
-                            *reinterpret_cast<u32x2_t*>(pp) = o;   // the lane rewrites exactly the bytes it has read
-                        }
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int pix = m0 + q * 128 + j * 32 + pr0 + 8 * it;
-                        const u32x4_t o = *reinterpret_cast<const u32x4_t*>(R + roff(pr0 + 8 * it, chunk * 16));
-                        if (pix < M) *reinterpret_cast<u32x4_t*>(tout + (size_t)pix * N3 + ct0 * 32 + chunk * 8) = o;
-                    }
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_wave_barrier();
-                });
-            }
-        }
-        return;
-    }
-
     // ---- epilogue.  Accumulator element e of lane l: channel 8*(e/4) + 4*(l/32) + e%4, pixel l%32.
     OutT* __restrict__ out0 = static_cast<OutT*>(a.out0);
     OutT* __restrict__ out1 = static_cast<OutT*>(a.out1);
@@ -993,12 +713,11 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     }
 }
 
-// Whether launch_conv picks the 256 x 256 bf16 tile for this layer (the only variant with the fused predictors).
+// Whether a layer gets the 256 x 256 bf16 tile of conv_large.hip for the sake of what that alone can fuse (predictors).
 static bool takes_large_tile(const ConvArgs& a) {
     const long long M = (long long)a.N * a.Ho * a.Wo;
-    const long long K = (long long)a.kh * a.kw * a.Cin + (a.in2 ? a.Cin2 : 0);
-    const long long tiles_l = ((M + 255) / 256) * ((a.Cout + 255) / 256);
-    return a.Cout % 256 == 0 && K >= 512 && (tiles_l >= 200 || (tiles_l >= 150 && K >= 8192)) && a.out1 == nullptr;
+    const long long K = (long long)a.kh * a.kw * a.Cin;
+    return K >= 512 && ((M + 255) / 256) * (a.Cout / 256) >= 200 && conv_large_supported(a, 1, 256, 256);
 }
 
 bool conv_heads_supported(const ConvArgs& a, int precision) {
@@ -1024,11 +743,7 @@ bool conv_supported(const ConvArgs& a, int precision) {
 
 template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0>
 static hipError_t launch_cfg(const ConvArgs& a, hipStream_t s) {
-    // (the expansion tail parks an unpadded 256 x 512-byte tile and gives each of the 8 wavefronts 4 KB beside it: the CU's whole LDS)
-    const size_t pipe = (size_t)STAGES * (BN + BM) * (BKB == 128 ? BKB : BKB + 16);
-    // (the fused-predictor path of the large bf16 tile parks a padded 256 x 528-byte tile, more than the two pipeline buffers)
-    const size_t heads = (std::is_same<T, bf16_t>::value && BM == 256 && BN == 256 && MODE == 0) ? (size_t)BM * (BN * 2 + 16) : 0;
-    const size_t lds = MODE == 4 ? (size_t)160 * 1024 : (pipe > heads ? pipe : heads);
+    const size_t lds = (size_t)STAGES * (BN + BM) * (BKB == 128 ? BKB : BKB + 16);
     auto kern = conv_igemm_kernel<T, BM, BN, BKB, WAVES_M, WAVES_N, MODE, OutT, STAGES, PROD>;
     {
         hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
@@ -1054,7 +769,7 @@ static hipError_t launch_one(const ConvArgs& a, hipStream_t s) {
 }
 
 bool conv_tail_supported(const ConvArgs& a, int precision) {
-    if (precision != 1 || !conv_supported(a, precision)) return false;
+    if (!conv_large_supported(a, precision, 256, 256)) return false;
     if (!a.tail_w || !a.tail_b || !a.tail_res || !a.tail_out || a.tail_res == a.tail_out) return false;
     if (a.tail_n < 512 || a.tail_n % 512 || a.tail_n > 4096) return false;
     if (a.Cout != 256 || !a.relu || a.res != nullptr || a.out1 != nullptr || a.in2 != nullptr || a.head_w != nullptr) return false;
@@ -1132,49 +847,58 @@ static hipError_t launch_out_f32(const ConvArgs& a, hipStream_t s) {
     return a.Cout <= 64 ? launch_one<bf16_t, 128, 64, 128, 2, 2, float>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, float>(a, s);
 }
 
+// Layers with more pixels.  A round of 256 blocks of a large tile takes, in 1/100 us, step for every K tile and fixed for what does
+// not grow with K (set-up, first operands, epilogue, stores); a last round that is not full costs less, its blocks having the
+// caches and the power budget of the others.  The tile with the least sum is taken, the larger one if they are equal.  Measured
+// in us, 256 x 256 / 192 x 256 / 256 x 128 / 192 x 128 / 128 x 128 (two blocks per CU, what these layers ran on): K 12544 to 1024
+// channels: 9 600 rows 228 / 199 / 254 / 268 / 274, 4 800 198 / 168 / 124 / 118 / 175; K 1024, 9 600 rows 27 / 23 / 29 / 25 / 30; 3x3
+// 512 -> 512: 16 320 pixels 90 / 81 / 72 / 105 / 94, 12 544 80 / 69 / 62 / 98 / 85, 50 176 192 / 234 / 243 / 261 / 247; 3x3 256 -> 256:
+// 32 640 49 / 44 / 38 / 58 / 49, 130 560 123 / 141 / 146 / 185 / 147; 3x3 128 -> 128, 802 816: - / - / 273 / 306 / 307.  Below K 512 a launch is
+// mostly epilogue (256 -> 1024 channels with a residual, 32 640 pixels: 40 / 41 / 44 / 46 / 38), which the two resident blocks of
+// 128 x 128 overlap with each other's K loop, except with a second source, where 200 tiles pay from K 384 on.
+static bool launch_large_bf16(const ConvArgs& a, long long K, hipStream_t s, hipError_t* e) {
+    const struct { int bm, bn, step, fixed; } tiles[4] = {{256, 256, 138, 900}, {192, 256, 106, 800}, {256, 128, 84, 700}, {192, 128, 64, 600}};
+    const long long M = (long long)a.N * a.Ho * a.Wo, KT = K / 64;
+    if (K < 512) {
+        if (a.in2 == nullptr || K < 384 || ((M + 255) / 256) * (a.Cout / 256) < 200 || !conv_large_supported(a, 1, 256, 256)) return false;
+        *e = launch_conv_large(a, 256, 256, s);
+        return true;
+    }
+    long long best = 0;
+    int pick = -1;
+    for (int i = 0; i < 4; ++i) {
+        if (!conv_large_supported(a, 1, tiles[i].bm, tiles[i].bn)) continue;
+        const long long n = ((M + tiles[i].bm - 1) / tiles[i].bm) * (a.Cout / tiles[i].bn), last = n % 256;
+        const long long rounds = 100 * (n / 256) + (last ? 60 + 40 * last / 256 : 0);   // in 1/100
+        const long long cost = rounds * (KT * tiles[i].step + tiles[i].fixed);
+        if (pick < 0 || cost < best) { best = cost; pick = i; }
+    }
+    if (pick < 0) return false;
+    *e = launch_conv_large(a, tiles[pick].bm, tiles[pick].bn, s);
+    return true;
+}
+
 hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream_t s) {
     if (!conv_supported(a, precision)) return hipErrorInvalidValue;
     if (a.tail_w != nullptr) {   // expansion tail: one kernel variant only
         if (out_f32 || !conv_tail_supported(a, precision)) return hipErrorInvalidValue;
-        return launch_cfg<bf16_t, 256, 256, 128, 2, 4, 4, bf16_t>(a, s);
+        return launch_conv_large(a, 256, 256, s);
     }
     if (a.head_w != nullptr) {   // fused predictors exist in one kernel variant only
         if (out_f32 || !conv_heads_supported(a, precision)) return hipErrorInvalidValue;
-        return launch_one<bf16_t, 256, 256, 128, 2, 4, bf16_t, true>(a, s);
+        return launch_conv_large(a, 256, 256, s);
     }
     const bool narrow = a.Cout <= 64;
     if (precision == 0) return launch_fp32(a, (long long)a.kh * a.kw * a.Cin + (a.in2 ? a.Cin2 : 0), s);
     if (out_f32) return launch_out_f32(a, s);
-    // Long-K layers are bound by L2 -> CU bandwidth with a 128 x 128 tile (64 flop per byte staged); a
-    // 256 x 256 tile halves that traffic.  It runs with 8 wavefronts (128 x 64 each), so that one block per
-    // CU still keeps two wavefronts per SIMD, and with 128-byte K rows, which doubles the bytes in flight
-    // per CU against the 64-byte variant (measured 15 % faster).  (4 wavefronts of 128 x 128 - also with the
-    // K step software-pipelined by hand and pinned with scheduling-group barriers, 30 % slower - and
-    // 256 x 128 with 64-byte K rows were measured and are slower; with fewer than ~200 tiles the 256 CUs
-    // are better filled by the 128 x 128 tile, except for very long K; with K < 512 the kernel is mostly epilogue
-    // (streaming the wide output), which two resident 128 x 128 blocks overlap with each other's K loop - except with a second source
-    // (projection shortcut folded in), where K >= 384 already pays for the large tile: measured 30 us faster per launch; 16 wavefronts of 64 x 64 on the
-    // 256 x 256 tile spill; 256 x 128 with 8 wavefronts and 64-byte rows is 1.5x slower.)
-    {
-        const long long M = (long long)a.N * a.Ho * a.Wo;
-        const long long K = (long long)a.kh * a.kw * a.Cin + (a.in2 ? a.Cin2 : 0);
-        // Short-K layers are pure streaming: what matters is how many independent tiles a CU has in
-        // flight, so they take the small-footprint 128 x 64 tile (4 blocks of 4 wavefronts per CU).
-        if (K <= 128 && a.out1 == nullptr && a.in2 == nullptr) return launch_one<bf16_t, 128, 64, 64, 2, 2, bf16_t>(a, s);
-        const long long tiles_l = ((M + 255) / 256) * ((a.Cout + 255) / 256);
-        hipError_t e;
-        if (tiles_l < 200 && launch_ring_bf16(a, K, s, &e)) return e;
-        // Very long K with a tile count that leaves CUs idle in a single round (the first FC layer: 152 tiles of
-        // 256 x 256 on 256 CUs): 192-pixel tiles give 200 tiles of 3/4 the work each.  Up to two 128 x 128 tiles per CU the
-        // pair is faster than one large tile on part of the CUs (4 800 x 1024, K 12544: 175 against 213 us; 8 000: 209 / 224;
-        // 9 600, 600 tiles: 347 / 278).
-        const long long tiles_192 = ((M + 191) / 192) * ((a.Cout + 255) / 256);
-        if (a.Cout % 256 == 0 && K >= 8192 && tiles_l < 200 && tiles_192 <= 256 && tiles_192 > tiles_l && tile_rounds(a, 128, 128) > 2 &&
-            a.out1 == nullptr && a.in2 == nullptr)
-            return launch_one<bf16_t, 192, 256, 128, 2, 4, bf16_t>(a, s);
-        if (a.Cout % 256 == 0 && (K >= 512 || (a.in2 != nullptr && K >= 384)) && (tiles_l >= 200 || (tiles_l >= 150 && K >= 8192)) && a.out1 == nullptr)
-            return launch_one<bf16_t, 256, 256, 128, 2, 4, bf16_t, true>(a, s);
-    }
+    const long long M = (long long)a.N * a.Ho * a.Wo;
+    const long long K = (long long)a.kh * a.kw * a.Cin + (a.in2 ? a.Cin2 : 0);
+    // Short-K layers are pure streaming: what matters is how many independent tiles a CU has in
+    // flight, so they take the small-footprint 128 x 64 tile (4 blocks of 4 wavefronts per CU).
+    if (K <= 128 && a.out1 == nullptr && a.in2 == nullptr) return launch_one<bf16_t, 128, 64, 64, 2, 2, bf16_t>(a, s);
+    hipError_t e;
+    if (((M + 255) / 256) * ((a.Cout + 255) / 256) < 200 && launch_ring_bf16(a, K, s, &e)) return e;
+    if (launch_large_bf16(a, K, s, &e)) return e;
     return narrow ? launch_one<bf16_t, 128, 64, 64, 2, 2, bf16_t>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 4, bf16_t, true>(a, s);
 }
 

@@ -80,6 +80,7 @@ def test_conv_op_matches_oracle(precision, case):
     dict(H=1, W=1, Cin=1024, Cout=55, k=1, stride=1, pad=0),       # channel count that is not a multiple of 4
     dict(H=7, W=5, Cin=64, Cout=128, k=3, stride=1, pad=1),        # 3x3 borders, rows shorter than a tile
     dict(H=9, W=21, Cin=128, Cout=136, k=3, stride=2, pad=1),      # strided 3x3, ragged channels
+    dict(H=9, W=21, Cin=128, Cout=256, k=3, stride=2, pad=1),      # strided 3x3 on the large tiles, images of 55 pixels
 ])
 def test_conv_result_does_not_depend_on_the_tile(precision, case):
     """The tile a layer runs on is chosen by its number of pixels (32 x 32 or 32 x 64 up to 256 x 256).  Every tile adds in
@@ -116,8 +117,13 @@ def test_conv_result_does_not_depend_on_the_tile(precision, case):
     (0, 128, 75, 1, False, 8160, 9000),        # 64 x 64 ring | 32 x 32 ring (last round of the former nearly empty)
     (0, 128, 256, 1, False, 2040, 4080),       # 32 x 32 ring | 64 x 64 ring
     (1, 256, 55, 1, True, 48000, 52000),       # predictors: 64 x 64 ring | 128 x 64
-    (1, 512, 256, 1, False, 8160, 8500),       # 64 x 128 ring in one round | 128 x 128
-    (1, 8192, 1024, 1, False, 300, 8200),      # 32 x 64 ring | 192 x 256
+    (1, 512, 256, 1, False, 8160, 8500),       # 64 x 128 ring in one round | 192 x 128
+    (1, 8192, 1024, 1, False, 300, 8200),      # 32 x 64 ring | 192 x 128
+    (1, 64, 256, 3, False, 8160, 8520),        # 64 x 128 ring | 192 x 128, an odd number of K tiles
+    (1, 64, 256, 3, False, 8520, 25320),       # | 256 x 128
+    (1, 64, 256, 3, False, 25320, 33000),      # | 192 x 256
+    (1, 64, 256, 3, False, 33000, 50040),      # | 256 x 256
+    (1, 1024, 1024, 1, False, 4200, 8300),     # 192 x 128 | 192 x 256, several channel tiles
 ])
 def test_layers_on_either_side_of_the_tile_rules(precision, Cin, Cout, k, out_f32, few, many):
     """Pixel counts around the lines between two tiles: the same values bit for bit on both."""
