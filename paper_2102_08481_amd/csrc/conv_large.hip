@@ -429,18 +429,21 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
         }
     }
 
-    // ---- expansion tail (large bf16 tile only): the block's ReLU'd 256 x 256 tile, rounded to bf16 as the stored tensor
-    // would be, is parked in LDS (unpadded 512-byte rows, 16-byte chunk index XOR-ed with the row) and contracted with the
-    // next 1x1 layer's weights (fragment order, streamed from L2).  Wavefront wv owns output channels tail_n / 8 * wv ..
-    // and walks them 64 at a time over the two 128-pixel halves of the tile.  Residual and result pass through a 4 KB
-    // wavefront-private LDS region as bf16 (32 pixels x 64 channels), so that global loads and stores are 16 bytes per
-    // lane and cover whole 128-byte lines; the sum is formed in accumulator layout in fp32 and rounded once.
+    // ---- expansion tail (256 x 256 tile only): the block's ReLU'd tile, rounded to bf16 as the stored tensor would be, is
+    // parked in LDS (unpadded 512-byte rows, 16-byte chunk index XOR-ed with the row) and contracted with the next 1x1 layer's
+    // weights (fragment order).  The eight wavefronts take 32 channels each of 256 at a time, for one 128-pixel half of the
+    // tile after the other.  It is bound by memory: residual and result are four times the tile (268 MB for 65 280 pixels, 53 us at
+    // the rate of a copy) and nothing else of the launch touches memory much.  So the residual of the next half is requested
+    // as soon as the registers of this one's are free, with the products of a half to arrive under, and the weights stay in
+    // registers for both halves (refilled under the second): loads complete in order, a weight fetched from L2 behind the
+    // residual would wait for it.  Residual and result pass through a 4 KB wavefront-private LDS region as bf16, so that global
+    // loads and stores are 16 bytes per lane and cover whole lines together with the neighbouring wavefront's; the sum is formed
+    // in accumulator layout in fp32 and rounded once.
     if constexpr (MODE == 4) {
         constexpr int TKS = BN / 16;               // k-steps of the tail contraction (16)
-        constexpr int TR = 4;                      // k-steps of weight fragments in flight
         const int lh = lane >> 5;
         auto yoff = [](int row, int byteoff) { return row * 512 + ((((byteoff >> 4) ^ row) & 31) << 4) + (byteoff & 15); };
-        auto roff = [](int row, int byteoff) { return row * 128 + ((((byteoff >> 4) ^ row) & 7) << 4) + (byteoff & 15); };
+        auto roff = [](int row, int byteoff) { return row * 64 + ((((byteoff >> 4) ^ (row >> 2)) & 3) << 4) + (byteoff & 15); };
 #pragma unroll
         for (int j = 0; j < TM; ++j)
 #pragma unroll
@@ -452,95 +455,110 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
                                  pack_bf16x2(fmaxf(acc[i][j][4 * v + 2], 0.f), fmaxf(acc[i][j][4 * v + 3], 0.f))};
                     *reinterpret_cast<u32x2_t*>(smem + yoff(wm * WM + j * 32 + frag_row, ch * 2)) = o;
                 }
-        __syncthreads();
-        const int N3 = a.tail_n, ctw = N3 / 256;   // 32-channel tiles per wavefront
-        const u32x4_t* __restrict__ twf = reinterpret_cast<const u32x4_t*>(a.tail_w) + lane;
-        const T* __restrict__ tres = static_cast<const T*>(a.tail_res);
-        T* __restrict__ tout = static_cast<T*>(a.tail_out);
+        __builtin_amdgcn_sched_barrier(0);
+        const int N3 = a.tail_n, groups = N3 / 256;
+        // descriptors over the tile's rows that exist: reads of the others give zeros, stores are dropped
+        const uint32_t tile_bytes = (uint32_t)((M - m0 < BM ? M - m0 : BM) * N3 * 2);
+        const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.tail_w), 0, (uint32_t)N3 * 512, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(static_cast<const T*>(a.tail_res) + (size_t)m0 * N3), 0, tile_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(static_cast<T*>(a.tail_out) + (size_t)m0 * N3, 0, tile_bytes, 0x00020000);
+        const uint32_t piece = (uint32_t)((lane >> 2) * N3 * 2 + (lane & 3) * 16);   // the lane's 16 bytes of a row's 64; rows lane / 4 + 16 it
+        auto place = [&](int hp, int j, int it) { return piece + (uint32_t)((hp * 128 + j * 32 + 16 * it) * N3 * 2); };
+        u32x4_t wt[TKS], rq[4][2];
+        f32x4_t bq[4];
+        auto fetch_w = [&](int g, int ks) { return __builtin_amdgcn_raw_buffer_load_b128(rt, (uint32_t)lane * 16, ((8 * g + wv) * TKS + ks) * 1024, 0); };
+        auto fetch_b = [&](int g, int v) { return *reinterpret_cast<const f32x4_t*>(a.tail_b + (8 * g + wv) * 32 + 8 * v + 4 * lh); };
+        auto fetch_res = [&](int g, int hp, int j, int it) { return __builtin_amdgcn_raw_buffer_load_b128(rres, place(hp, j, it), (8 * g + wv) * 64, 0); };
+#pragma unroll
+        for (int v = 0; v < 4; ++v) bq[v] = fetch_b(0, v);
+#pragma unroll
+        for (int ks = 0; ks < TKS; ++ks) wt[ks] = fetch_w(0, ks);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int it = 0; it < 2; ++it) rq[j][it] = fetch_res(0, 0, j, it);
+        barrier();
         unsigned char* R = smem + 256 * 512 + wv * 4096;
         // pixel operand of the tail's MFMAs: row hp * 128 + j * 32 + frag_row, logical chunk 2 ks + lane / 32; the rows of one
         // fragment differ in their low five bits only (= frag_row), so the swizzled chunk is (x0 ^ 2 ks) for every j and hp
-        const int x0 = ((lane >> 5) ^ frag_row) & 31;
+        const int x0 = (lh ^ frag_row) & 31;
         const unsigned char* ylane = smem + frag_row * 512;
-        const int pr0 = lane >> 3, ck = lane & 7;   // this lane's 16-byte pieces: pixels pr0 + 8 it, channels 8 ck .. + 7
-        for (int cp = 0; cp < ctw; cp += 2) {
-            const int ct0 = wv * ctw + cp;
-            for (int hp = 0; hp < 2; ++hp) {
-                u32x4_t rq[2][4];
-                auto fetch_res = [&](int j, u32x4_t* dst) {
+        // one half of the tile against 256 channels; MORE: channels come behind these
+        auto half = [&](auto hc, auto more, int g) {
+            constexpr int hp = decltype(hc)::value;
+            constexpr bool MORE = decltype(more)::value != 0, NEXT = hp == 0 || MORE;
+            f32x16_t t4[4];
 #pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int pix = m0 + hp * 128 + j * 32 + pr0 + 8 * it;
-                        dst[it] = *reinterpret_cast<const u32x4_t*>(tres + (size_t)(pix < M ? pix : 0) * N3 + ct0 * 32 + ck * 8);
-                    }
-                };
-                fetch_res(0, rq[0]);
-                u32x4_t tw[2][TR];
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int v = 0; v < 4; ++v) { t4[j][4 * v] = bq[v].x; t4[j][4 * v + 1] = bq[v].y; t4[j][4 * v + 2] = bq[v].z; t4[j][4 * v + 3] = bq[v].w; }
+            u32x4_t y[2][4];   // the next k-step's pixels are read while this one's are multiplied
+            auto read_y = [&](int ks, u32x4_t* to) {
 #pragma unroll
-                    for (int k = 0; k < TR; ++k) tw[i][k] = twf[((size_t)(ct0 + i) * TKS + k) * 64];
-                f32x16_t t4[2][4];
+                for (int j = 0; j < 4; ++j) to[j] = *reinterpret_cast<const u32x4_t*>(ylane + (hp * 128 + j * 32) * 512 + ((x0 ^ (2 * ks)) << 4));
+            };
+            read_y(0, y[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<0, TKS>([&](auto kc) {
+                constexpr int ks = decltype(kc)::value;
+                if constexpr (ks + 1 < TKS) read_y(ks + 1, y[(ks + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
+                for (int j = 0; j < 4; ++j) mma_step<T>(t4[j], wt[ks], y[ks & 1][j]);
+                if constexpr (hp == 1 && MORE) wt[ks] = fetch_w(g + 1, ks);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (hp == 1 && MORE) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) bq[v] = fetch_b(g + 1, v);
+            }
+            static_for<0, 2>([&](auto pc) {   // two 32-pixel sub-tiles at a time
+                constexpr int j0 = 2 * decltype(pc)::value;
+#pragma unroll
+                for (int j = j0; j < j0 + 2; ++j)
+#pragma unroll
+                    for (int it = 0; it < 2; ++it) *reinterpret_cast<u32x4_t*>(R + (j - j0) * 2048 + roff((lane >> 2) + 16 * it, (lane & 3) * 16)) = rq[j][it];
+                if constexpr (NEXT) {
+#pragma unroll
+                    for (int j = j0; j < j0 + 2; ++j)
+#pragma unroll
+                        for (int it = 0; it < 2; ++it) rq[j][it] = fetch_res(hp == 0 ? g : g + 1, 1 - hp, j, it);
+                }
+                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the region is private to this wavefront
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int j = j0; j < j0 + 2; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const f32x4_t bq = *reinterpret_cast<const f32x4_t*>(a.tail_b + (ct0 + i) * 32 + 8 * v + 4 * lh);
-                        t4[i][0][4 * v] = bq.x; t4[i][0][4 * v + 1] = bq.y; t4[i][0][4 * v + 2] = bq.z; t4[i][0][4 * v + 3] = bq.w;
+                        unsigned char* pp = R + (j - j0) * 2048 + roff(frag_row, (8 * v + 4 * lh) * 2);
+                        const u32x2_t r = *reinterpret_cast<const u32x2_t*>(pp);
+                        const float r0 = fmaxf(t4[j][4 * v] + __uint_as_float(r.x << 16), 0.f);
+                        const float r1 = fmaxf(t4[j][4 * v + 1] + __uint_as_float(r.x & 0xffff0000u), 0.f);
+                        const float r2 = fmaxf(t4[j][4 * v + 2] + __uint_as_float(r.y << 16), 0.f);
+                        const float r3 = fmaxf(t4[j][4 * v + 3] + __uint_as_float(r.y & 0xffff0000u), 0.f);
+                        const u32x2_t o = {pack_bf16x2(r0, r1), pack_bf16x2(r2, r3)};
+                        *reinterpret_cast<u32x2_t*>(pp) = o;   // the lane rewrites exactly the bytes it has read
                     }
+                __builtin_amdgcn_s_waitcnt(0xc07f);
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int j = 1; j < 4; ++j) t4[i][j] = t4[i][0];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                static_for<0, TKS>([&](auto kc) {
-                    constexpr int ks = decltype(kc)::value;
-                    u32x4_t wf[2];
+                for (int j = j0; j < j0 + 2; ++j)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        wf[i] = tw[i][ks % TR];
-                        if (ks + TR < TKS) tw[i][ks % TR] = twf[((size_t)(ct0 + i) * TKS + ks + TR) * 64];
+                    for (int it = 0; it < 2; ++it) {
+                        const u32x4_t o = *reinterpret_cast<const u32x4_t*>(R + (j - j0) * 2048 + roff((lane >> 2) + 16 * it, (lane & 3) * 16));
+                        __builtin_amdgcn_raw_buffer_store_b128(o, rout, place(hp, j, it), (8 * g + wv) * 64, 0);
                     }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const u32x4_t b = *reinterpret_cast<const u32x4_t*>(ylane + (hp * 128 + j * 32) * 512 + ((x0 ^ (2 * ks)) << 4));
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) mma_step<T>(t4[i][j], wf[i], b);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-                static_for<0, 4>([&](auto jc) {
-                    constexpr int j = decltype(jc)::value;
-                    if (j + 1 < 4) fetch_res(j + 1, rq[(j + 1) & 1]);
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) *reinterpret_cast<u32x4_t*>(R + roff(pr0 + 8 * it, ck * 16)) = rq[j & 1][it];
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            unsigned char* pp = R + roff(frag_row, (i * 32 + 8 * v + 4 * lh) * 2);
-                            const u32x2_t r = *reinterpret_cast<const u32x2_t*>(pp);
-                            const float r0 = fmaxf(t4[i][j][4 * v] + __uint_as_float(r.x << 16), 0.f);
-                            const float r1 = fmaxf(t4[i][j][4 * v + 1] + __uint_as_float(r.x & 0xffff0000u), 0.f);
-                            const float r2 = fmaxf(t4[i][j][4 * v + 2] + __uint_as_float(r.y << 16), 0.f);
-                            const float r3 = fmaxf(t4[i][j][4 * v + 3] + __uint_as_float(r.y & 0xffff0000u), 0.f);
-                            const u32x2_t o = {pack_bf16x2(r0, r1), pack_bf16x2(r2, r3)};
-                            *reinterpret_cast<u32x2_t*>(pp) = o;   // the lane rewrites exactly the bytes it has read
-                        }
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int pix = m0 + hp * 128 + j * 32 + pr0 + 8 * it;
-                        const u32x4_t o = *reinterpret_cast<const u32x4_t*>(R + roff(pr0 + 8 * it, ck * 16));
-                        if (pix < M) *reinterpret_cast<u32x4_t*>(tout + (size_t)pix * N3 + ct0 * 32 + ck * 8) = o;
-                    }
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_wave_barrier();
-                });
-            }
+                __builtin_amdgcn_s_waitcnt(0xc07f);
+                __builtin_amdgcn_wave_barrier();
+            });
+        };
+        int g = 0;
+        for (; g + 1 < groups; ++g) {
+            half(H0, H1, g);
+            half(H1, H1, g);
         }
+        half(H0, H0, g);
+        half(H1, H0, g);
         return;
     }
 
