@@ -310,6 +310,7 @@ __global__ __launch_bounds__(256, 2) void bottleneck_fused_kernel(const FusedBlo
             }
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the region is private to this wavefront
         __builtin_amdgcn_wave_barrier();
+        if (TAILN > 0 && a.tail_only) return;   // (531 MB less to write at exit 1 of 32 frames: 484 -> 412 us)
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int item = lane + 64 * it;

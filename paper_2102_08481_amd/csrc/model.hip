@@ -527,6 +527,7 @@ struct Tail {
     const float* bt = nullptr;
     void* z = nullptr;
     int n = 0, relu = 0;
+    bool only = false;   // nothing else reads the block's output
 };
 
 // Normalisation, stem and max-pool.
@@ -556,7 +557,7 @@ Tail stage_tail(const thia_model* m, int s, int ep_here) {
     if (!m->fuse_blocks || m->precision != 1) return tl;
     if (ep_here > 0) {
         const ExitUnit& E = m->ex[ep_here - 1];
-        if (m->has_lateral && E.lat_f) { tl.wtf = E.lat_f; tl.bt = E.lateral.b; tl.z = m->ws.hf; tl.n = E.lateral.co; tl.relu = 0; }
+        if (m->has_lateral && E.lat_f) { tl.wtf = E.lat_f; tl.bt = E.lateral.b; tl.z = m->ws.hf; tl.n = E.lateral.co; tl.relu = 0; tl.only = !m->debug; }
     } else if (s + 1 < 4 && !m->stage[s + 1].empty()) {
         const Block& N = m->stage[s + 1][0];
         if (N.tf) { tl.wtf = N.tf; tl.bt = N.c1.b; tl.z = m->ws.act[2]; tl.n = N.c1.co; tl.relu = 1; }
@@ -594,6 +595,7 @@ int run_stage(thia_model* m, int s, int nb, Trunk& t, const Tail* tail = nullptr
                 if (tail && tail->wtf && bi + 1 == nblocks && !B.has_sc && B.c1.co == 64) {
                     FusedBlockArgs ft = fa;
                     ft.wtf = tail->wtf; ft.bt = tail->bt; ft.z = static_cast<bf16_t*>(tail->z); ft.tail_n = tail->n; ft.tail_relu = tail->relu;
+                    ft.tail_only = tail->only ? 1 : 0;
                     if (fused_block_supported(ft, B.c1.co)) { fa = ft; with_tail = true; }
                 }
                 Scope sc(m, THIA_K_CONV);

@@ -125,6 +125,7 @@ struct FusedBlockArgs {
     const float* bt = nullptr;
     bf16_t* z = nullptr;
     int tail_n = 0, tail_relu = 0;
+    int tail_only = 0;   // y is read by the tail layer alone: it is not written
 };
 bool fused_block_supported(const FusedBlockArgs& a, int width);
 hipError_t launch_fused_block(const FusedBlockArgs& a, int width, hipStream_t s);
