@@ -32,8 +32,8 @@ __device__ inline void load_to_lds16(const void* g, void* lds) {
 __device__ __align__(256) unsigned char g_zero_page[256];
 
 // MODE 0: any filter size; 1: 1x1 unpadded (no tap bookkeeping); 2: 1x1 with a second source tensor.
-// STAGES 2: double-buffered operand tiles; more: a ring of that many (see RING below).
-template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0>
+// STAGES 2: double-buffered operand tiles; more: a ring of that many, U of them handed over at a time (see RING below).
+template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0, int U = 1>
 __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1) void conv_igemm_kernel(const ConvArgs a) {
     // (64-byte K rows: streaming layers, which want four blocks per CU, that is 128 registers)
     constexpr bool ONE = MODE == 1 || MODE == 2, DUAL = MODE == 2;
@@ -52,6 +52,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     constexpr bool DIRECT = BKB == 128;
     constexpr int LDS_ROW = DIRECT ? BKB : BKB + 16;   // staged path: padded row pitch (an odd multiple of 16 bytes)
     constexpr bool RING = STAGES > 2;
+    static_assert(RING ? STAGES % U == 0 && STAGES / U > 2 : U == 1, "the ring holds whole groups of tiles");
     static_assert(RING == (PROD > 0), "the ring is filled by loading wavefronts, the other paths have none");
     static_assert(!RING || DIRECT, "the ring holds direct-to-LDS tiles");
     constexpr int KK = BKB / 32;               // MFMA k-steps per tile row (32 bytes = 2 lane halves x 16 bytes)
@@ -356,13 +357,19 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         // PROD wavefronts do nothing but request tiles: issued by the multiplying wavefronts the requests stand in line with
         // their fragment reads and products (300 x 1024, K 12544: 128 us with two buffers, 60 with the ring, 39 / 32 with two /
         // four loading wavefronts; the ring's depth beyond 4 changes nothing).
-        // Step kt: the fragments of tile kt are in registers; tile kt + 1 is waited for (the newest STAGES - 2 tiles may
-        // still be on their way; loads complete in order), and past the barrier every wavefront has tile kt in registers,
-        // so its buffer takes tile kt + STAGES while the fragments of kt + 1 are read under the products of kt.
+        // U tiles (a group) are handed over per barrier: a step is one barrier, one round trip of the fragment reads and the products
+        // of a group, of which only the products grow with U (32 x 64, U 1 / 3: 300 x 1024, K 12544 36.4 / 31.5 us, 3x3 512 -> 512 at
+        // 510 pixels 16.2 / 14.5, what is left being the requests: 12 KB per K tile at 64 bytes a cycle; fp32 32 x 32, U 1 / 2:
+        // 200 x 1024, K 12544 119.7 / 115.1).  Larger groups need larger rings: where two blocks share a CU U is 1.
+        // Step g: the fragments of group g are in registers; group g + 1 is waited for (the newest STAGES / U - 2 groups may
+        // still be on their way; loads complete in order), and past the barrier every wavefront has group g in registers,
+        // so its buffers take group g + STAGES / U while the fragments of g + 1 are read under the products of g.
+        constexpr int GROUPS = STAGES / U;                      // groups the ring holds
         constexpr int PER_TILE = PA + PB;                       // requests of one thread per tile
-        constexpr int LEFT = (STAGES - 2) * PER_TILE;           // requests that may be outstanding when the next tile is needed
+        constexpr int LEFT = (GROUPS - 2) * U * PER_TILE;       // requests that may be outstanding when the next group is needed
         static_assert(LEFT < 64, "vmcnt counts to 63");
         constexpr int WAIT_LEFT = 0x0070 | (LEFT & 15) | ((LEFT >> 4) << 14);   // vmcnt(LEFT) lgkmcnt(0)
+        const int KG = (KT + U - 1) / U;                        // groups of the layer; the last one may lack tiles
         int q_kt = 0, q_c = 0, q_kx = 0, q_tap = 0;
         long long q_off = 0;                                    // element offset of (tap, first channel) from the pixel's tap 0
         const int kt1 = DUAL ? a.Cin / BK : 0;
@@ -404,38 +411,45 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             if (steady) __builtin_amdgcn_s_waitcnt(WAIT_LEFT);
             else __builtin_amdgcn_s_waitcnt(0x0070);            // the last tiles: vmcnt(0) lgkmcnt(0)
         };
+        auto request_group = [&](int buf) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (q_kt < KT) request(buf * U + u);
+        };
         if (loads) {
 #pragma unroll
-            for (int s = 0; s < STAGES - 1; ++s)
-                if (s < KT) request(s);
-            landed(KT >= STAGES - 1);
+            for (int s = 0; s < GROUPS - 1; ++s) request_group(s);
+            landed(KT >= (GROUPS - 1) * U);
             barrier();
-            if (STAGES - 1 < KT) request(STAGES - 1);
+            request_group(GROUPS - 1);
             int buf = 0;
-            for (int kt = 0; kt + 1 < KT; ++kt) {
-                landed(kt + STAGES - 1 < KT);
+            for (int g = 0; g + 1 < KG; ++g) {
+                landed((g + GROUPS) * U <= KT);
                 barrier();
-                if (kt + STAGES < KT) request(buf);
-                buf = buf + 1 == STAGES ? 0 : buf + 1;
+                request_group(buf);
+                buf = buf + 1 == GROUPS ? 0 : buf + 1;
             }
             barrier();                                          // the one in front of the epilogue
             return;
         }
-        struct TileFrags { Frags k[KK]; };
+        struct TileFrags { Frags k[U][KK]; };
         TileFrags g0, g1;
-        auto read_tile = [&](int buf, TileFrags& g) {
+        auto read_group = [&](int group, TileFrags& g) {        // (tiles that the last group lacks are read and not multiplied)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
+                const int buf = group * U + u;
                 if constexpr (F16) {
                     // k groups come in pairs: lanes 0..31 read group kk, lanes 32..63 group kk + 1 (16 bytes of row lane % 16,
                     // half (lane / 16) & 1 of the group); pair_k deals them out
                     if ((kk & 1) == 0) {
                         const int row = lane & 15, koff = ((2 * (kk + (lane >> 5)) + ((lane >> 4) & 1)) ^ (row & 7) ^ (row >> 3)) * 16;
-                        g.k[kk].a[0] = *reinterpret_cast<const u32x4_t*>(sA + (size_t)(buf * BN + wn * WN + row) * LDS_ROW + koff);
-                        g.k[kk].b[0] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + row) * LDS_ROW + koff);
+                        g.k[u][kk].a[0] = *reinterpret_cast<const u32x4_t*>(sA + (size_t)(buf * BN + wn * WN + row) * LDS_ROW + koff);
+                        g.k[u][kk].b[0] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + row) * LDS_ROW + koff);
                     }
                 } else {
-                    read_frags(buf, kk, g.k[kk]);
+                    read_frags(buf, kk, g.k[u][kk]);
                 }
             }
         };
@@ -450,12 +464,12 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             second = __uint_as_float(r[1]);
 #endif
         };
-        auto mma_tile = [&](const TileFrags& g) {
+        auto mma_tile = [&](const TileFrags& g, int u) {
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 if constexpr (F16) {
                     if ((kk & 1) == 0) {
-                        const u32x4_t fa = g.k[kk].a[0], fb = g.k[kk].b[0];
+                        const u32x4_t fa = g.k[u][kk].a[0], fb = g.k[u][kk].b[0];
                         float a0[4], b0[4];   // group kk: [0], [1]; group kk + 1: [2], [3]
                         pair_k(fa.x, fa.y, a0[0], a0[2]); pair_k(fa.z, fa.w, a0[1], a0[3]);
                         pair_k(fb.x, fb.y, b0[0], b0[2]); pair_k(fb.z, fb.w, b0[1], b0[3]);
@@ -463,7 +477,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
                         for (int q = 0; q < 4; ++q) acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[q], b0[q], acc4, 0, 0, 0);
                     }
                 } else {
-                    mma_frags(g.k[kk]);
+                    mma_frags(g.k[u][kk]);
                 }
             }
         };
@@ -483,22 +497,25 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
 #pragma unroll
                 for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(acc[i][j]));
         }
-        read_tile(0, g0);
-        int buf = 0;                                            // buffer of tile kt
-        auto step = [&](int kt, const TileFrags& now, TileFrags& next) {
+        read_group(0, g0);
+        int buf = 0;                                            // buffer of group g
+        auto step = [&](int g, const TileFrags& now, TileFrags& next) {
             // (waited for on both sides of the branch: where only one side does, the compiler puts a wait for everything in
             // front of the products and the next tile's reads are no longer behind them)
             in_registers();
-            if (kt + 1 < KT) {
+            if (g + 1 < KG) {
                 barrier();
-                buf = buf + 1 == STAGES ? 0 : buf + 1;
-                read_tile(buf, next);
+                buf = buf + 1 == GROUPS ? 0 : buf + 1;
+                read_group(buf, next);
             }
-            mma_tile(now);
+            mma_tile(now, 0);
+#pragma unroll
+            for (int u = 1; u < U; ++u)
+                if (g * U + u < KT) mma_tile(now, u);
         };
-        for (int kt = 0; kt < KT; kt += 2) {
-            step(kt, g0, g1);
-            if (kt + 1 < KT) step(kt + 1, g1, g0);
+        for (int g = 0; g < KG; g += 2) {
+            step(g, g0, g1);
+            if (g + 1 < KG) step(g + 1, g1, g0);
         }
         // (a wavefront's epilogue region lies in other wavefronts' operand tiles)
         in_registers();
@@ -741,10 +758,10 @@ bool conv_supported(const ConvArgs& a, int precision) {
     return true;
 }
 
-template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0>
+template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0, int U = 1>
 static hipError_t launch_cfg(const ConvArgs& a, hipStream_t s) {
     const size_t lds = (size_t)STAGES * (BN + BM) * (BKB == 128 ? BKB : BKB + 16);
-    auto kern = conv_igemm_kernel<T, BM, BN, BKB, WAVES_M, WAVES_N, MODE, OutT, STAGES, PROD>;
+    auto kern = conv_igemm_kernel<T, BM, BN, BKB, WAVES_M, WAVES_N, MODE, OutT, STAGES, PROD, U>;
     {
         hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
         if (e != hipSuccess) return e;
@@ -758,14 +775,14 @@ static hipError_t launch_cfg(const ConvArgs& a, hipStream_t s) {
 }
 
 // 1x1 unpadded convolutions (and the FC layers) get the variant without filter-tap bookkeeping.
-template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, typename OutT, bool ALLOW_DUAL = false, int STAGES = 2, int PROD = 0>
+template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, typename OutT, bool ALLOW_DUAL = false, int STAGES = 2, int PROD = 0, int U = 1>
 static hipError_t launch_one(const ConvArgs& a, hipStream_t s) {
     if (a.in2 != nullptr) {
-        if constexpr (ALLOW_DUAL) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 2, OutT, STAGES, PROD>(a, s);
+        if constexpr (ALLOW_DUAL) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 2, OutT, STAGES, PROD, U>(a, s);
         else return hipErrorInvalidValue;
     }
-    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 1, OutT, STAGES, PROD>(a, s);
-    return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 0, OutT, STAGES, PROD>(a, s);
+    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 1, OutT, STAGES, PROD, U>(a, s);
+    return launch_cfg<T, BM, BN, BKB, WAVES_M, WAVES_N, 0, OutT, STAGES, PROD, U>(a, s);
 }
 
 bool conv_tail_supported(const ConvArgs& a, int precision) {
@@ -783,12 +800,12 @@ static long long tile_rounds(const ConvArgs& a, int bm, int bn) {
     return (((M + bm - 1) / bm) * ((a.Cout + bn - 1) / bn) + 255) / 256;
 }
 
-// Smallest tile, with four loading wavefronts for 1x1 layers (32.3 us against 38.7 with two at 300 x 1024, K 12544) and two
-// for the others (17.4 against 19.1 at 510 x 512, K 4608).
+// Smallest tile, with four loading wavefronts for 1x1 layers (one tile per barrier: 32.3 us against 38.7 with two at 300 x 1024,
+// K 12544) and two for the others (17.4 against 19.1 at 510 x 512, K 4608).
 static hipError_t launch_ring_32x64(const ConvArgs& a, hipStream_t s) {
-    if (a.in2 != nullptr) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 2, bf16_t, 6, 4>(a, s);
-    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 1, bf16_t, 6, 4>(a, s);
-    return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 0, bf16_t, 6, 2>(a, s);
+    if (a.in2 != nullptr) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 2, bf16_t, 9, 4, 3>(a, s);
+    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 1, bf16_t, 9, 4, 3>(a, s);
+    return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 0, bf16_t, 9, 2, 3>(a, s);
 }
 
 // Calls with few pixels.  A 128 x 128 tile takes 0.64 us per K step (64 bf16 / 32 fp32 of every row) however few blocks
@@ -812,7 +829,7 @@ static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipE
     const long long best = c32 < c64 ? c32 : c64, wide = c64w < c128 ? c64w : c128;
     if ((best < wide ? best : wide) >= 64) return false;
     if (best <= wide) *e = c32 < c64 ? launch_ring_32x64(a, s) : launch_one<bf16_t, 64, 64, 128, 2, 2, bf16_t, true, 5, 4>(a, s);
-    else *e = c64w <= c128 ? launch_one<bf16_t, 64, 128, 128, 2, 2, bf16_t, true, 3, 4>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, bf16_t, true, 4, 4>(a, s);
+    else *e = c64w <= c128 ? launch_one<bf16_t, 64, 128, 128, 2, 2, bf16_t, true, 6, 4, 2>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, bf16_t, true, 4, 4>(a, s);
     return true;
 }
 
@@ -832,8 +849,9 @@ static hipError_t launch_fp32(const ConvArgs& a, long long K, hipStream_t s) {
     const long long r64 = tile_rounds(a, 64, 64), rw = tile_rounds(a, 128, 64);
     const long long c32 = 28 * tile_rounds(a, 32, 32), c64 = 57 * r64;
     const long long base = narrow ? (rw == 1 ? 150 : 106 * rw) : 207 * tile_rounds(a, 128, 128);
-    if (c32 < c64 && c32 < base) return launch_one<float, 32, 32, 128, 2, 2, float, true, 8, 4>(a, s);
-    if (c64 < base && !(narrow && K < 256 && r64 > 2)) return launch_one<float, 64, 64, 128, 2, 2, float, true, 5, 4>(a, s);
+    if (c32 < c64 && c32 < base) return launch_one<float, 32, 32, 128, 2, 2, float, true, 8, 4, 2>(a, s);
+    if (c64 < base && !(narrow && K < 256 && r64 > 2))
+        return r64 == 1 ? launch_one<float, 64, 64, 128, 2, 2, float, true, 6, 4, 2>(a, s) : launch_one<float, 64, 64, 128, 2, 2, float, true, 5, 4>(a, s);
     return narrow ? launch_one<float, 128, 64, 128, 2, 2, float>(a, s) : launch_one<float, 128, 128, 128, 2, 2, float, true>(a, s);
 }
 
@@ -842,7 +860,7 @@ static hipError_t launch_fp32(const ConvArgs& a, long long K, hipStream_t s) {
 // 32 640 18.3 / 14.2 (64 x 64); 55 channels, K 1024, 4 800 rows: 15.5 / 7.5.  Up to 64 channels the 128-pixel tile is no wider
 // than the ring's: 60 channels, K 256, 48 000 pixels 14.5 / 14.2, 64 800 15.7 / 17.5.
 static hipError_t launch_out_f32(const ConvArgs& a, hipStream_t s) {
-    if (tile_rounds(a, 32, 64) <= 1) return launch_one<bf16_t, 32, 64, 128, 1, 2, float, false, 6, 4>(a, s);
+    if (tile_rounds(a, 32, 64) <= 1) return launch_one<bf16_t, 32, 64, 128, 1, 2, float, false, 9, 4, 3>(a, s);
     if (tile_rounds(a, 64, 64) <= (a.Cout <= 64 ? 3 : 4)) return launch_one<bf16_t, 64, 64, 128, 2, 2, float, false, 5, 4>(a, s);
     return a.Cout <= 64 ? launch_one<bf16_t, 128, 64, 128, 2, 2, float>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, float>(a, s);
 }
