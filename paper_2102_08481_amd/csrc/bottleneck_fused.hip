@@ -38,6 +38,12 @@ __device__ inline void mma(f32x16_t& acc, const u32x4_t& a, const u32x4_t& b) {
 }
 __device__ inline uint32_t pack2(float lo, float hi) { return pack_bf16x2(lo, hi); }
 
+template <bool STREAM>
+__device__ inline void store_out(bf16_t* p, const u32x4_t& v) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(p));
+    else *reinterpret_cast<u32x4_t*>(p) = v;
+}
+
 // Scheduling fence for global memory instructions only: the compiler otherwise sinks prefetch loads
 // down to their first use to save registers, which exposes the L2 latency once per fragment.
 __device__ inline void pin_vmem() { __builtin_amdgcn_sched_barrier(0x78f); }
@@ -62,8 +68,9 @@ constexpr int NPX = TH * TW;            // 128
 // FIRST = true:  a stage's first block at stride 1: x has WD channels and enters the output through the
 //                projection shortcut; w3f holds [W3 | Ws] along K (2 WD) and b3 the summed biases, so phase 3 is one
 //                contraction over (t2 channels, x channels) with the x operand read from the staging tile.
+// STREAM: y is written past the caches.
 // TAILN = 128 or 256 (identity blocks only): z = [relu](Wt y + bt) with TAILN output channels is written to a.z as well.
-template <int WD, bool FIRST, int TAILN = 0>
+template <int WD, bool FIRST, int TAILN, bool STREAM>
 __global__ __launch_bounds__(256, 2) void bottleneck_fused_kernel(const FusedBlockArgs a) {
     static_assert(WD == 64, "work split below is written for 64-channel intermediates");
     static_assert(TAILN == 0 || (!FIRST && (TAILN == 128 || TAILN == 256)), "tail layer: identity blocks, 128 or 256 outputs");
@@ -315,7 +322,7 @@ __global__ __launch_bounds__(256, 2) void bottleneck_fused_kernel(const FusedBlo
         for (int it = 0; it < 4; ++it) {
             const int item = lane + 64 * it;
             const u32x4_t o = *reinterpret_cast<const u32x4_t*>(ep + (item >> 3) * EPITCH + (item & 7) * 16);
-            if (ooff[pt][it] != ~0u) *reinterpret_cast<u32x4_t*>(yout + ooff[pt][it]) = o;
+            if (ooff[pt][it] != ~0u) store_out<STREAM>(yout + ooff[pt][it], o);
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_wave_barrier();
@@ -682,6 +689,12 @@ bool fused_block_supported(const FusedBlockArgs& a, int width) {
     return tiles < (1ll << 30);
 }
 
+// Bytes of y above which it is written past the caches: what the memory-side cache (256 MB) cannot hold for the next kernel is
+// better kept out of the L2 as well, whose halo rows and weights stay.  32 frames at 540 x 960 (531 MB), written through / past:
+// first block 257 / 232 us, identity block 302 / 294, with the 128-channel tail 395 / 389.  Smaller outputs are read back from the
+// caches: written past them, whole calls took 1 % (32 frames, other layers) to 5 % (eight frames at 1080 x 1920) longer.
+constexpr long long kStreamBytes = 256ll << 20;
+
 template <typename Kern>
 static hipError_t launch_fused_kernel(Kern kern, size_t lds, const FusedBlockArgs& a, hipStream_t s) {
     {
@@ -694,15 +707,20 @@ static hipError_t launch_fused_kernel(Kern kern, size_t lds, const FusedBlockArg
     return hipGetLastError();
 }
 
+template <bool STREAM>
+static hipError_t launch_fused64(const FusedBlockArgs& a, hipStream_t s) {
+    constexpr size_t lds = (size_t)NHP * ((64 * 2 + 16) + (64 * 2 + 16)) + (size_t)NPX * (64 * 2 + 16);
+    if (a.tail_n == 128) return launch_fused_kernel(bottleneck_fused_kernel<64, false, 128, STREAM>, lds, a, s);
+    if (a.tail_n == 256) return launch_fused_kernel(bottleneck_fused_kernel<64, false, 256, STREAM>, lds, a, s);
+    if (a.first) return launch_fused_kernel(bottleneck_fused_kernel<64, true, 0, STREAM>, lds, a, s);
+    return launch_fused_kernel(bottleneck_fused_kernel<64, false, 0, STREAM>, lds, a, s);
+}
+
 hipError_t launch_fused_block(const FusedBlockArgs& a, int width, hipStream_t s) {
     if (!fused_block_supported(a, width)) return hipErrorInvalidValue;
-    constexpr size_t lds64 = (size_t)NHP * ((64 * 2 + 16) + (64 * 2 + 16)) + (size_t)NPX * (64 * 2 + 16);
     constexpr size_t lds128 = (size_t)NH * 256 + (size_t)NPX * 256;
     if (width == 128) return launch_fused_kernel(bottleneck_fused128_kernel, lds128, a, s);
-    if (a.tail_n == 128) return launch_fused_kernel(bottleneck_fused_kernel<64, false, 128>, lds64, a, s);
-    if (a.tail_n == 256) return launch_fused_kernel(bottleneck_fused_kernel<64, false, 256>, lds64, a, s);
-    if (a.first) return launch_fused_kernel(bottleneck_fused_kernel<64, true>, lds64, a, s);
-    return launch_fused_kernel(bottleneck_fused_kernel<64, false>, lds64, a, s);
+    return (long long)a.N * a.H * a.W * 512 > kStreamBytes ? launch_fused64<true>(a, s) : launch_fused64<false>(a, s);
 }
 
 // Host-side packing of a [Cout][K] bf16 weight matrix (K contiguous) into MFMA fragment order:
