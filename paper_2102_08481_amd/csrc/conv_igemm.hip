@@ -360,7 +360,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         // U tiles (a group) are handed over per barrier: a step is one barrier, one round trip of the fragment reads and the products
         // of a group, of which only the products grow with U (32 x 64, U 1 / 3: 300 x 1024, K 12544 36.4 / 31.5 us, 3x3 512 -> 512 at
         // 510 pixels 16.2 / 14.5, what is left being the requests: 12 KB per K tile at 64 bytes a cycle; fp32 32 x 32, U 1 / 2:
-        // 200 x 1024, K 12544 119.7 / 115.1).  Larger groups need larger rings: where two blocks share a CU U is 1.
+        // 200 x 1024, K 12544 119.7 / 115.1 before the step below).  Larger groups need larger rings: where two blocks share a CU U is 1.
         // Step g: the fragments of group g are in registers; group g + 1 is waited for (the newest STAGES / U - 2 groups may
         // still be on their way; loads complete in order), and past the barrier every wavefront has group g in registers,
         // so its buffers take group g + STAGES / U while the fragments of g + 1 are read under the products of g.
@@ -432,90 +432,125 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             barrier();                                          // the one in front of the epilogue
             return;
         }
-        struct TileFrags { Frags k[U][KK]; };
-        TileFrags g0, g1;
-        auto read_group = [&](int group, TileFrags& g) {        // (tiles that the last group lacks are read and not multiplied)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                const int buf = group * U + u;
-                if constexpr (F16) {
-                    // k groups come in pairs: lanes 0..31 read group kk, lanes 32..63 group kk + 1 (16 bytes of row lane % 16,
-                    // half (lane / 16) & 1 of the group); pair_k deals them out
-                    if ((kk & 1) == 0) {
-                        const int row = lane & 15, koff = ((2 * (kk + (lane >> 5)) + ((lane >> 4) & 1)) ^ (row & 7) ^ (row >> 3)) * 16;
-                        g.k[u][kk].a[0] = *reinterpret_cast<const u32x4_t*>(sA + (size_t)(buf * BN + wn * WN + row) * LDS_ROW + koff);
-                        g.k[u][kk].b[0] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + row) * LDS_ROW + koff);
-                    }
-                } else {
-                    read_frags(buf, kk, g.k[u][kk]);
-                }
-            }
-        };
-        // (lanes 0..31 of x, lanes 0..31 of y) and (lanes 32..63 of x, lanes 32..63 of y): lane group g = lane / 16 supplies k
-        // slot g, k = 0, 4, 1, 5 of the group's 8, then 2, 6, 3, 7 - the order of the 32x32 tiles - for group kk and kk + 1.
-        // (Every lane reading 16 bytes and using half of them needs twice the LDS reads: 130 us against 118 at 200 x 1024,
-        // K 12544; two 4-byte reads per lane conflict in the banks.)
-        auto pair_k = [&](uint32_t x, uint32_t y, float& first, float& second) {
-#if defined(__HIP_DEVICE_COMPILE__)
-            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-            first = __uint_as_float(r[0]);
-            second = __uint_as_float(r[1]);
-#endif
-        };
-        auto mma_tile = [&](const TileFrags& g, int u) {
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                if constexpr (F16) {
-                    if ((kk & 1) == 0) {
-                        const u32x4_t fa = g.k[u][kk].a[0], fb = g.k[u][kk].b[0];
-                        float a0[4], b0[4];   // group kk: [0], [1]; group kk + 1: [2], [3]
-                        pair_k(fa.x, fa.y, a0[0], a0[2]); pair_k(fa.z, fa.w, a0[1], a0[3]);
-                        pair_k(fb.x, fb.y, b0[0], b0[2]); pair_k(fb.z, fb.w, b0[1], b0[3]);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[q], b0[q], acc4, 0, 0, 0);
-                    }
-                } else {
-                    mma_frags(g.k[u][kk]);
-                }
-            }
-        };
         auto in_registers = [&]() {                             // the fragments read last are in registers
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_waitcnt(0xc07f);                 // lgkmcnt(0)
         };
-        in_registers();
-        barrier();                                              // tile 0 has landed
-        start_sums();
-        // (the bias is waited for here: left to the first product, the compiler puts that wait into every step of the loop)
+        int buf = 0;                                            // buffer of the group read last
         if constexpr (F16) {
-            asm volatile("" : "+v"(acc4));
-        } else {
+            // The matrix instruction wants one k of four from each lane group: 0, 4, 1, 5 of a group of 8, then 2, 6, 3, 7 (the order of
+            // the 32x32 tiles).  Lanes read 16 bytes instead, lanes 0..31 of k group 2 p and lanes 32..63 of 2 p + 1, and swap
+            // halves in registers (4-byte reads conflict in the banks: 124 us against 115 at 200 x 1024, K 12544).  A product is 32
+            // cycles and waits for the one before; everything else stands between the products of group g, one thing behind
+            // each: the swaps of group g + 1 and the reads of group g + 2, in three sets of registers.  200 x 1024, K 12544: swaps in front
+            // of the products 115 us, between them 103, the reads as well 96 (the products alone are 44).
+            struct Raw { uint32_t a[U][KK / 2][4], b[U][KK / 2][4]; } r0, r1, r2;
+            auto read_one = [&](int group, Raw& r, int u, int p, bool weights) {
+                const int row = lane & 15, koff = ((2 * (2 * p + (lane >> 5)) + ((lane >> 4) & 1)) ^ (row & 7) ^ (row >> 3)) * 16;
+                const unsigned char* at = weights ? sA + (size_t)((group * U + u) * BN + wn * WN + row) * LDS_ROW : sB + (size_t)((group * U + u) * BM + wm * WM + row) * LDS_ROW;
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(at + koff);
+                uint32_t* to = weights ? r.a[u][p] : r.b[u][p];
 #pragma unroll
-            for (int i = 0; i < TN; ++i)
+                for (int e = 0; e < 4; ++e) to[e] = v[e];
+            };
+            auto read_group = [&](int group, Raw& r) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int p = 0; p < KK / 2; ++p) { read_one(group, r, u, p, true); read_one(group, r, u, p, false); }
+            };
+            // x: lanes 0..31 of x and of y, y: lanes 32..63 of x and of y
+            auto swap = [&](uint32_t& x, uint32_t& y) {
+#if defined(__HIP_DEVICE_COMPILE__)
+                const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+                x = r[0];
+                y = r[1];
+#endif
+            };
+            auto deal = [&](Raw& r, int u, int p, int part) {   // one of the four swaps of k groups 2 p, 2 p + 1
+                if (part == 0) swap(r.a[u][p][0], r.a[u][p][1]);
+                if (part == 1) swap(r.b[u][p][0], r.b[u][p][1]);
+                if (part == 2) swap(r.a[u][p][2], r.a[u][p][3]);
+                if (part == 3) swap(r.b[u][p][2], r.b[u][p][3]);
+            };
+            in_registers();
+            barrier();                                          // group 0 has landed
+            start_sums();
+            // (the bias is waited for here: left to the first product, the compiler puts that wait into every step of the loop)
+            asm volatile("" : "+v"(acc4));
+            read_group(0, r0);
+            in_registers();
+            if (KG > 1) { barrier(); buf = 1; read_group(1, r1); }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int p = 0; p < KK / 2; ++p)
+#pragma unroll
+                    for (int part = 0; part < 4; ++part) deal(r0, u, p, part);
+            auto step = [&](int g, Raw& now, Raw& next, Raw& read) {
+                in_registers();
+                if (g + 2 < KG) barrier();
+                buf = buf + 1 == GROUPS ? 0 : buf + 1;          // (past the last group the ring's old contents are read and not used)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (u > 0 && g * U + u >= KT) break;        // (only the last group lacks tiles: nothing to deal either)
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int p = 0; p < KK / 2; ++p)
+#pragma unroll
+                        for (int part = 0; part < 4; ++part) {
+                            constexpr int at[4] = {0, 2, 1, 3};   // k group 2 p: words 0 and 2; 2 p + 1: 1 and 3
+                            acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(now.a[u][p][at[part]]), __uint_as_float(now.b[u][p][at[part]]), acc4, 0, 0, 0);
+                            deal(next, u, p, part);
+                            if (part % 2 == 0) read_one(buf, read, u, p, part == 0);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                }
+            };
+            for (int g = 0; g < KG; g += 3) {
+                step(g, r0, r1, r2);
+                if (g + 1 < KG) step(g + 1, r1, r2, r0);
+                if (g + 2 < KG) step(g + 2, r2, r0, r1);
+            }
+        } else {
+            struct TileFrags { Frags k[U][KK]; };
+            TileFrags g0, g1;
+            auto read_group = [&](int group, TileFrags& g) {    // (tiles that the last group lacks are read and not multiplied)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int kk = 0; kk < KK; ++kk) read_frags(group * U + u, kk, g.k[u][kk]);
+            };
+            auto mma_tile = [&](const TileFrags& g, int u) {
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) mma_frags(g.k[u][kk]);
+            };
+            in_registers();
+            barrier();                                          // group 0 has landed
+            start_sums();
+#pragma unroll
+            for (int i = 0; i < TN; ++i)                        // (as above)
 #pragma unroll
                 for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(acc[i][j]));
-        }
-        read_group(0, g0);
-        int buf = 0;                                            // buffer of group g
-        auto step = [&](int g, const TileFrags& now, TileFrags& next) {
-            // (waited for on both sides of the branch: where only one side does, the compiler puts a wait for everything in
-            // front of the products and the next tile's reads are no longer behind them)
-            in_registers();
-            if (g + 1 < KG) {
-                barrier();
-                buf = buf + 1 == GROUPS ? 0 : buf + 1;
-                read_group(buf, next);
-            }
-            mma_tile(now, 0);
+            read_group(0, g0);
+            auto step = [&](int g, const TileFrags& now, TileFrags& next) {
+                // (waited for on both sides of the branch: where only one side does, the compiler puts a wait for everything in
+                // front of the products and the next group's reads are no longer behind them)
+                in_registers();
+                if (g + 1 < KG) {
+                    barrier();
+                    buf = buf + 1 == GROUPS ? 0 : buf + 1;
+                    read_group(buf, next);
+                }
+                mma_tile(now, 0);
 #pragma unroll
-            for (int u = 1; u < U; ++u)
-                if (g * U + u < KT) mma_tile(now, u);
-        };
-        for (int g = 0; g < KG; g += 2) {
-            step(g, g0, g1);
-            if (g + 1 < KG) step(g + 1, g1, g0);
+                for (int u = 1; u < U; ++u)
+                    if (g * U + u < KT) mma_tile(now, u);
+            };
+            for (int g = 0; g < KG; g += 2) {
+                step(g, g0, g1);
+                if (g + 1 < KG) step(g + 1, g1, g0);
+            }
         }
         // (a wavefront's epilogue region lies in other wavefronts' operand tiles)
         in_registers();
@@ -835,10 +870,9 @@ static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipE
 
 // fp32.  Per K step and round of 256 blocks: 128 x 128 2.1 us and 64 x 64 ring 0.6, both bound by the fp32 matrix instructions
 // (1024 cycles per K step of a 64 x 64 tile), so that what counts is how many SIMDs share the work; 32 x 32 ring (16x16 matrix
-// tiles, four wavefronts) 0.33 in one round and 0.23 to 0.28 in several, about a third of it matrix instructions: the rest is
-// one barrier, the fragment reads and the exchange of lane halves per 32 values of K.  The rule counts 0.28 for it.  Measured
-// in us, 128 x 128 / 64 x 64 / 32 x 32: 200 x 1024, K 12544: 820 / 234 / 130; 600 x 1024: 833 / 250 / 304; 3x3 256 -> 256,
-// 1 020 pixels 164 / 50 / 28, 2 040 165 / 52 / 41, 4 080 168 / 56 / 77, 16 320 186 / 180 / 266; 1x1 64 -> 64, 8 160 pixels 64 x 64
+// tiles, four wavefronts) 0.24 in one round, half of it matrix instructions, and 0.23 to 0.28 in several.  The rule counts 0.28 for it.  Measured
+// in us, 128 x 128 / 64 x 64 / 32 x 32: 200 x 1024, K 12544: 820 / 234 / 96; 600 x 1024: 833 / 250 / 304; 3x3 256 -> 256,
+// 1 020 pixels 164 / 50 / 22, 2 040 165 / 52 / 34, 4 080 168 / 56 / 77, 16 320 186 / 180 / 266; 1x1 64 -> 64, 8 160 pixels 64 x 64
 // 5.9, 32 x 32 5.1, 9 000 pixels 5.9 / 6.8.
 // Up to 64 channels the two-buffer tile is 128 x 64: 1.5 us with one block per CU, 1.06 a round where two share it, so that
 // the ring pays while its last round is not full (64 x 64 ring / 128 x 64: 3x3 64 -> 64, 32 400 pixels 31.2 / 33.8, 66 000 64.6 / 69.9,
