@@ -359,8 +359,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         // four loading wavefronts; the ring's depth beyond 4 changes nothing).
         // U tiles (a group) are handed over per barrier: a step is one barrier, one round trip of the fragment reads and the products
         // of a group, of which only the products grow with U (32 x 64, U 1 / 3: 300 x 1024, K 12544 36.4 / 31.5 us, 3x3 512 -> 512 at
-        // 510 pixels 16.2 / 14.5, what is left being the requests: 12 KB per K tile at 64 bytes a cycle; fp32 32 x 32, U 1 / 2:
-        // 200 x 1024, K 12544 119.7 / 115.1 before the step below).  Larger groups need larger rings: where two blocks share a CU U is 1.
+        // 510 pixels 16.2 / 14.5; 64 x 64, U 1 / 2: 900 rows 45.2 / 40.6; fp32 32 x 32, U 1 / 2: 200 x 1024, K 12544 119.7 / 115.1; all but the
+        // second before the reads stood between the products).  Larger groups need larger rings: where two blocks share a CU U is 1.
         // Step g: the fragments of group g are in registers; group g + 1 is waited for (the newest STAGES / U - 2 groups may
         // still be on their way; loads complete in order), and past the barrier every wavefront has group g in registers,
         // so its buffers take group g + STAGES / U while the fragments of g + 1 are read under the products of g.
@@ -515,16 +515,6 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         } else {
             struct TileFrags { Frags k[U][KK]; };
             TileFrags g0, g1;
-            auto read_group = [&](int group, TileFrags& g) {    // (tiles that the last group lacks are read and not multiplied)
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int kk = 0; kk < KK; ++kk) read_frags(group * U + u, kk, g.k[u][kk]);
-            };
-            auto mma_tile = [&](const TileFrags& g, int u) {
-#pragma unroll
-                for (int kk = 0; kk < KK; ++kk) mma_frags(g.k[u][kk]);
-            };
             in_registers();
             barrier();                                          // group 0 has landed
             start_sums();
@@ -532,20 +522,27 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             for (int i = 0; i < TN; ++i)                        // (as above)
 #pragma unroll
                 for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(acc[i][j]));
-            read_group(0, g0);
-            auto step = [&](int g, const TileFrags& now, TileFrags& next) {
-                // (waited for on both sides of the branch: where only one side does, the compiler puts a wait for everything in
-                // front of the products and the next group's reads are no longer behind them)
-                in_registers();
-                if (g + 1 < KG) {
-                    barrier();
-                    buf = buf + 1 == GROUPS ? 0 : buf + 1;
-                    read_group(buf, next);
-                }
-                mma_tile(now, 0);
 #pragma unroll
-                for (int u = 1; u < U; ++u)
-                    if (g * U + u < KT) mma_tile(now, u);
+            for (int i = 0; i < U * KK; ++i) read_frags(i / KK, i % KK, g0.k[i / KK][i % KK]);
+            auto step = [&](int g, const TileFrags& now, TileFrags& next) {
+                // The next group's fragments are read between the products, two k-steps behind each of the first half: in front of all
+                // products they queue at the LDS (300 x 1024, K 12544 31.2 / 27.8 us, 1500 x 1024 59 / 55, 3x3 256 -> 256 at 4 715 pixels 14.9 / 14.0).
+                in_registers();
+                if (g + 1 < KG) barrier();
+                buf = buf + 1 == GROUPS ? 0 : buf + 1;          // (past the last group the ring's old contents are read and not used)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (u > 0 && g * U + u >= KT) break;        // (only the last group lacks tiles)
+#pragma unroll
+                    for (int kk = 0; kk < KK; ++kk) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        mma_frags(now.k[u][kk]);
+#pragma unroll
+                        for (int i = 2 * (u * KK + kk); i < 2 * (u * KK + kk) + 2; ++i)
+                            if (i < U * KK) read_frags(buf * U + i / KK, i % KK, next.k[i / KK][i % KK]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             };
             for (int g = 0; g < KG; g += 2) {
                 step(g, g0, g1);
@@ -835,14 +832,6 @@ static long long tile_rounds(const ConvArgs& a, int bm, int bn) {
     return (((M + bm - 1) / bm) * ((a.Cout + bn - 1) / bn) + 255) / 256;
 }
 
-// Smallest tile, with four loading wavefronts for 1x1 layers (one tile per barrier: 32.3 us against 38.7 with two at 300 x 1024,
-// K 12544) and two for the others (17.4 against 19.1 at 510 x 512, K 4608).
-static hipError_t launch_ring_32x64(const ConvArgs& a, hipStream_t s) {
-    if (a.in2 != nullptr) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 2, bf16_t, 9, 4, 3>(a, s);
-    if (a.kh == 1 && a.kw == 1 && a.pad == 0) return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 1, bf16_t, 9, 4, 3>(a, s);
-    return launch_cfg<bf16_t, 32, 64, 128, 1, 2, 0, bf16_t, 9, 2, 3>(a, s);
-}
-
 // Calls with few pixels.  A 128 x 128 tile takes 0.64 us per K step (64 bf16 / 32 fp32 of every row) however few blocks
 // there are, because a block waits for the one tile it has in flight; the ring tiles take, per K step and round of 256
 // blocks: 32 x 64 0.16 us, 64 x 64 0.24, 64 x 128 0.31, 128 x 128 0.49 (measured at K 12544).  The rule takes the
@@ -863,8 +852,12 @@ static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipE
     const long long c64w = K >= 512 && !narrow && tile_rounds(a, 64, 128) == 1 ? 31 : 1000, c128 = K >= 768 && !narrow ? 49 : 1000;
     const long long best = c32 < c64 ? c32 : c64, wide = c64w < c128 ? c64w : c128;
     if ((best < wide ? best : wide) >= 64) return false;
-    if (best <= wide) *e = c32 < c64 ? launch_ring_32x64(a, s) : launch_one<bf16_t, 64, 64, 128, 2, 2, bf16_t, true, 5, 4>(a, s);
-    else *e = c64w <= c128 ? launch_one<bf16_t, 64, 128, 128, 2, 2, bf16_t, true, 6, 4, 2>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, bf16_t, true, 4, 4>(a, s);
+    if (best <= wide)
+        *e = c32 < c64                     ? launch_one<bf16_t, 32, 64, 128, 1, 2, bf16_t, true, 9, 4, 3>(a, s)
+             : tile_rounds(a, 64, 64) == 1 ? launch_one<bf16_t, 64, 64, 128, 2, 2, bf16_t, true, 6, 4, 2>(a, s)
+                                           : launch_one<bf16_t, 64, 64, 128, 2, 2, bf16_t, true, 5, 4>(a, s);
+    else
+        *e = c64w <= c128 ? launch_one<bf16_t, 64, 128, 128, 2, 2, bf16_t, true, 6, 4, 2>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, bf16_t, true, 4, 4>(a, s);
     return true;
 }
 
