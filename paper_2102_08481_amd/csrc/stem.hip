@@ -84,9 +84,16 @@ __global__ __launch_bounds__(256) void stem_kernel(const uint8_t* __restrict__ f
 typedef __attribute__((ext_vector_type(8))) __bf16 sbf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float sf32x16_t;
 
+template <int I, int N, typename F>
+__device__ inline void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
 constexpr int MP_W = 72;                       // patch columns (2 * 32 stem columns + taps)
 constexpr int MK_ROWS = 22;                    // 21 (c,ky) rows + 1 zero row
-constexpr int MW_PITCH = MK_ROWS * 16 + 16;    // bytes per channel row of the weight tile (padded)
 constexpr int ME_PITCH = 128 + 16;             // epilogue row pitch (64 bf16 + pad)
 
 // Stem and max-pool in one kernel (bf16 models): the stem tensor is four times the size of the pooled one
@@ -107,7 +114,6 @@ __global__ __launch_bounds__(256, 2) void stem_pool_mfma_kernel(const uint8_t* _
                                                              const float* __restrict__ bias, float mean, float stdv,
                                                              bf16_t* __restrict__ out) {
     __shared__ __align__(16) bf16_t patch[3 * QPR * MP_W];
-    __shared__ __align__(16) unsigned char wt[64 * MW_PITCH];
     __shared__ __align__(16) unsigned char etile[4 * 32 * ME_PITCH];
     __shared__ bf16_t lut[256];
     __shared__ __align__(16) float sbias[64];
@@ -116,23 +122,27 @@ __global__ __launch_bounds__(256, 2) void stem_pool_mfma_kernel(const uint8_t* _
     // Persistent blocks: weights and the normalisation table are staged once, and the raw pixels of the next
     // tile are requested (9 dwords per thread, held in registers) before the current tile is multiplied.
     lut[t] = f32_to_bf16(((float)t - mean) / stdv);
-    for (int i = t; i < 64 * MK_ROWS; i += 256) {
-        const int ch = i / MK_ROWS, r = i - ch * MK_ROWS;
-        *reinterpret_cast<u32x4_t*>(wt + ch * MW_PITCH + r * 16) = *reinterpret_cast<const u32x4_t*>(wk + (size_t)ch * MK_ROWS * 8 + r * 8);
-    }
+    // The weights stay in registers (fragments of k-step s: channel 32 i + lane % 32, row 2 s + lane / 32 of the 22): read from LDS
+    // for every product they were two fifths of the kernel's LDS traffic.  32 frames at 540 x 960 193 -> 152 us (with the k-steps unrolled,
+    // their addresses in the instructions, and no spills), five of 361 x 643, whose rows start on odd addresses, 41 -> 18.  The
+    // products take 57 us; the rest is the pool's selects and maxima and the fill of the patch, each wavefront in turn.
+    u32x4_t wf[MK_ROWS / 2][2];
+#pragma unroll
+    for (int s = 0; s < MK_ROWS / 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) wf[s][i] = *reinterpret_cast<const u32x4_t*>(wk + ((size_t)(i * 32 + (lane & 31)) * MK_ROWS + 2 * s + (lane >> 5)) * 8);
     const int tiles_x = (Wp + QP_COLS - 1) / QP_COLS, tiles_y = (Hp + QP_ROWS - 1) / QP_ROWS;
     const int total = n * tiles_y * tiles_x;
-    constexpr int DW_ROW = MP_W / 4;
-    constexpr int N_DW = 3 * QPR * DW_ROW;
-    constexpr int PER_T = (N_DW + 255) / 256;
-    const bool dwords = (W & 3) == 0;   // every patch row then starts on a 4-byte boundary of the frame
-    // patch coordinates (channel, row, dword) of dword q of this thread
-    auto dword_pos = [&](int q, int& c, int& py, int& pd) {
-        const int i = min(q * 256 + t, N_DW - 1);
-        c = i / (QPR * DW_ROW);
-        const int r = i - c * (QPR * DW_ROW);
-        py = r / DW_ROW;
-        pd = r - py * DW_ROW;
+    // Patch rows (channel c, row py: c QPR + py) of 18 dwords.  Thread t < 252 loads dword t % 18 of the rows t / 18 + 14 q, so that all
+    // its dwords lie in one column of the patch.  Every load is unconditional, at a clamped place; `there` below says which of
+    // the four pixels lie inside the image.  (A dword that reaches past the last column is loaded to end there and shifted.)
+    constexpr int DW_ROW = MP_W / 4, ROWS_Q = 14, PER_T = (3 * QPR + ROWS_Q - 1) / ROWS_Q;
+    static_assert(ROWS_Q * DW_ROW <= 256, "one thread per dword of 14 rows");
+    const int row0 = min(t / DW_ROW, ROWS_Q - 1), pd = t % DW_ROW;
+    auto row_pos = [&](int q, int& c, int& py) {
+        const int row = row0 + ROWS_Q * q;
+        c = (row >= QPR ? 1 : 0) + (row >= 2 * QPR ? 1 : 0);
+        py = row - c * QPR;
     };
     struct TileOrg { int img, px0, py0, ix0, iy0; };
     auto tile_org = [&](int tile) {
@@ -150,66 +160,58 @@ __global__ __launch_bounds__(256, 2) void stem_pool_mfma_kernel(const uint8_t* _
     uint32_t raw[PER_T];
     auto load_raw = [&](const TileOrg& o) {
         const uint8_t* f = frames + (size_t)o.img * 3 * H * W;
+        const int ix = min(max(o.ix0 + 4 * pd, 0), W - 4);
 #pragma unroll
         for (int q = 0; q < PER_T; ++q) {
-            int c, py, pd;
-            dword_pos(q, c, py, pd);
-            const int iy = o.iy0 + py, ix = o.ix0 + 4 * pd;
-            raw[q] = 0u;
-            if ((unsigned)iy < (unsigned)H && ix >= 0 && ix + 3 < W) raw[q] = *reinterpret_cast<const uint32_t*>(f + ((size_t)c * H + iy) * W + ix);
+            int c, py;
+            row_pos(q, c, py);
+            const int iy = min(max(o.iy0 + py, 0), H - 1);
+            __builtin_memcpy(&raw[q], f + ((size_t)c * H + iy) * W + ix, 4);   // (rows of odd widths start anywhere)
         }
     };
     int tile = blockIdx.x;
     if (tile >= total) return;
     TileOrg cur = tile_org(tile);
-    if (dwords) load_raw(cur);
-    __syncthreads();   // lut and weights visible
+    load_raw(cur);
+#pragma unroll
+    for (int s = 0; s < MK_ROWS / 2; ++s)   // (the weights are waited for here: left to the products, the compiler waits for them in every tile)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(wf[s][i]));
+    __syncthreads();   // lut and bias visible
     const int g = lane >> 5, pxl = lane & 31;
     for (; tile < total; tile += gridDim.x) {
         // ---- patch fill: out-of-image pixels become the bf16 zero of the normalised tensor
-        if (dwords) {
+        {
+            const int ix = cur.ix0 + 4 * pd;                             // (a multiple of 4)
+            const int in_row = ix >= 0 ? W - ix : 0;                     // pixels of the row from ix on
+            const int shift = in_row > 0 && in_row < 4 ? 8 * (4 - in_row) : 0;
+            uint32_t* dst = reinterpret_cast<uint32_t*>(patch + row0 * MP_W + 4 * pd);
 #pragma unroll
             for (int q = 0; q < PER_T; ++q) {
-                if (q * 256 + t < N_DW) {
-                    int c, py, pd;
-                    dword_pos(q, c, py, pd);
-                    const int iy = cur.iy0 + py, ix = cur.ix0 + 4 * pd;
-                    const bool in = (unsigned)iy < (unsigned)H && ix >= 0 && ix + 3 < W;
-                    uint32_t lo = 0u, hi = 0u;
-                    if (in) {
-                        lo = (uint32_t)lut[raw[q] & 0xffu] | ((uint32_t)lut[(raw[q] >> 8) & 0xffu] << 16);
-                        hi = (uint32_t)lut[(raw[q] >> 16) & 0xffu] | ((uint32_t)lut[raw[q] >> 24] << 16);
-                    }
-                    uint32_t* d = reinterpret_cast<uint32_t*>(patch + (c * QPR + py) * MP_W + 4 * pd);
+                int c, py;
+                row_pos(q, c, py);
+                const int there = (unsigned)(cur.iy0 + py) < (unsigned)H ? in_row : 0;
+                const uint32_t v = raw[q] >> shift;
+                uint32_t lo = (uint32_t)lut[v & 0xffu] | (uint32_t)lut[(v >> 8) & 0xffu] << 16;
+                uint32_t hi = (uint32_t)lut[(v >> 16) & 0xffu] | (uint32_t)lut[v >> 24] << 16;
+                if (there < 4) {
+                    hi = there < 3 ? 0u : hi & 0xffffu;
+                    lo = there < 1 ? 0u : there < 2 ? lo & 0xffffu : lo;
+                }
+                if (t < ROWS_Q * DW_ROW && row0 + ROWS_Q * q < 3 * QPR) {
+                    uint32_t* d = dst + q * ROWS_Q * (MP_W / 2);
                     d[0] = lo;
                     d[1] = hi;
                 }
             }
-        } else {
-            const uint8_t* f = frames + (size_t)cur.img * 3 * H * W;
-            for (int i = t; i < 3 * QPR * MP_W; i += 256) {
-                const int c = i / (QPR * MP_W), r = i - c * (QPR * MP_W), py = r / MP_W, px = r - py * MP_W;
-                const int iy = cur.iy0 + py, ix = cur.ix0 + px;
-                bf16_t v = 0;
-                if ((unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)W) v = lut[f[((size_t)c * H + iy) * W + ix]];
-                patch[i] = v;
-            }
         }
         __syncthreads();
         const TileOrg nxt = tile_org(min(tile + (int)gridDim.x, total - 1));
-        if (dwords && tile + (int)gridDim.x < total) load_raw(nxt);
+        if (tile + (int)gridDim.x < total) load_raw(nxt);
 
         // Stem rows 0..2 of this wavefront give its first pooled row, rows 2..4 the second: rows 0..2 are
         // multiplied first, rows 3..4 after the first pooled row has left the registers (96 live accumulator
         // registers instead of 160).
-        sf32x16_t bias_t[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const f32x4_t q = *reinterpret_cast<const f32x4_t*>(sbias + i * 32 + 8 * v + 4 * g);   // LDS copy: no per-tile global wait
-                bias_t[i][4 * v] = q.x; bias_t[i][4 * v + 1] = q.y; bias_t[i][4 * v + 2] = q.z; bias_t[i][4 * v + 3] = q.w;
-            }
         const int sx0 = 2 * cur.px0 - 1, sy0 = 2 * cur.py0 - 1;
         unsigned char* ep = etile + wv * 32 * ME_PITCH;
         const bool colok = (unsigned)(sx0 + pxl) < (unsigned)Ws;
@@ -217,28 +219,39 @@ __global__ __launch_bounds__(256, 2) void stem_pool_mfma_kernel(const uint8_t* _
         auto mma_rows = [&](auto r0c, auto nrc) {
             constexpr int r0 = decltype(r0c)::value, nr = decltype(nrc)::value;
 #pragma unroll
-            for (int r = 0; r < nr; ++r)
+            for (int i = 0; i < 2; ++i)   // accumulators start from the bias
 #pragma unroll
-                for (int i = 0; i < 2; ++i) acc[r][i] = bias_t[i];   // accumulators start from the bias
-#pragma unroll 2
-            for (int s = 0; s < MK_ROWS / 2; ++s) {   // (a full unroll hoists every operand load and spills)
-                const int rr = 2 * s + g;
-                const int rq = rr < 21 ? rr : 0;
-                const int c = rq / 7, ky = rq - 7 * c;
-                u32x4_t fa[2];
+                for (int v = 0; v < 4; ++v) {
+                    const f32x4_t q = *reinterpret_cast<const f32x4_t*>(sbias + i * 32 + 8 * v + 4 * g);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const u32x4_t*>(wt + (i * 32 + pxl) * MW_PITCH + rr * 16);
+                    for (int r = 0; r < nr; ++r) { acc[r][i][4 * v] = q.x; acc[r][i][4 * v + 1] = q.y; acc[r][i][4 * v + 2] = q.z; acc[r][i][4 * v + 3] = q.w; }
+                }
+            // k-step s, this lane's half: row rr = 2 s + g of the 21 (channel rr / 7, filter row rr % 7; the 22nd has zero weights)
+            u32x4_t fb[2][nr];
+            auto read_step = [&](auto sc) {
+                constexpr int s = decltype(sc)::value, r1 = 2 * s + 1 < 21 ? 2 * s + 1 : 0;
+                constexpr int o0 = (2 * s / 7 * QPR + 2 * s % 7) * MP_W, o1 = (r1 / 7 * QPR + r1 % 7) * MP_W;
+                const bf16_t* at = patch + 8 * wv * MP_W + 2 * pxl + 2 + (g ? o1 : o0);
 #pragma unroll
                 for (int r = 0; r < nr; ++r) {
-                    const int row = 2 * (4 * wv + r0 + r) + ky;
-                    const uint32_t* src = reinterpret_cast<const uint32_t*>(patch + (c * QPR + row) * MP_W + 2 * pxl + 2);
-                    u32x4_t fb = {src[0], src[1], src[2], src[3]};
+                    const uint32_t* src = reinterpret_cast<const uint32_t*>(at + 2 * (r0 + r) * MP_W);
+                    fb[s & 1][r] = u32x4_t{src[0], src[1], src[2], src[3]};
+                }
+            };
+            // (the next step's pixels are read while this one's are multiplied; pinned, or all reads are hoisted and spill)
+            read_step(std::integral_constant<int, 0>{});
+            static_for<0, MK_ROWS / 2>([&](auto sc) {
+                constexpr int s = decltype(sc)::value;
+                if constexpr (s + 1 < MK_ROWS / 2) read_step(std::integral_constant<int, s + 1>{});
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < nr; ++r)
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
-                        acc[r][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sbf16x8_t, fa[i]),
-                                                                            __builtin_bit_cast(sbf16x8_t, fb), acc[r][i], 0, 0, 0);
-                }
-            }
+                        acc[r][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sbf16x8_t, wf[s][i]),
+                                                                            __builtin_bit_cast(sbf16x8_t, fb[s & 1][r]), acc[r][i], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            });
         };
         auto pooled_row = [&](int half, const bool rowok[3]) {
 #pragma unroll
