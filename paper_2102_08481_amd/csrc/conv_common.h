@@ -81,6 +81,16 @@ __device__ inline void store8(float* p, const float r[8]) {
     *reinterpret_cast<f32x4_t*>(p + 4) = hi;
 }
 
+// One bit per filter tap (ky kw + kx; kh kw <= 32) that lies inside the image, for the filter whose tap 0 is at (iy0, ix0).
+// every_row: a bit at ky kw for each ky < kh.
+__host__ __device__ inline uint32_t tap_mask(int iy0, int ix0, int H, int W, int kh, int kw, uint32_t every_row) {
+    const int x0 = ix0 < 0 ? (-ix0 < kw ? -ix0 : kw) : 0, x1 = W - ix0 < kw ? W - ix0 : kw;
+    const int y0 = iy0 < 0 ? (-iy0 < kh ? -iy0 : kh) : 0, y1 = H - iy0 < kh ? H - iy0 : kh;
+    if (x1 <= x0 || y1 <= y0) return 0u;
+    const uint32_t cols = (uint32_t)((1ull << x1) - (1ull << x0)), rows = (uint32_t)((1ull << (y1 * kw)) - (1ull << (y0 * kw)));
+    return cols * (every_row & rows);   // (the columns once per row: no carries)
+}
+
 // compile-time loop: the body sees the index as a constant (keeps accumulator indices static)
 template <int I, int N, typename F>
 __device__ inline void static_for(F&& f) {

@@ -94,7 +94,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     // that the larger operand, the weights, is read by one XCD only instead of by all eight)
     const int tiles_m = (M + BM - 1) / BM;
     const bool pixels_first = RING && M < a.Cout;
-    const int tile_n = pixels_first ? tile / tiles_m : tile % tiles_n, tile_m = pixels_first ? tile % tiles_m : tile / tiles_n;
+    const int slow = a.by_tiles(tile), fast = tile - slow * (pixels_first ? tiles_m : tiles_n);
+    const int tile_n = pixels_first ? slow : fast, tile_m = pixels_first ? fast : slow;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
     const T* __restrict__ in = static_cast<const T*>(a.in);
@@ -128,36 +129,16 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     long long b_off0[ONE ? 1 : PB];
     uint32_t b_taps[ONE ? 1 : PB];
     bool b_ok[PB];
-    // (image, row, column) of the thread's first tile row by division; its other rows are RPP pixels further on each and
-    // are reached by stepping (a few carries) unless the output rows are very short
-    int s_img, s_oy, s_ox;
-    {
-        const int m = m0 + lrow;
-        const int mm = m < M ? m : 0;
-        s_img = mm / HoWo;
-        const int rem = mm - s_img * HoWo;
-        s_oy = rem / a.Wo;
-        s_ox = rem - s_oy * a.Wo;
-    }
-    const bool step_rows = a.Wo >= 16;
+    uint32_t every_row = 0;
+    if constexpr (!ONE)
+        for (int ky = 0; ky < a.kh; ++ky) every_row |= 1u << (ky * a.kw);
 #pragma unroll
     for (int p = 0; p < PB; ++p) {
         const int m = m0 + lrow + RPP * p;
         b_ok[p] = m < M;
-        int img, oy, ox;
-        if (p == 0 || !b_ok[p]) {   // (rows beyond M are clamped to row 0: they only feed outputs that are never stored)
-            img = b_ok[p] ? s_img : 0; oy = b_ok[p] ? s_oy : 0; ox = b_ok[p] ? s_ox : 0;
-        } else if (step_rows) {
-            s_ox += RPP;
-            while (s_ox >= a.Wo) { s_ox -= a.Wo; ++s_oy; }
-            while (s_oy >= a.Ho) { s_oy -= a.Ho; ++s_img; }
-            img = s_img; oy = s_oy; ox = s_ox;
-        } else {
-            img = m / HoWo;
-            const int rem = m - img * HoWo;
-            oy = rem / a.Wo;
-            ox = rem - oy * a.Wo;
-        }
+        const int mm = b_ok[p] ? m : 0;   // (rows beyond M are clamped to row 0: they only feed outputs that are never stored)
+        const int img = a.by_hw(mm), rem = mm - img * HoWo;
+        const int oy = a.by_w(rem), ox = rem - oy * a.Wo;
         const int iy0 = oy * a.stride - a.pad, ix0 = ox * a.stride - a.pad;
         b_base[p] = (size_t)img * a.H * a.W * a.Cin + (size_t)lchunk * EPC;
         // 1x1, unpadded: the row's input pixel is fixed for the whole K loop
@@ -165,12 +146,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             b_base[p] += ((size_t)iy0 * a.W + ix0) * a.Cin;
         } else {
             b_off0[p] = (long long)b_base[p] + ((long long)iy0 * a.W + ix0) * a.Cin;
-            // tap (ky, kx) lies inside the image iff row iy0 + ky and column ix0 + kx do
-            uint32_t cols = 0;
-            for (int kx = 0; kx < a.kw; ++kx) cols |= ((unsigned)(ix0 + kx) < (unsigned)a.W) ? (1u << kx) : 0u;
-            uint32_t bits = 0;
-            for (int ky = 0; ky < a.kh; ++ky) bits |= ((unsigned)(iy0 + ky) < (unsigned)a.H) ? (cols << (ky * a.kw)) : 0u;
-            b_taps[p] = bits;
+            b_taps[p] = tap_mask(iy0, ix0, a.H, a.W, a.kh, a.kw, every_row);
         }
         if constexpr (DUAL)
             b_base2[p] = (((size_t)img * a.H2 + (size_t)oy * a.stride2) * a.W2 + (size_t)ox * a.stride2) * a.Cin2 + (size_t)lchunk * EPC;
@@ -791,7 +767,12 @@ bool conv_supported(const ConvArgs& a, int precision) {
 }
 
 template <typename T, int BM, int BN, int BKB, int WAVES_M, int WAVES_N, int MODE, typename OutT, int STAGES = 2, int PROD = 0, int U = 1>
-static hipError_t launch_cfg(const ConvArgs& a, hipStream_t s) {
+static hipError_t launch_cfg(const ConvArgs& args, hipStream_t s) {
+    ConvArgs a = args;
+    const int tiles_m = (int)(((long long)a.N * a.Ho * a.Wo + BM - 1) / BM), tiles_n = (a.Cout + BN - 1) / BN;
+    a.by_hw = FastDiv(a.Ho * a.Wo);
+    a.by_w = FastDiv(a.Wo);
+    a.by_tiles = FastDiv(PROD > 0 && (long long)a.N * a.Ho * a.Wo < a.Cout ? tiles_m : tiles_n);
     const size_t lds = (size_t)STAGES * (BN + BM) * (BKB == 128 ? BKB : BKB + 16);
     auto kern = conv_igemm_kernel<T, BM, BN, BKB, WAVES_M, WAVES_N, MODE, OutT, STAGES, PROD, U>;
     {

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
     const int per_xcd = (total_tiles + 7) >> 3;
     const int tile = (int)(blockIdx.x & 7u) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= total_tiles) return;
-    const int tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
+    const int tile_m = a.by_tiles(tile), tile_n = tile - tile_m * tiles_n;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
     // ---- bias: where the sums start
@@ -122,28 +122,26 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
         else return p < 2 ? p * 96 + r : (r < 32 ? 64 + r : 128 + r);
     };
     // offsets count from tap 0 of the pixel (0, 0) of the block's first image
-    const int img0 = m0 / HoWo;
+    const int img0 = a.by_hw(m0);
     const T* x_base = static_cast<const T*>(a.in) + (size_t)img0 * a.H * a.W * a.Cin - (size_t)(ONE ? 0 : a.pad * (a.W + 1)) * a.Cin;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(x_base), 0, 0x80000000, 0x00020000);
     const __amdgpu_buffer_rsrc_t rx2 = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(static_cast<const T*>(DUAL ? a.in2 : a.in) + (DUAL ? (size_t)img0 * a.H2 * a.W2 * a.Cin2 : 0)), 0, 0x80000000, 0x00020000);
     uint32_t x_off[PB], x_off2[DUAL ? PB : 1], x_taps[ONE ? 1 : PB];
+    uint32_t every_row = 0;
+    if constexpr (!ONE)
+        for (int ky = 0; ky < a.kh; ++ky) every_row |= 1u << (ky * a.kw);
 #pragma unroll
     for (int p = 0; p < PB; ++p) {
         const int m = m0 + x_row(p, q);
-        const int img = m / HoWo, rem = m - img * HoWo;
-        const int oy = rem / a.Wo, ox = rem - oy * a.Wo;
+        const int img = a.by_hw(m), rem = m - img * HoWo;
+        const int oy = a.by_w(rem), ox = rem - oy * a.Wo;
         const bool ok = m < M;
         x_off[p] = (uint32_t)((((img - img0) * a.H + oy * a.stride) * a.W + ox * a.stride) * a.Cin * 2 + chunk * 16);
         if constexpr (ONE) {
             x_off[p] = ok ? x_off[p] : OUTSIDE;
         } else {
-            // one bit per tap (kh * kw <= 32) that lies inside the image
-            const int iy0 = oy * a.stride - a.pad, ix0 = ox * a.stride - a.pad;
-            uint32_t cols = 0, bits = 0;
-            for (int kx = 0; kx < a.kw; ++kx) cols |= ((unsigned)(ix0 + kx) < (unsigned)a.W) ? (1u << kx) : 0u;
-            for (int ky = 0; ky < a.kh; ++ky) bits |= ((unsigned)(iy0 + ky) < (unsigned)a.H) ? (cols << (ky * a.kw)) : 0u;
-            x_taps[p] = ok ? bits : 0u;
+            x_taps[p] = ok ? tap_mask(oy * a.stride - a.pad, ox * a.stride - a.pad, a.H, a.W, a.kh, a.kw, every_row) : 0u;
         }
         if constexpr (DUAL)
             x_off2[p] = ok ? (uint32_t)((((img - img0) * a.H2 + oy * a.stride2) * a.W2 + ox * a.stride2) * a.Cin2 * 2 + chunk * 16) : OUTSIDE;
@@ -653,7 +651,11 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
 }
 
 template <int BM, int BN, int MODE>
-static hipError_t launch_large_cfg(const ConvArgs& a, hipStream_t s) {
+static hipError_t launch_large_cfg(const ConvArgs& args, hipStream_t s) {
+    ConvArgs a = args;
+    a.by_hw = FastDiv(a.Ho * a.Wo);
+    a.by_w = FastDiv(a.Wo);
+    a.by_tiles = FastDiv(a.Cout / BN);
     // two buffers of 256 rows per operand; the fused predictors park a padded 256 x 528-byte tile instead, the expansion tail an
     // unpadded 256 x 512-byte tile and 4 KB per wavefront beside it (the CU's whole LDS)
     const size_t lds = BN != 256 ? (size_t)3 * (BN + BM) * 128 : MODE == 4 ? (size_t)160 * 1024 : BM == 256 && MODE == 0 ? (size_t)256 * 528 : (size_t)128 * 1024;

@@ -55,6 +55,23 @@ __host__ __device__ inline float bf16_to_f32(bf16_t h) {
     return v.f;
 }
 
+// Division of a non-negative int by a divisor known at the launch: n / d = floor(n mul / 2^(32 + shift)) for n < 2^31, with
+// mul = floor(2^(31 + l) / d) + 1 and l = ceil(log2 d): mul d - 2^(31 + l) is in 1..d, so the product is too large by less than
+// 2^(31 + l) / d.  (The division of two registers is 30 to 40 instructions, at the start of every block of a layer kernel.)
+struct FastDiv {
+    uint32_t mul = 0;   // 0: divisor 1
+    int shift = 0;
+    FastDiv() = default;
+    explicit FastDiv(int d) {
+        if (d <= 1) return;
+        int l = 1;
+        while ((1ll << l) < d) ++l;
+        mul = (uint32_t)((1ull << (31 + l)) / (uint32_t)d + 1);
+        shift = l - 1;
+    }
+    __host__ __device__ int operator()(int n) const { return mul ? (int)((uint32_t)(((uint64_t)(uint32_t)n * mul) >> 32) >> shift) : n; }
+};
+
 // ---------------------------------------------------------------- convolution (implicit GEMM)
 // NHWC activations; weights [Cout][kh][kw][Cin] (K contiguous per output channel).
 // out[m, n] = act(bias[n] + sum_k W[n, k] * im2col(in)[m, k] + res[m, n]),  m = (img, oy, ox); every kernel that runs a layer
@@ -92,6 +109,7 @@ struct ConvArgs {
     const void* tail_res = nullptr;
     void* tail_out = nullptr;
     int tail_n = 0;
+    FastDiv by_hw, by_w, by_tiles;   // set at the launch: Ho Wo, Wo, and the tiles along the dimension that is walked first
 };
 // precision 0: float tensors, fp32 MFMA; 1: bf16 tensors, bf16 MFMA with fp32 accumulation.
 // out_f32: store float outputs even when tensors are bf16.  Returns hipSuccess or the launch error.

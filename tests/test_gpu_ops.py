@@ -81,6 +81,7 @@ def test_conv_op_matches_oracle(precision, case):
     dict(H=7, W=5, Cin=64, Cout=128, k=3, stride=1, pad=1),        # 3x3 borders, rows shorter than a tile
     dict(H=9, W=21, Cin=128, Cout=136, k=3, stride=2, pad=1),      # strided 3x3, ragged channels
     dict(H=9, W=21, Cin=128, Cout=256, k=3, stride=2, pad=1),      # strided 3x3 on the large tiles, images of 55 pixels
+    dict(H=6, W=9, Cin=64, Cout=128, k=5, stride=2, pad=3),        # 25 taps, padding wider than half the filter
 ])
 def test_conv_result_does_not_depend_on_the_tile(precision, case):
     """The tile a layer runs on is chosen by its number of pixels (32 x 32 or 32 x 64 up to 256 x 256).  Every tile adds in
@@ -243,7 +244,7 @@ def test_bottleneck_op_rejects_unsupported():
 
 
 @pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("size", [(70, 93), (64, 128), (131, 252), (33, 37)])
+@pytest.mark.parametrize("size", [(70, 93), (64, 128), (131, 252), (33, 37), (47, 66), (40, 99)])
 def test_stem_op_matches_oracle(precision, size):
     """Normalisation + 7x7 stem + ReLU + 3x3 max-pool (one kernel for bf16 models): odd and even sizes,
     widths that are and are not multiples of 4, several tiles with ragged right and bottom edges."""
