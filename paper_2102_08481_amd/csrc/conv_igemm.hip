@@ -55,12 +55,13 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     static_assert(RING ? STAGES % U == 0 && STAGES / U > 2 : U == 1, "the ring holds whole groups of tiles");
     static_assert(RING == (PROD > 0), "the ring is filled by loading wavefronts, the other paths have none");
     static_assert(!RING || DIRECT, "the ring holds direct-to-LDS tiles");
-    constexpr int KK = BKB / 32;               // MFMA k-steps per tile row (32 bytes = 2 lane halves x 16 bytes)
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wavefront tile (pixels x channels)
-    // F16 (fp32 ring): a wavefront owns one 16x16 tile instead, so that four times as many wavefronts share the work of a
-    // short call; the contraction takes its k in the order of the 32x32 tiles.
-    constexpr bool F16 = WM == 16 && WN == 16;
-    static_assert(!F16 || (std::is_same<T, float>::value && std::is_same<OutT, float>::value && STAGES > 2), "16x16 tiles: fp32 ring only");
+    // F16 (ring): a wavefront owns one 16x16 tile instead, so that four times as many wavefronts share the work of a short call; the
+    // contraction takes its k in the order of the 32x32 tiles (bf16: the 16x16x32 instruction adds its four groups of eight
+    // products one after the other, as two 32x32x16 do their two: the same bits).
+    constexpr bool F16 = WM == 16 && WN == 16, F32 = std::is_same<T, float>::value;
+    static_assert(!F16 || STAGES > 2, "16x16 tiles: ring only");
+    constexpr int KK = F16 && !F32 ? BKB / 64 : BKB / 32;   // MFMA k-steps per tile row (16 bytes for each of 4 lane groups, or 2 lane halves)
     constexpr int TM = F16 ? 1 : WM / 32, TN = F16 ? 1 : WN / 32;  // 32x32 MFMA tiles per wavefront
     constexpr int LPP = WN / 8;                // epilogue: lanes per pixel (8 channels each)
     constexpr int PPI = 64 / LPP;              // epilogue: pixels per wavefront instruction
@@ -281,7 +282,14 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     const T* __restrict__ res = static_cast<const T*>(a.res);
     Vec8<T> rres[PREFETCH_RES ? TM * NIT : 1];
     if (RING && multiplies) load_bias();   // (in front of the residual: the sums wait for the bias only)
-    if (PREFETCH_RES && multiplies && vec && res != nullptr) {  // residual tile: issued now, consumed after the K loop
+    struct alignas(4 * sizeof(T)) Quad { T v[4]; };
+    Quad rquad = {};                                     // F16: the residual of the lane's four channels
+    const bool quads = F16 && res != nullptr && (a.Cout & 3) == 0;
+    if (quads && multiplies) {
+        const int pix = m0 + wm * WM + (lane & 15), ch = n0 + wn * WN + 4 * (lane >> 4);
+        if (pix < M && ch < a.Cout) rquad = *reinterpret_cast<const Quad*>(res + (size_t)pix * a.Cout + ch);
+    }
+    if (!F16 && PREFETCH_RES && multiplies && vec && res != nullptr) {  // residual tile: issued now, consumed after the K loop
 #pragma unroll
         for (int j = 0; j < TM; ++j)
 #pragma unroll
@@ -296,6 +304,12 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     const int frag_swz = (frag_row & 7) ^ ((frag_row >> 3) & 1);
     struct Frags { u32x4_t a[TN], b[TM]; };
     auto read_frags = [&](int buf, int kk, Frags& f) {
+        if constexpr (F16) {
+            const int row = lane & 15, slot = ((4 * kk + (lane >> 4)) ^ (row & 7) ^ (row >> 3)) * 16;
+            f.a[0] = *reinterpret_cast<const u32x4_t*>(sA + (size_t)(buf * BN + wn * WN + row) * LDS_ROW + slot);
+            f.b[0] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + row) * LDS_ROW + slot);
+            return;
+        }
         const int koff = DIRECT ? ((2 * kk + (lane >> 5)) ^ frag_swz) * 16 : kk * 32 + frag_off;
 #pragma unroll
         for (int i = 0; i < TN; ++i)
@@ -305,10 +319,14 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             f.b[j] = *reinterpret_cast<const u32x4_t*>(sB + (size_t)(buf * BM + wm * WM + j * 32 + frag_row) * LDS_ROW + koff);
     };
     auto mma_frags = [&](const Frags& f) {
+        if constexpr (F16) {
+            acc4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f.a[0]), __builtin_bit_cast(bf16x8_t, f.b[0]), acc4, 0, 0, 0);
+        } else {
 #pragma unroll
-        for (int i = 0; i < TN; ++i)
+            for (int i = 0; i < TN; ++i)
 #pragma unroll
-            for (int j = 0; j < TM; ++j) mma_step<T>(acc[i][j], f.a[i], f.b[j]);
+                for (int j = 0; j < TM; ++j) mma_step<T>(acc[i][j], f.a[i], f.b[j]);
+        }
     };
     auto compute = [&](int buf) {
 #pragma unroll
@@ -413,7 +431,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             __builtin_amdgcn_s_waitcnt(0xc07f);                 // lgkmcnt(0)
         };
         int buf = 0;                                            // buffer of the group read last
-        if constexpr (F16) {
+        if constexpr (F16 && F32) {
             // The matrix instruction wants one k of four from each lane group: 0, 4, 1, 5 of a group of 8, then 2, 6, 3, 7 (the order of
             // the 32x32 tiles).  Lanes read 16 bytes instead, lanes 0..31 of k group 2 p and lanes 32..63 of 2 p + 1, and swap
             // halves in registers (4-byte reads conflict in the banks: 124 us against 115 at 200 x 1024, K 12544).  A product is 32
@@ -494,10 +512,14 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
             in_registers();
             barrier();                                          // group 0 has landed
             start_sums();
+            if constexpr (F16) {                                // (as above)
+                asm volatile("" : "+v"(acc4));
+            } else {
 #pragma unroll
-            for (int i = 0; i < TN; ++i)                        // (as above)
+                for (int i = 0; i < TN; ++i)
 #pragma unroll
-                for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(acc[i][j]));
+                    for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(acc[i][j]));
+            }
 #pragma unroll
             for (int i = 0; i < U * KK; ++i) read_frags(i / KK, i % KK, g0.k[i / KK][i % KK]);
             auto step = [&](int g, const TileFrags& now, TileFrags& next) {
@@ -531,15 +553,15 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         if constexpr (F16) {
             const int pix = m0 + wm * WM + (lane & 15), ch = n0 + wn * WN + 4 * (lane >> 4);
             if (pix >= M) return;
-            float* o0 = static_cast<float*>(a.out0);
-            float* o1 = static_cast<float*>(a.out1);
-            const float* r0 = static_cast<const float*>(a.res);
+            OutT* o0 = static_cast<OutT*>(a.out0);
+            OutT* o1 = static_cast<OutT*>(a.out1);
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const bool in_range = ch + e < a.Cout;
                 v[e] = acc4[e];
-                if (r0 && in_range) v[e] += r0[(size_t)pix * a.Cout + ch + e];
+                if (quads) v[e] += load_elem(&rquad.v[e]);
+                else if (res != nullptr && in_range) v[e] += load_elem(res + (size_t)pix * a.Cout + ch + e);
                 if (a.relu) v[e] = fmaxf(v[e], 0.f);
             }
             if (o1 == nullptr && (a.Cout & 3) == 0 && (a.ld0 & 3) == 0) {
@@ -548,8 +570,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int c = ch + e;
-                    if (c < a.n_split) { if (c < a.Cout) o0[(size_t)pix * a.ld0 + c] = v[e]; }
-                    else if (c < a.Cout) o1[(size_t)pix * a.ld1 + (c - a.n_split)] = v[e];
+                    if (c < a.n_split) { if (c < a.Cout) store_elem(o0 + (size_t)pix * a.ld0 + c, v[e]); }
+                    else if (c < a.Cout) store_elem(o1 + (size_t)pix * a.ld1 + (c - a.n_split), v[e]);
                 }
             }
             return;
@@ -824,11 +846,17 @@ static long long tile_rounds(const ConvArgs& a, int bm, int bn) {
 // one round only (256 channels: 8 160 pixels K 512 10.2 / 7.9, K 704 12.5 / 9.1; in two rounds, 8 500 pixels, K 512 10.2 / 11.6,
 // K 704 12.7 / 13.6), and 128 x 128 from K 768 (K 768 13.5 / 12.1, K 1024 16.8 / 13.9).  64 x 64 pays from K 256 in up to two rounds
 // (8 160 pixels, 256 channels, K 256 7.0 / 6.4, K 448 9.3 / 7.7).  Below K 256 the detectors have K 64 and 128 only, the streaming
-// tile's; at K 192 the small tiles would pay too (2 040 pixels, 256 channels 5.4 / 4.0).  Returns false if no ring tile pays.
+// tile's; at K 192 the small tiles would pay too (2 040 pixels, 256 channels 5.4 / 4.0).  Up to 256 tiles of 32 x 32 (four
+// wavefronts of one 16x16 tile, K tiles of 8 KB) that tile is the one that uses most CUs, 32 x 64 / 32 x 32: 510 pixels, 3x3 512 -> 512 14.9 /
+// 12.7, 2048 -> 256 6.6 / 5.7, 100 rows x 1024, K 12544 26.8 / 19.1, 500 x 512, K 384 3.7 / 3.9.  Returns false if no ring tile pays.
 static bool launch_ring_bf16(const ConvArgs& a, long long K, hipStream_t s, hipError_t* e) {
     if (K < 256 || a.out1 != nullptr) return false;
     const bool narrow = a.Cout <= 64;
     if (narrow ? tile_rounds(a, 64, 64) > 1 : tile_rounds(a, 128, 128) > 1) return false;
+    if (tile_rounds(a, 32, 32) == 1) {
+        *e = launch_one<bf16_t, 32, 32, 128, 2, 2, bf16_t, true, 16, 4, 4>(a, s);
+        return true;
+    }
     const long long c32 = 16 * tile_rounds(a, 32, 64), c64 = 24 * tile_rounds(a, 64, 64);
     const long long c64w = K >= 512 && !narrow && tile_rounds(a, 64, 128) == 1 ? 31 : 1000, c128 = K >= 768 && !narrow ? 49 : 1000;
     const long long best = c32 < c64 ? c32 : c64, wide = c64w < c128 ? c64w : c128;
@@ -864,10 +892,11 @@ static hipError_t launch_fp32(const ConvArgs& a, long long K, hipStream_t s) {
 }
 
 // fp32 outputs of bf16 tensors (the predictors, at most a few channel tiles wide): the general epilogue's time goes with the
-// tile.  Measured, 128-pixel tile / ring: 75 channels, K 256: 300 pixels 17.3 / 5.7 us (32 x 64), 16 320 17.5 / 8.2 and
+// tile.  Measured, 128-pixel tile / ring: 75 channels, K 256: 300 pixels 17.3 / 5.7 us (32 x 64), 510 pixels 32 x 64 / 32 x 32 4.5 / 3.6, 16 320 17.5 / 8.2 and
 // 32 640 18.3 / 14.2 (64 x 64); 55 channels, K 1024, 4 800 rows: 15.5 / 7.5.  Up to 64 channels the 128-pixel tile is no wider
 // than the ring's: 60 channels, K 256, 48 000 pixels 14.5 / 14.2, 64 800 15.7 / 17.5.
 static hipError_t launch_out_f32(const ConvArgs& a, hipStream_t s) {
+    if (tile_rounds(a, 32, 32) <= 1) return launch_one<bf16_t, 32, 32, 128, 2, 2, float, false, 16, 4, 4>(a, s);
     if (tile_rounds(a, 32, 64) <= 1) return launch_one<bf16_t, 32, 64, 128, 1, 2, float, false, 9, 4, 3>(a, s);
     if (tile_rounds(a, 64, 64) <= (a.Cout <= 64 ? 3 : 4)) return launch_one<bf16_t, 64, 64, 128, 2, 2, float, false, 5, 4>(a, s);
     return a.Cout <= 64 ? launch_one<bf16_t, 128, 64, 128, 2, 2, float>(a, s) : launch_one<bf16_t, 128, 128, 128, 2, 2, float>(a, s);

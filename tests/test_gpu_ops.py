@@ -118,6 +118,7 @@ def test_conv_result_does_not_depend_on_the_tile(precision, case):
     (0, 128, 75, 1, False, 8160, 9000),        # 64 x 64 ring | 32 x 32 ring (last round of the former nearly empty)
     (0, 128, 256, 1, False, 2040, 4080),       # 32 x 32 ring | 64 x 64 ring
     (1, 256, 55, 1, True, 48000, 52000),       # predictors: 64 x 64 ring | 128 x 64
+    (1, 1024, 256, 1, False, 1024, 1030),      # 32 x 32 ring (16x16x32 instructions) | 32 x 64
     (1, 512, 256, 1, False, 8160, 8500),       # 64 x 128 ring in one round | 192 x 128
     (1, 8192, 1024, 1, False, 300, 8200),      # 32 x 64 ring | 192 x 128
     (1, 64, 256, 3, False, 8160, 8520),        # 64 x 128 ring | 192 x 128, an odd number of K tiles
