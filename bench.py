@@ -309,7 +309,7 @@ def main():
     conv_launches = sum(prof[c][1] for c in CONV_CLASSES) / args.steps
     achieved = conv_flops_step / (conv_ms * 1e-3) / 1e12
     roofline = {
-        "kernel": "implicit-GEMM MFMA kernels: conv_igemm_kernel instantiations + bottleneck_fused kernels (backbone, lateral, RPN, FC)",
+        "kernel": "implicit-GEMM MFMA kernels: conv_igemm_kernel and conv_large_kernel instantiations + bottleneck_fused kernels (backbone, lateral, RPN, FC)",
         "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
         "traffic": None,   # filled below: bytes per launch from the committed --pmc runs
         "flops_per_step": conv_flops_step, "launches_per_step": conv_launches, "avg_launch_us": 1e3 * conv_ms / max(conv_launches, 1),

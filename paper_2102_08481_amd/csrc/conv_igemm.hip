@@ -337,13 +337,9 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         }
     };
 
-    // Software pipeline: while tile kt is multiplied out of LDS buffer kt&1, the loads of tile kt+1 are
-    // in flight into registers; they are written to the other buffer at the end of the step.  (A second
-    // register stage was measured: it costs the second resident block per CU and is slower.  Cycle stamps on
-    // the 256 x 256 tile: of ~4700 cycles per step ~1800 go to issuing the 8 loads per thread - the CU's one
-    // address unit takes ~20 cycles per 1 KiB instruction and a wavefront issues in order - but spreading the
-    // loads between the MFMAs of the step, pinned with scheduling barriers, was measured 3-8 % slower, also
-    // with the two wavefronts of a SIMD taking turns.)
+    // Software pipeline of the staged path: while tile kt is multiplied out of LDS buffer kt & 1, the loads of tile kt + 1 are in
+    // flight into registers; they are written to the other buffer at the end of the step.  (A second register stage costs the
+    // second resident block per CU and is slower.)
     if constexpr (RING) {
         // Ring of STAGES operand tiles, STAGES - 1 of them requested ahead: a call with few pixels has no more than one or
         // two blocks per CU, so the time of a K step is the latency of its operands (0.65 us from L2 with one tile in
@@ -837,8 +833,8 @@ static long long tile_rounds(const ConvArgs& a, int bm, int bn) {
 
 // Calls with few pixels.  A 128 x 128 tile takes 0.64 us per K step (64 bf16 / 32 fp32 of every row) however few blocks
 // there are, because a block waits for the one tile it has in flight; the ring tiles take, per K step and round of 256
-// blocks: 32 x 64 0.16 us, 64 x 64 0.24, 64 x 128 0.31, 128 x 128 0.49 (measured at K 12544).  The rule takes the
-// cheapest by that count.  Measured in us, two-buffer tile / ring tile: 300 x 1024, K 12544: 128 / 32 (32 x 64);
+// blocks: 32 x 64 0.16 us, 64 x 64 0.24, 64 x 128 0.31, 128 x 128 0.49 (measured at K 12544; 0.13, 0.20, 0.28, 0.49 since reads
+// stand between the products, which gives the same order from K 1024 on).  The rule takes the cheapest by the first count.  Measured in us, two-buffer tile / ring tile: 300 x 1024, K 12544: 128 / 32 (32 x 64);
 // 900: 212 / 47 (64 x 64); 1500: 212 / 67 (64 x 128); 2400: 212 / 98 (128 x 128); 3x3 256 -> 256: 2 040 pixels
 // 24.6 / 10.8, 8 160 26 / 17.5; 3x3 512 -> 512: 510 pixels 45 / 17.4, 4 080 55 / 30, 8 160 60 / 47.  More than 256 tiles
 // of 128 x 128 run two blocks per CU and overlap each other: no ring tile is faster there.  The count holds for long K; for
