@@ -6,7 +6,7 @@
 // n = output channel and k = (ky, kx, ci); activations are NHWC so a K tile of one
 // filter tap is a contiguous run of input channels of one input pixel.
 //
-// Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.hip, chosen
+// Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.h, chosen
 // by the layer's size in launch_conv) and walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Operand tiles go from
 // global memory straight into LDS, two buffers requested by the multiplying wavefronts or, in calls with few pixels, a ring
 // of 3 to 8 filled by wavefronts of its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
@@ -756,7 +756,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     }
 }
 
-// Whether a layer gets the 256 x 256 bf16 tile of conv_large.hip for the sake of what that alone can fuse (predictors).
+// Whether a layer gets the 256 x 256 bf16 tile of conv_large.h for the sake of what that alone can fuse (predictors).
 static bool takes_large_tile(const ConvArgs& a) {
     const long long M = (long long)a.N * a.Ho * a.Wo;
     const long long K = (long long)a.kh * a.kw * a.Cin;
@@ -954,3 +954,6 @@ hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream
 }
 
 }  // namespace thia
+
+// The kernel of the large tiles: part of this translation unit, so that whoever links the layer kernels needs one object.
+#include "conv_large.h"

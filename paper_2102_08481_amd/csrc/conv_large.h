@@ -30,6 +30,7 @@
 // library product of the same size: 1 069), at exit 2 328 -> 261, 3x3 256 -> 256 + expansion 149 -> 131, 1024 -> 256 39 -> 33, first
 // FC layer (192 x 256) 291 -> 207.  A K tile takes 1.0 us while a third of the CUs work and 1.38 when all do: the chip's clock
 // comes down under matrix work.
+#pragma once
 #include "conv_common.h"
 
 namespace thia {
