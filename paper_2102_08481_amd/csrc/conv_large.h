@@ -217,6 +217,7 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
 #pragma unroll
             for (int j = 0; j < (h == 0 ? 2 : TM1); ++j) mma_step<T>(acc[g][2 * h + j], wf[g][kk], xf[j][kk]);
     };
+    // waits for nothing but the other wavefronts: LDS accesses that others depend on are waited for (lgkmcnt) in front of it
     auto barrier = [&]() {
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
@@ -476,6 +477,7 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int it = 0; it < 2; ++it) rq[j][it] = fetch_res(0, 0, j, it);
+        wait(std::integral_constant<int, 63>{});   // the wavefront's part of the tile is in LDS (the loads stay on their way)
         barrier();
         unsigned char* R = smem + 256 * 512 + wv * 4096;
         // pixel operand of the tail's MFMAs: row hp * 128 + j * 32 + frag_row, logical chunk 2 ks + lane / 32; the rows of one
