@@ -91,6 +91,10 @@ __host__ __device__ inline uint32_t tap_mask(int iy0, int ix0, int H, int W, int
     return cols * (every_row & rows);   // (the columns once per row: no carries)
 }
 
+// Large tiles: the row of a block's first image from which the offsets of its input pixels count, oy0 being its first output row.
+// (The first filter's row, before padding; with wide padding it may lie below the image, in front of which the next one begins.)
+__host__ __device__ inline int large_first_row(int oy0, int stride, int H) { return oy0 * stride < H ? oy0 * stride : H; }
+
 // compile-time loop: the body sees the index as a constant (keeps accumulator indices static)
 template <int I, int N, typename F>
 __device__ inline void static_for(F&& f) {

@@ -122,12 +122,13 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
         else if constexpr (BM == 256) return (p & 1) * 128 + (p >> 1) * 64 + r;
         else return p < 2 ? p * 96 + r : (r < 32 ? 64 + r : 128 + r);
     };
-    // offsets count from tap 0 of the pixel (0, 0) of the block's first image
-    const int img0 = a.by_hw(m0);
-    const T* x_base = static_cast<const T*>(a.in) + (size_t)img0 * a.H * a.W * a.Cin - (size_t)(ONE ? 0 : a.pad * (a.W + 1)) * a.Cin;
+    // offsets count from tap 0 of the first pixel of the block's first row (large_first_row), so that they have 31 bits whatever the
+    // size of an image
+    const int img0 = a.by_hw(m0), oy0 = a.by_w(m0 - img0 * HoWo), row0 = large_first_row(oy0, a.stride, a.H);
+    const T* x_base = static_cast<const T*>(a.in) + (((long long)img0 * a.H + row0) * a.W - (ONE ? 0 : (long long)a.pad * (a.W + 1))) * a.Cin;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(x_base), 0, 0x80000000, 0x00020000);
     const __amdgpu_buffer_rsrc_t rx2 = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T*>(static_cast<const T*>(DUAL ? a.in2 : a.in) + (DUAL ? (size_t)img0 * a.H2 * a.W2 * a.Cin2 : 0)), 0, 0x80000000, 0x00020000);
+        const_cast<T*>(static_cast<const T*>(DUAL ? a.in2 : a.in) + (DUAL ? ((long long)img0 * a.H2 + oy0 * a.stride2) * a.W2 * a.Cin2 : 0)), 0, 0x80000000, 0x00020000);
     uint32_t x_off[PB], x_off2[DUAL ? PB : 1], x_taps[ONE ? 1 : PB];
     uint32_t every_row = 0;
     if constexpr (!ONE)
@@ -138,14 +139,14 @@ __global__ __launch_bounds__(512, 1) void conv_large_kernel(const ConvArgs a) {
         const int img = a.by_hw(m), rem = m - img * HoWo;
         const int oy = a.by_w(rem), ox = rem - oy * a.Wo;
         const bool ok = m < M;
-        x_off[p] = (uint32_t)((((img - img0) * a.H + oy * a.stride) * a.W + ox * a.stride) * a.Cin * 2 + chunk * 16);
+        x_off[p] = (uint32_t)((((img - img0) * a.H + oy * a.stride - row0) * a.W + ox * a.stride) * a.Cin * 2 + chunk * 16);
         if constexpr (ONE) {
             x_off[p] = ok ? x_off[p] : OUTSIDE;
         } else {
             x_taps[p] = ok ? tap_mask(oy * a.stride - a.pad, ox * a.stride - a.pad, a.H, a.W, a.kh, a.kw, every_row) : 0u;
         }
         if constexpr (DUAL)
-            x_off2[p] = ok ? (uint32_t)((((img - img0) * a.H2 + oy * a.stride2) * a.W2 + ox * a.stride2) * a.Cin2 * 2 + chunk * 16) : OUTSIDE;
+            x_off2[p] = ok ? (uint32_t)((((img - img0) * a.H2 + (oy - oy0) * a.stride2) * a.W2 + ox * a.stride2) * a.Cin2 * 2 + chunk * 16) : OUTSIDE;
     }
     const uint32_t x_dst = lds0 + XOFF;
     const int cin_tiles = a.Cin / BK;   // K tiles of a tap, or of the first source
@@ -673,15 +674,23 @@ static hipError_t launch_large_cfg(const ConvArgs& args, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Bytes of the source [H][W][Cin] from where a block's offsets count (large_first_row) to the end of what its pixels' taps reach.
+// bm pixels lie in at most `down` + 1 output rows: from the first on, `stride` input rows for each, at the end of an image also the rows that
+// no filter starts in, and the rows by which the first filter may start below its image.
+static long long large_span(const ConvArgs& a, int bm, int stride, int H, int W, int Cin) {
+    const long long down = (bm - 1 + a.Wo - 1) / a.Wo, images = (down + a.Ho - 1) / a.Ho;
+    const long long unused = H - (long long)a.Ho * stride, below = (a.Ho - 1ll) * stride - H;
+    const long long rows = down * stride + (unused > 0 ? images * unused : 0) + (below > 0 ? below : 0) + a.kh - 1;
+    return (rows * W + W + a.pad) * Cin * 2;
+}
+
 bool conv_large_supported(const ConvArgs& a, int precision, int bm, int bn) {
     if (precision != 1 || !conv_supported(a, precision) || a.Cout % bn != 0 || a.out1 != nullptr || (a.ld0 & 7) != 0) return false;
     const long long K = (long long)a.kh * a.kw * a.Cin + (a.in2 ? a.Cin2 : 0);
     if (K < 128) return false;   // the loops have two K tiles under way
-    // byte offsets within a block have 31 bits: of its weight rows, and of the images its pixels lie in
-    const long long images = (bm - 1) / ((long long)a.Ho * a.Wo) + 2, limit = 1ll << 31;
-    if (bn * K * 2 >= limit) return false;
-    if ((images * a.H * a.W + (long long)(a.kh + 1) * (a.W + a.kw)) * a.Cin * 2 >= limit) return false;
-    return a.in2 == nullptr || images * a.H2 * a.W2 * a.Cin2 * 2 < limit;
+    // byte offsets within a block have 31 bits: of its weight rows, and of the input rows that its pixels read
+    if (bn * K * 2 >= 1ll << 31 || large_span(a, bm, a.stride, a.H, a.W, a.Cin) >= 1ll << 31) return false;
+    return a.in2 == nullptr || large_span(a, bm, a.stride2, a.H2, a.W2, a.Cin2) < 1ll << 31;
 }
 
 template <int BM, int BN>

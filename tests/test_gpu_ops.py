@@ -143,6 +143,23 @@ def test_layers_on_either_side_of_the_tile_rules(precision, Cin, Cout, k, out_f3
     assert torch.isfinite(c.float()).all() and torch.equal(a[:, :rows], c[:, :rows])
 
 
+def test_maps_of_more_than_31_bits_of_bytes():
+    """A map of 2.2 GB on the large tiles, whose offsets have 32 bits: bands of it alone give the same values bit for bit."""
+    m, _ = _model(1)
+    rs = np.random.RandomState(21)
+    w = (rs.randn(128, 64, 3, 3) * np.sqrt(2.0 / 576)).astype(np.float32)
+    b = rs.randn(128).astype(np.float32) * 0.1
+    H, W, band = 8300, 2048, 40
+    assert H * W * 128 > 2 ** 31
+    x = torch.randn(1, H, W, 64, generator=torch.Generator(device="cuda").manual_seed(21), device="cuda", dtype=torch.bfloat16)
+    y = m.op_conv(x, w, b, pad=1)
+    for y0 in (0, H // 2, H - band):
+        part = m.op_conv(x[:, y0:y0 + band].contiguous(), w, b, pad=1)
+        torch.cuda.synchronize()
+        r0, r1 = (0 if y0 == 0 else 1), (band if y0 == H - band else band - 1)   # (rows whose neighbours the band has)
+        assert float(part.abs().max()) > 0 and torch.equal(part[:, r0:r1], y[:, y0 + r0:y0 + r1]), y0
+
+
 def test_bf16_output_rounding_is_nearest_even_bit_exact():
     """The kernels round fp32 results to bf16 with the hardware conversion; the oracle with integer
     arithmetic.  A convolution with zero weights returns round(bias): ties both ways, values next to
