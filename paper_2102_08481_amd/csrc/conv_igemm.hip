@@ -906,7 +906,10 @@ static hipError_t launch_out_f32(const ConvArgs& a, hipStream_t s) {
 // 512 -> 512: 16 320 pixels 90 / 81 / 72 / 105 / 94, 12 544 80 / 69 / 62 / 98 / 85, 50 176 192 / 234 / 243 / 261 / 247; 3x3 256 -> 256:
 // 32 640 49 / 44 / 38 / 58 / 49, 130 560 123 / 141 / 146 / 185 / 147; 3x3 128 -> 128, 802 816: - / - / 273 / 306 / 307.  Below K 512 a launch is
 // mostly epilogue (256 -> 1024 channels with a residual, 32 640 pixels: 40 / 41 / 44 / 46 / 38), which the two resident blocks of
-// 128 x 128 overlap with each other's K loop, except with a second source, where 200 tiles pay from K 384 on.
+// 128 x 128 overlap with each other's K loop, except with a second source, where 200 tiles pay from K 384 on.  Up to K 704 the
+// 128 x 128 tile's smaller set-up and epilogue also win where one round of it holds the layer (512 -> 256, 11 468 pixels 7.5 against 7.8
+// on 192 x 128; 512 -> 2048 with a residual, 2 007 pixels 8.5 / 9.5; 3x3 64 -> 128, 27 840 pixels 9.6 / 10.2; K 704 to 512 channels, 5 734
+// pixels 8.8 / 9.0), from K 768 on no longer (10.2 / 9.7); in two rounds it does not (3x3 64 -> 128, 36 000 pixels 13.6 / 10.5).
 static bool launch_large_bf16(const ConvArgs& a, long long K, hipStream_t s, hipError_t* e) {
     const struct { int bm, bn, step, fixed; } tiles[4] = {{256, 256, 138, 900}, {192, 256, 106, 800}, {256, 128, 84, 700}, {192, 128, 64, 600}};
     const long long M = (long long)a.N * a.Ho * a.Wo, KT = K / 64;
@@ -915,6 +918,7 @@ static bool launch_large_bf16(const ConvArgs& a, long long K, hipStream_t s, hip
         *e = launch_conv_large(a, 256, 256, s);
         return true;
     }
+    if (K < 768 && tile_rounds(a, 128, 128) <= 1) return false;
     long long best = 0;
     int pick = -1;
     for (int i = 0; i < 4; ++i) {

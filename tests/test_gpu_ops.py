@@ -119,9 +119,13 @@ def test_conv_result_does_not_depend_on_the_tile(precision, case):
     (0, 128, 256, 1, False, 2040, 4080),       # 32 x 32 ring | 64 x 64 ring
     (1, 256, 55, 1, True, 48000, 52000),       # predictors: 64 x 64 ring | 128 x 64
     (1, 1024, 256, 1, False, 1024, 1030),      # 32 x 32 ring (16x16x32 instructions) | 32 x 64
-    (1, 512, 256, 1, False, 8160, 8500),       # 64 x 128 ring in one round | 192 x 128
-    (1, 8192, 1024, 1, False, 300, 8200),      # 32 x 64 ring | 192 x 128
-    (1, 64, 256, 3, False, 8160, 8520),        # 64 x 128 ring | 192 x 128, an odd number of K tiles
+    (1, 512, 256, 1, False, 8160, 8500),       # 64 x 128 ring in one round | 128 x 128 in one round
+    (1, 512, 256, 1, False, 16384, 16400),     # 128 x 128 in one round | 192 x 128
+    (1, 768, 256, 1, False, 16384, 16400),     # 128 x 128 ring | 192 x 128
+    (1, 8192, 1024, 1, False, 300, 8200),      # 32 x 64 ring | 192 x 256
+    (1, 8192, 1024, 1, False, 300, 4200),      # | 192 x 128, long K
+    (1, 64, 256, 3, False, 8160, 8520),        # 64 x 128 ring | 128 x 128, an odd number of K tiles
+    (1, 64, 256, 3, False, 16320, 16560),      # 128 x 128 in one round | 192 x 128
     (1, 64, 256, 3, False, 8520, 25320),       # | 256 x 128
     (1, 64, 256, 3, False, 25320, 33000),      # | 192 x 256
     (1, 64, 256, 3, False, 33000, 50040),      # | 256 x 256
