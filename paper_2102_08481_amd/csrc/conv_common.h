@@ -1,4 +1,4 @@
-// Element, fragment and matrix-instruction helpers shared by the layer kernels (conv_igemm.hip, conv_large.h).
+// Element, fragment and matrix-instruction helpers shared by the layer kernels (conv_igemm.hip, conv_large.inc).
 #pragma once
 #include <type_traits>
 

@@ -6,7 +6,7 @@
 // n = output channel and k = (ky, kx, ci); activations are NHWC so a K tile of one
 // filter tap is a contiguous run of input channels of one input pixel.
 //
-// Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.h, chosen
+// Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.inc, chosen
 // by the layer's size in launch_conv) and walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Operand tiles go from
 // global memory straight into LDS, two buffers requested by the multiplying wavefronts or, in calls with few pixels, a ring
 // of 3 to 8 filled by wavefronts of its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
@@ -67,7 +67,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     constexpr int PPI = 64 / LPP;              // epilogue: pixels per wavefront instruction
     constexpr int NIT = 32 / PPI;              // epilogue: instructions per 32-pixel sub-tile
     constexpr int EPITCH = WN * 4 + 16;        // epilogue: padded fp32 row pitch in LDS (bytes)
-    constexpr bool PREFETCH_RES = TM * NIT <= 8;  // residual tile small enough to hold across the K loop
+    static_assert(TM * NIT <= 8, "the residual tile is held across the K loop");
+    static_assert(DIRECT || !DUAL, "the staged path has one source");
     static_assert(WAVES_M * WAVES_N * 32 * EPITCH <= STAGES * (BN + BM) * LDS_ROW, "epilogue tile must fit in the pipeline buffers");
     static_assert(!DIRECT || (CPR == 8 && (NT / 64) % 2 == 0), "direct loads: 8 chunks per row, an even number of wavefronts");
     static_assert(BM % RPP == 0 && BN % RPP == 0, "tile rows must be a multiple of the rows staged per pass");
@@ -164,15 +165,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         // never stored), padded filter taps are fetched from a valid in-image address and zeroed at the LDS write.
         st.zmask = 0;
         if constexpr (ONE) {
-            const int kt1 = a.Cin / BK;  // K tiles of the first source
-            if (!DUAL || kt < kt1) {
 #pragma unroll
-                for (int p = 0; p < PB; ++p) st.b[p] = *reinterpret_cast<const u32x4_t*>(in + b_base[p] + (size_t)kt * BK);
-            } else {
-#pragma unroll
-                for (int p = 0; p < PB; ++p)
-                    st.b[p] = *reinterpret_cast<const u32x4_t*>(in2 + b_base2[DUAL ? p : 0] + (size_t)(kt - kt1) * BK);
-            }
+            for (int p = 0; p < PB; ++p) st.b[p] = *reinterpret_cast<const u32x4_t*>(in + b_base[p] + (size_t)kt * BK);
 #pragma unroll
             for (int p = 0; p < PA; ++p) st.a[p] = *reinterpret_cast<const u32x4_t*>(wgt + a_base[p] + (size_t)kt * BK);
             return;
@@ -280,7 +274,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     // 8-channel-per-lane epilogue needs Cout, ld0 multiples of 8 and one dense output
     const bool vec = (a.out1 == nullptr) && ((a.Cout & 7) == 0) && ((a.ld0 & 7) == 0);
     const T* __restrict__ res = static_cast<const T*>(a.res);
-    Vec8<T> rres[PREFETCH_RES ? TM * NIT : 1];
+    Vec8<T> rres[TM * NIT];
     if (RING && multiplies) load_bias();   // (in front of the residual: the sums wait for the bias only)
     struct alignas(4 * sizeof(T)) Quad { T v[4]; };
     Quad rquad = {};                                     // F16: the residual of the lane's four channels
@@ -289,13 +283,13 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         const int pix = m0 + wm * WM + (lane & 15), ch = n0 + wn * WN + 4 * (lane >> 4);
         if (pix < M && ch < a.Cout) rquad = *reinterpret_cast<const Quad*>(res + (size_t)pix * a.Cout + ch);
     }
-    if (!F16 && PREFETCH_RES && multiplies && vec && res != nullptr) {  // residual tile: issued now, consumed after the K loop
+    if (!F16 && multiplies && vec && res != nullptr) {  // residual tile: issued now, consumed after the K loop
 #pragma unroll
         for (int j = 0; j < TM; ++j)
 #pragma unroll
             for (int it = 0; it < NIT; ++it) {
                 const int pix = m0 + wm * WM + j * 32 + it * PPI + lane / LPP, ch = n0 + wn * WN + (lane % LPP) * 8;
-                if (pix < M && ch < a.Cout) rres[PREFETCH_RES ? j * NIT + it : 0] = *reinterpret_cast<const Vec8<T>*>(res + (size_t)pix * a.Cout + ch);
+                if (pix < M && ch < a.Cout) rres[j * NIT + it] = *reinterpret_cast<const Vec8<T>*>(res + (size_t)pix * a.Cout + ch);
             }
     }
 
@@ -608,26 +602,16 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     start_sums();
     __syncthreads();
     // The requests for tile kt + 2 go out right after the LDS write of tile kt + 1 has freed the staging
-    // registers, so the data has a whole step to arrive.  With 8 wavefronts the two that share a SIMD (w and
-    // w + 4) do this staging at opposite ends of the step - one before its MFMAs, one after - so that one of them
-    // multiplies while the other writes LDS and queues at the CU's address unit (issued by all wavefronts at
-    // once right after the barrier, the loads cost ~1300 of ~4100 cycles per step with the matrix pipe idle).
-    const bool stage_first = NT == 512 && (wv >> 2) == 1;
+    // registers, so the data has a whole step to arrive.
     for (int kt = 0; kt < KT; ++kt) {
         const int buf = kt & 1;
-        if (stage_first) {
-            if (kt + 1 < KT) store_tiles(buf ^ 1, st0);
-            if (kt + 2 < KT) load_tiles(kt + 2, st0);
-        }
         // the wavefront that multiplies wins issue arbitration over the SIMD's other wavefront, which is staging
         // (LDS writes, global loads) at that moment: measured 0.5-1 % on the whole sweep
         __builtin_amdgcn_s_setprio(3);
         compute(buf);
         __builtin_amdgcn_s_setprio(0);
-        if (!stage_first) {
-            if (kt + 1 < KT) store_tiles(buf ^ 1, st0);
-            if (kt + 2 < KT) load_tiles(kt + 2, st0);
-        }
+        if (kt + 1 < KT) store_tiles(buf ^ 1, st0);
+        if (kt + 2 < KT) load_tiles(kt + 2, st0);
         __syncthreads();
     }
     }
@@ -673,20 +657,8 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
                 return;
             }
         }
-        // residual tiles that were not held across the K loop are fetched one sub-tile ahead of their use
-        Vec8<T> rq0[NIT], rq1[NIT];
-        auto fetch_res = [&](int j, Vec8<T>* dst) {
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                const int pix = m0 + wm * WM + j * 32 + it * PPI + lane / LPP, ch = n0 + wn * WN + (lane % LPP) * 8;
-                if (pix < M && ch < a.Cout) dst[it] = *reinterpret_cast<const Vec8<T>*>(res + (size_t)pix * a.Cout + ch);
-            }
-        };
-        if (!PREFETCH_RES && res != nullptr) fetch_res(0, rq0);
         static_for<0, TM>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            Vec8<T>* rnow = (j & 1) ? rq1 : rq0;
-            if (!PREFETCH_RES && res != nullptr && j + 1 < TM) fetch_res(j + 1, (j & 1) ? rq0 : rq1);
 #pragma unroll
             for (int i = 0; i < TN; ++i)
 #pragma unroll
@@ -707,8 +679,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
                 float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                 if (res) {
                     float q[8];
-                    if (PREFETCH_RES) unpack8(rres[PREFETCH_RES ? j * NIT + it : 0], q);
-                    else unpack8(rnow[it], q);
+                    unpack8(rres[j * NIT + it], q);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) r[e] += q[e];
                 }
@@ -756,7 +727,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     }
 }
 
-// Whether a layer gets the 256 x 256 bf16 tile of conv_large.h for the sake of what that alone can fuse (predictors).
+// Whether a layer gets the 256 x 256 bf16 tile of conv_large.inc for the sake of what that alone can fuse (predictors).
 static bool takes_large_tile(const ConvArgs& a) {
     const long long M = (long long)a.N * a.Ho * a.Wo;
     const long long K = (long long)a.kh * a.kw * a.Cin;
@@ -960,4 +931,4 @@ hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream
 }  // namespace thia
 
 // The kernel of the large tiles: part of this translation unit, so that whoever links the layer kernels needs one object.
-#include "conv_large.h"
+#include "conv_large.inc"
