@@ -476,6 +476,33 @@ def test_results_do_not_depend_on_the_microbatch(ep):
         m.set_microbatch(0)
 
 
+@pytest.mark.parametrize("n", [
+    100,   # 5 600 positions of the 256-wide stage: its first block's last 1x1 and shortcut, 768 values of K, on 192 x 128 tiles
+    140,   # 7 840: 256 x 128
+    200,   # 11 200: 192 x 256
+    256,   # 14 336: 256 x 256
+])
+def test_last_1x1_with_shortcut_on_every_large_tile(n):
+    """The contraction over two sources, on each of the large tiles against the small tiles of three frames at a time: the exit
+    tensor and the detections are the same bit for bit."""
+    m, _ = biased_model(BIASED, 0xBEEF + 57)
+    frames = to_dev(make_frames(SceneSpec(112, 128, n, 2, 4, 8, 40), 50))
+    m.set_debug(True)
+    try:
+        res = []
+        for mb in (n, 3):
+            m.set_microbatch(mb)
+            out = m.detect_chunk(frames, 3)
+            torch.cuda.synchronize()
+            res.append((m.tap("feat"), out))
+        assert np.isfinite(res[0][0]).all() and np.abs(res[0][0]).max() > 0
+        assert np.array_equal(res[0][0], res[1][0]), int((res[0][0] != res[1][0]).sum())
+        _same(res[0][1], res[1][1], n)
+    finally:
+        m.set_microbatch(0)
+        m.set_debug(False)
+
+
 def test_plans_and_all_exits_equal_calls_with_biases():
     """Chunks of one frame that share a micro-batch in a plan, and every exit of one backbone pass (where exit 1's lateral is a
     launch of its own and not its stage's last block), against stand-alone calls: same bits, biases not zero."""
