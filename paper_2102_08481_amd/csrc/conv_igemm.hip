@@ -9,7 +9,7 @@
 // Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.inc, chosen
 // by the layer's size in launch_conv) and walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Operand tiles go from
 // global memory straight into LDS, two buffers requested by the multiplying wavefronts or, in calls with few pixels, a ring
-// of 3 to 8 filled by wavefronts of its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
+// of 4 to 16 filled by wavefronts of its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
 // the tile as 32x32 MFMA tiles.  The weights are the MFMA "A" operand (rows = channels) and the activations the
 // "B" operand (columns = pixels): each lane then holds 4 consecutive channels of one
 // pixel per accumulator quad, which is the contiguous direction of the NHWC output.
@@ -339,12 +339,14 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
         // two blocks per CU, so the time of a K step is the latency of its operands (0.65 us from L2 with one tile in
         // flight) unless several tiles are in flight.  The order of the sums is the two-buffer loop's: same values bit for bit.
         // PROD wavefronts do nothing but request tiles: issued by the multiplying wavefronts the requests stand in line with
-        // their fragment reads and products (300 x 1024, K 12544: 128 us with two buffers, 60 with the ring, 39 / 32 with two /
-        // four loading wavefronts; the ring's depth beyond 4 changes nothing).
+        // their fragment reads and products (300 x 1024, K 12544, before groups and with the reads in front of the products: 128 us
+        // with two buffers, 60 with the ring, 39 / 32 with two / four loading wavefronts; the ring's depth beyond 4 changes nothing).
         // U tiles (a group) are handed over per barrier: a step is one barrier, one round trip of the fragment reads and the products
-        // of a group, of which only the products grow with U (32 x 64, U 1 / 3: 300 x 1024, K 12544 36.4 / 31.5 us, 3x3 512 -> 512 at
-        // 510 pixels 16.2 / 14.5; 64 x 64, U 1 / 2: 900 rows 45.2 / 40.6; fp32 32 x 32, U 1 / 2: 200 x 1024, K 12544 119.7 / 115.1; all but the
-        // second before the reads stood between the products).  Larger groups need larger rings: where two blocks share a CU U is 1.
+        // of a group, of which only the products grow with U.  U 1 / U, K 12544 to 1024 channels: 32 x 32, U 4, 100 rows 33.0 / 19.1 us;
+        // 32 x 64, U 3, 300 rows 35.4 / 27.7; 64 x 64, U 2, 900 rows 46.2 / 40.1; 64 x 128, U 2, 1500 rows 62.0 / 54.7; fp32 32 x 32, U 2, 200 rows
+        // 102.4 / 95.0; fp32 64 x 64, U 2, 600 rows 237 / 217.  Larger groups need larger rings: where two blocks share a CU U is 1.
+        // A layer of one or two groups gains nothing: up to K 320 (fp32: 128) it takes 0.1 to 0.2 us longer than with the shorter
+        // loop before (256 -> 75, 3 136 pixels 4.6 / 4.4; fp32 64 -> 64, 2 352 pixels 3.6 / 3.4).
         // Step g: the fragments of group g are in registers; group g + 1 is waited for (the newest STAGES / U - 2 groups may
         // still be on their way; loads complete in order), and past the barrier every wavefront has group g in registers,
         // so its buffers take group g + STAGES / U while the fragments of g + 1 are read under the products of g.
@@ -727,7 +729,9 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     }
 }
 
-// Whether a layer gets the 256 x 256 bf16 tile of conv_large.inc for the sake of what that alone can fuse (predictors).
+// Whether a layer gets the 256 x 256 bf16 tile of conv_large.inc for the sake of the predictors that it alone can fuse.  The 200
+// tiles are from the loop that this tile had before; with the present one a launch pays from fewer on, and the line has not been
+// moved yet (3x3 256 -> 256 with predictors, one launch / two in us: 96 tiles 43.0 / 39.0, 128 tiles 44.8 / 46.3, 160 tiles 50.9 / 61.2).
 static bool takes_large_tile(const ConvArgs& a) {
     const long long M = (long long)a.N * a.Ho * a.Wo;
     const long long K = (long long)a.kh * a.kw * a.Cin;
@@ -802,16 +806,20 @@ static long long tile_rounds(const ConvArgs& a, int bm, int bn) {
     return (((M + bm - 1) / bm) * ((a.Cout + bn - 1) / bn) + 255) / 256;
 }
 
-// Calls with few pixels.  A 128 x 128 tile takes 0.64 us per K step (64 bf16 / 32 fp32 of every row) however few blocks
-// there are, because a block waits for the one tile it has in flight; the ring tiles take, per K step and round of 256
+// Calls with few pixels.  A 128 x 128 tile of two operand tiles takes 0.64 us per K step (64 bf16 / 32 fp32 of every row) however few
+// blocks there are, because a block waits for the one tile it has in flight; the ring tiles take, per K step and round of 256
 // blocks: 32 x 64 0.16 us, 64 x 64 0.24, 64 x 128 0.31, 128 x 128 0.49 (measured at K 12544; 0.13, 0.20, 0.28, 0.49 since reads
-// stand between the products, which gives the same order from K 1024 on).  The rule takes the cheapest by the first count.  Measured in us, two-buffer tile / ring tile: 300 x 1024, K 12544: 128 / 32 (32 x 64);
-// 900: 212 / 47 (64 x 64); 1500: 212 / 67 (64 x 128); 2400: 212 / 98 (128 x 128); 3x3 256 -> 256: 2 040 pixels
-// 24.6 / 10.8, 8 160 26 / 17.5; 3x3 512 -> 512: 510 pixels 45 / 17.4, 4 080 55 / 30, 8 160 60 / 47.  More than 256 tiles
+// stand between the products, which gives the same order from K 1024 on).  The rule takes the cheapest by the first count.
+// Measured in us, two-buffer tile / ring tile: K 12544 to 1024 channels: 300 rows 127 / 28 (32 x 64), 1 020 128 / 42 (64 x 64), 1 500
+// 125 / 56 (64 x 128), 3 000 124 / 92 (128 x 128); 3x3 256 -> 256: 2 040 pixels 24 / 9.3, 8 160 25 / 15.6; 3x3 512 -> 512: 510
+// pixels 44 / 12.5, 4 080 54 / 26, 8 160 56 / 47.5.  From K 768 on what a layer takes without the ring is one of the large tiles; the
+// rule does not ask for their time, which is no less in all but the last sizes of the range (best large tile / ring tile: 300 rows
+// 85 / 28, 1 500 86 / 56, 3 000 91 / 92; 3x3 256 -> 256: 8 160 pixels 25 / 15.6, 12 240 25 / 22.4, 16 320 26 / 24.2; 3x3 512 -> 512: 4 080
+// pixels 44 / 26, 8 160 49.8 / 47.5; 1024 -> 256: 8 160 pixels 11.2 / 8.1, 16 320 13.3 / 15.1).  Below K 512 more than 256 tiles
 // of 128 x 128 run two blocks per CU and overlap each other: no ring tile is faster there.  The count holds for long K; for
 // short K a launch is set-up and epilogue, of which one large block per CU hides nothing.  So 64 x 128 runs from K 512 and in
-// one round only (256 channels: 8 160 pixels K 512 10.2 / 7.9, K 704 12.5 / 9.1; in two rounds, 8 500 pixels, K 512 10.2 / 11.6,
-// K 704 12.7 / 13.6), and 128 x 128 from K 768 (K 768 13.5 / 12.1, K 1024 16.8 / 13.9).  64 x 64 pays from K 256 in up to two rounds
+// one round only (256 channels, 8 160 pixels, two-buffer tile / ring tile: K 512 7.5 / 6.1, K 768 9.3 / 7.4), and 128 x 128 from K 768,
+// where the two are even (9 000 pixels: K 768 9.4 / 9.7, K 1024 11.0 / 11.3; 12 240 pixels, K 2304 25.6 / 22.4).  64 x 64 pays from K 256 in up to two rounds
 // (8 160 pixels, 256 channels, K 256 7.0 / 6.4, K 448 9.3 / 7.7).  Below K 256 the detectors have K 64 and 128 only, the streaming
 // tile's; at K 192 the small tiles would pay too (2 040 pixels, 256 channels 5.4 / 4.0).  Up to 256 tiles of 32 x 32 (four
 // wavefronts of one 16x16 tile, K tiles of 8 KB) that tile is the one that uses most CUs, 32 x 64 / 32 x 32: 510 pixels, 3x3 512 -> 512 14.9 /
@@ -872,7 +880,7 @@ static hipError_t launch_out_f32(const ConvArgs& a, hipStream_t s) {
 // Layers with more pixels.  A round of 256 blocks of a large tile takes, in 1/100 us, step for every K tile and fixed for what does
 // not grow with K (set-up, first operands, epilogue, stores); a last round that is not full costs less, its blocks having the
 // caches and the power budget of the others.  The tile with the least sum is taken, the larger one if they are equal.  Measured
-// in us, 256 x 256 / 192 x 256 / 256 x 128 / 192 x 128 / 128 x 128 (two blocks per CU, what these layers ran on): K 12544 to 1024
+// in us, 256 x 256 / 192 x 256 / 256 x 128 / 192 x 128 / 128 x 128 (two buffers, two blocks per CU): K 12544 to 1024
 // channels: 9 600 rows 228 / 199 / 254 / 268 / 274, 4 800 198 / 168 / 124 / 118 / 175; K 1024, 9 600 rows 27 / 23 / 29 / 25 / 30; 3x3
 // 512 -> 512: 16 320 pixels 90 / 81 / 72 / 105 / 94, 12 544 80 / 69 / 62 / 98 / 85, 50 176 192 / 234 / 243 / 261 / 247; 3x3 256 -> 256:
 // 32 640 49 / 44 / 38 / 58 / 49, 130 560 123 / 141 / 146 / 185 / 147; 3x3 128 -> 128, 802 816: - / - / 273 / 306 / 307.  Below K 512 a launch is

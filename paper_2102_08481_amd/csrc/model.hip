@@ -607,8 +607,9 @@ int run_stage(thia_model* m, int s, int nb, Trunk& t, const Tail* tail = nullptr
         }
         if (!(bi == 0 && skip_c1)) TRY(run_conv(m, THIA_K_CONV, B.c1, x, nb, h, w, 1, 0, nullptr, true, false, ws.act[2]));
         if (B.t3f && m->fuse_blocks && !B.has_sc && B.stride == 1) {
-            // 3x3 and the last 1x1 (+ residual) in one launch: the 256-channel tensor between them stays in LDS.  Worth it
-            // only where the 3x3 runs on the large tile anyway (enough 256-pixel tiles to fill the chip).
+            // 3x3 and the last 1x1 (+ residual) in one launch: the 256-channel tensor between them stays in LDS.  The 200 tiles are
+            // where it paid with the loop that the large tile had before; now one launch / two take (us) 67.2 / 65.7 at 104 tiles of
+            // 256 pixels, 68.4 / 76.9 at 128, 84.7 / 104.9 at 192, and the line has not been moved yet.
             ConvArgs a;
             fill_conv_args(m, a, B.c2, ws.act[2], nb, h, w, 1, 1, nullptr, true, ws.act[3], nullptr, -1, nullptr);
             a.tail_w = B.t3f; a.tail_b = B.c3.b; a.tail_res = x; a.tail_out = y; a.tail_n = B.c3.co;
