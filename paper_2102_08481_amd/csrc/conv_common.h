@@ -1,4 +1,4 @@
-// Element, fragment and matrix-instruction helpers shared by the layer kernels (conv_igemm.hip, conv_large.inc).
+// Element, fragment and matrix-instruction helpers shared by the layer kernels (conv_igemm.hip, conv_large.h).
 #pragma once
 #include <type_traits>
 

@@ -6,7 +6,7 @@
 // n = output channel and k = (ky, kx, ci); activations are NHWC so a K tile of one
 // filter tap is a contiguous run of input channels of one input pixel.
 //
-// Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.inc, chosen
+// Tiling: a block owns BM pixels x BN channels (32 x 32 to 128 x 128 here, 192 x 128 to 256 x 256 in conv_large.h, chosen
 // by the layer's size in launch_conv) and walks K in 128-byte steps (64 bf16 / 32 fp32 per row).  Operand tiles go from
 // global memory straight into LDS, two buffers requested by the multiplying wavefronts or, in calls with few pixels, a ring
 // of 4 to 16 filled by wavefronts of its own; the streaming tile of the short-K layers (64-byte rows) stages them in registers.  Each wavefront owns part of
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(64 * (WAVES_M * WAVES_N + PROD), BKB == 64 ? 4 : 1)
     }
 }
 
-// Whether a layer gets the 256 x 256 bf16 tile of conv_large.inc for the sake of the predictors that it alone can fuse.  The 200
+// Whether a layer gets the 256 x 256 bf16 tile of conv_large.h for the sake of the predictors that it alone can fuse.  The 200
 // tiles are from the loop that this tile had before; with the present one a launch pays from fewer on, and the line has not been
 // moved yet (3x3 256 -> 256 with predictors, one launch / two in us: 96 tiles 43.0 / 39.0, 128 tiles 44.8 / 46.3, 160 tiles 50.9 / 61.2).
 static bool takes_large_tile(const ConvArgs& a) {
@@ -939,4 +939,4 @@ hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream
 }  // namespace thia
 
 // The kernel of the large tiles: part of this translation unit, so that whoever links the layer kernels needs one object.
-#include "conv_large.inc"
+#include "conv_large.h"

@@ -116,7 +116,7 @@ struct ConvArgs {
 hipError_t launch_conv(const ConvArgs& a, int precision, bool out_f32, hipStream_t s);
 // Shapes the kernel accepts.
 bool conv_supported(const ConvArgs& a, int precision);
-// The kernel of the large tiles (conv_large.inc), bm = 256 or 192 pixels x bn = 256 or 128 channels, and the shapes it accepts.
+// The kernel of the large tiles (conv_large.h), bm = 256 or 192 pixels x bn = 256 or 128 channels, and the shapes it accepts.
 hipError_t launch_conv_large(const ConvArgs& a, int bm, int bn, hipStream_t s);
 bool conv_large_supported(const ConvArgs& a, int precision, int bm, int bn);
 // True if launch_conv would run `a` (bf16, with head_* set) on the kernel variant that has the fused predictors.
